@@ -1259,39 +1259,16 @@ int lion_get_energy(lion_sim* s, double* kinetic, double* coulomb, double* dc_tr
     if (check_handle(s)) return LION_ERR_ARG;
     if (!s->state_set) return fail(s, LION_ERR_STATE, "lion_set_state has not been called");
     LION_HIP(s, hipSetDevice(s->device));
-    const int64_t n = s->n;
     hipStream_t st = s->stream;
-    LION_HIP(s, lion::launch_coulomb_potential(s->d, s->n_traps, st));
-    std::vector<double> pe(n), vx(n), vy(n), vz(n);
-    std::vector<double4> src(n);
-    LION_HIP(s, hipMemcpyAsync(pe.data(), s->d.scratch, n * 8, hipMemcpyDeviceToHost, st));
-    LION_HIP(s, hipMemcpyAsync(src.data(), s->d.src, n * sizeof(double4), hipMemcpyDeviceToHost, st));
-    LION_HIP(s, hipMemcpyAsync(vx.data(), s->d.vx, n * 8, hipMemcpyDeviceToHost, st));
-    LION_HIP(s, hipMemcpyAsync(vy.data(), s->d.vy, n * 8, hipMemcpyDeviceToHost, st));
-    LION_HIP(s, hipMemcpyAsync(vz.data(), s->d.vz, n * 8, hipMemcpyDeviceToHost, st));
+    double* sums = nullptr;
+    double e[3] = {0.0, 0.0, 0.0};
+    LION_HIP(s, lion::launch_energy(s->d, s->n_traps, &sums, st));
+    LION_HIP(s, hipMemcpyAsync(e, sums, sizeof(e), hipMemcpyDeviceToHost, st));
     LION_HIP(s, hipStreamSynchronize(st));
-    // compensated host sums
-    auto add = [](double& sum, double& c, double v) {
-        double t = sum + v;
-        c += std::fabs(sum) >= std::fabs(v) ? (sum - t) + v : (v - t) + sum;
-        sum = t;
-    };
     const double ke_e2 = lion::kElementaryCharge * lion::kElementaryCharge / (4.0 * lion::kPi * lion::kEps0);
-    double K = 0, Kc = 0, C = 0, Cc = 0, D = 0, Dc = 0;
-    for (int k = 0; k < s->n_traps; ++k) {
-        const double a_dc = s->traps[k].a_dc, ps = s->traps[k].ps;
-        for (int64_t i = s->offsets[k]; i < s->offsets[k + 1]; ++i) {
-            const double m = s->mass[i], q = s->charge[i];
-            add(K, Kc, 0.5 * m * (vx[i] * vx[i] + vy[i] * vy[i] + vz[i] * vz[i]));
-            add(C, Cc, 0.5 * ke_e2 * (q / lion::kElementaryCharge) * pe[i]);
-            const double4 p = src[i];
-            add(D, Dc, q * a_dc * (p.z * p.z - 0.5 * (p.x * p.x + p.y * p.y)));
-            if (ps != 0.0) add(D, Dc, 0.5 * q * (q / m) * ps * (p.x * p.x + p.y * p.y));
-        }
-    }
-    if (kinetic) *kinetic = K + Kc;
-    if (coulomb) *coulomb = C + Cc;
-    if (dc_trap) *dc_trap = D + Dc;
+    if (kinetic) *kinetic = e[0];
+    if (coulomb) *coulomb = ke_e2 * e[1];
+    if (dc_trap) *dc_trap = e[2];
     return LION_OK;
 }
 

@@ -153,7 +153,7 @@ struct DevState {
     double* mass;     // kg
     int32_t* trap_of; // trap index per ion
     double* part;     // [j_split][3][n_pad] partial field sums
-    double* scratch;  // [n_pad] per-ion diagnostics
+    double* scratch;  // [n_pad] partial sums of the energies
     TrapDev* traps;   // [n_traps]
     int64_t* offsets; // [n_traps + 1]
     int32_t* order;   // [n_traps] launch order (largest trap first)
@@ -256,7 +256,9 @@ int eigh_device(void* h, double* A, int m, double* W, double* E, int* info, bool
 hipError_t launch_rows(const DevState& s, int precision, const LaunchShape& ls, int mode,
                        int k_in_chunk, int parity_in, bool home_out, hipStream_t st);
 hipError_t launch_counter_add(const DevState& s, int64_t k, hipStream_t st);
-hipError_t launch_coulomb_potential(const DevState& s, int n_traps, hipStream_t st);
+// Energies of all traps: *out is the device address of {kinetic (J), sum over
+// pairs of q_i q_j / r_ij (e^2/m), static trap energy (J)}.
+hipError_t launch_energy(const DevState& s, int n_traps, double** out, hipStream_t st);
 hipError_t launch_check_finite(const DevState& s, hipStream_t st);
 // Counts ions beyond r_lost (m) of the trap centre, or non-finite, into flags[1].
 hipError_t launch_count_lost(const DevState& s, double r_lost, hipStream_t st);
