@@ -96,10 +96,18 @@ int slices_for(int64_t n) {
     return std::max(j_max_for(n), nb <= lion::kMaxSymTiles ? nb : 0);
 }
 
+// Bath kicks drawn ahead of the steps: half-steps per launch of the draws, at
+// most 2^21 ion half-steps (50 MB) and 1024 half-steps, at least the three that
+// the start and the first step of a chunk need.
+int64_t noise_stride_for(int64_t n) { return round_up(n, 64); }
+int noise_half_steps(int64_t n) {
+    return (int)std::max<int64_t>(3, std::min<int64_t>(1024, (int64_t(1) << 21) / noise_stride_for(n)));
+}
+
 struct Layout {
     size_t src, srcm, v, a, qm, qe, mass, trap_of, part, scratch, traps, offsets, order, counter,
         flags, body_code, tile_body, tile_brange, body_gmin, body_gmax, cool, species, vacc, vavg, rigid, rb, dbody,
-        rmembers, rstart, minst, minpart, src2, srcm2, total;
+        rmembers, rstart, minst, minpart, src2, srcm2, noise_c, noise, total;
 };
 
 Layout layout_for(int64_t n, int32_t n_traps, int precision, bool batched) {
@@ -146,6 +154,8 @@ Layout layout_for(int64_t n, int32_t n_traps, int precision, bool batched) {
     // second position buffers of the one-launch step (single trap)
     L.src2 = batched ? SIZE_MAX : take(np * sizeof(double4));
     L.srcm2 = (precision != LION_FP64 && !batched) ? take(np * sizeof(lion::MixedSrc)) : SIZE_MAX;
+    L.noise_c = take(noise_stride_for(n) * sizeof(double));
+    L.noise = take((size_t)noise_half_steps(n) * 3 * noise_stride_for(n) * sizeof(double));
     L.total = o;
     return L;
 }
@@ -246,6 +256,17 @@ int upload_traps(lion_sim* s) {
     return LION_OK;
 }
 
+// Captured graphs hold the kernels built with or without cooling, and the draws
+// of the baths only while one is on.
+int switch_cooling(lion_sim* s, bool on, bool baths) {
+    if (on == s->ls.cool_on && baths == s->ls.bath_on) return LION_OK;
+    LION_HIP(s, hipStreamSynchronize(s->stream));  // no launch of a graph still pending
+    clear_graphs(s);
+    s->ls.cool_on = on;
+    s->ls.bath_on = baths;
+    return LION_OK;
+}
+
 // Half-step factors of the beams and baths for step size dt, and the run-wide
 // step count, into device memory.  Uses one dt for every trap (the first).
 int upload_cooling(lion_sim* s, double dt) {
@@ -277,13 +298,9 @@ int upload_cooling(lion_sim* s, double dt) {
     C.step_base = s->steps_done;
     C.avg_window = s->avg_window;
     C.avg_origin = s->avg_origin;
-    // captured graphs hold the kernels built with or without these features
     const bool on = C.nbeams > 0 || C.nbaths > 0 || C.avg_window > 0;
-    if (on != s->ls.cool_on) {
-        LION_HIP(s, hipStreamSynchronize(s->stream));  // no launch of a graph still pending
-        clear_graphs(s);
-        s->ls.cool_on = on;
-    }
+    int rc = switch_cooling(s, on, C.nbaths > 0);
+    if (rc) return rc;
     LION_HIP(s, hipMemcpyAsync(s->d.cool, &s->cool, sizeof(lion::CoolDev), hipMemcpyHostToDevice,
                                s->stream));
     return LION_OK;
@@ -322,39 +339,67 @@ int refresh_accel(lion_sim* s) {
     }
     if (rows_active(s)) {
         LION_HIP(s, lion::launch_rows(s->d, s->precision, s->ls, lion::kModeAccel, 0, 0, true,
-                                      s->stream));
+                                      0, s->stream));
         return LION_OK;
     }
     LION_HIP(s, lion::launch_pair(s->d, s->precision, s->ls, false, s->stream));
-    LION_HIP(s, lion::launch_update(s->d, s->precision, s->ls, lion::kModeAccel, false, s->stream));
+    LION_HIP(s, lion::launch_update(s->d, s->precision, s->ls, lion::kModeAccel, false, 0, s->stream));
     return LION_OK;
+}
+
+// L steps of the kernels that step a trap inside one workgroup, as many per
+// launch as the bath table holds half-steps of.
+hipError_t enqueue_one_workgroup(lion_sim* s, int64_t L, hipStream_t st) {
+    const int64_t most = s->ls.bath_on ? s->d.noise_h / 2 : L;
+    hipError_t e = hipSuccess;
+    for (int64_t done = 0; done < L && e == hipSuccess;) {
+        const int64_t K = std::min(most, L - done);
+        if (s->ls.bath_on) e = lion::launch_noise(s->d, 2, (int)(2 * K), st);
+        if (e == hipSuccess)
+            e = lion::launch_batch(s->d, s->precision, s->n_traps, s->max_trap, s->ls, (int)K, 0, st);
+        if (e == hipSuccess) e = lion::launch_counter_add(s->d, K, st);
+        done += K;
+    }
+    return e;
 }
 
 // Kernels of one chunk of L steps on stream st.
 hipError_t enqueue_chunk(lion_sim* s, int64_t L, hipStream_t st) {
-    hipError_t e;
-    if (s->batched) {
-        e = lion::launch_batch(s->d, s->precision, s->n_traps, s->max_trap, s->ls, (int)L, 0, st);
-        if (e != hipSuccess) return e;
-        return lion::launch_counter_add(s->d, L, st);
-    }
+    hipError_t e = hipSuccess;
+    if (s->batched) return enqueue_one_workgroup(s, L, st);
     if (small_path_active(s)) {
-        // the whole trap inside one workgroup, L steps per launch
-        e = lion::launch_batch(s->d, s->precision, 1, (int)s->n, s->ls, (int)L, 0, st);
-        if (e == hipSuccess) e = lion::launch_counter_add(s->d, L, st);
+        // the whole trap inside one workgroup
+        e = enqueue_one_workgroup(s, L, st);
         if (e == hipSuccess && s->d.srcm) e = lion::launch_pack_mixed(s->d, st);
         return e;
     }
     const bool rigid = s->d.nbodies > 0;
+    // bath table: the first block holds the drift's half-step and those of the
+    // steps that follow, later blocks whole steps; step k (from 1) ends with its
+    // second half at bath_at(k) and the next step's first half behind it
+    const int64_t per = (s->d.noise_h - 1) / 2;  // steps per block
+    auto bath_at = [&](int64_t k) { return (int)(2 * ((k - 1) % per) + (k <= per ? 1 : 0)); };
+    // the draws of step k's block when it starts one (steps: steps completed by
+    // the device's counter when the launch runs)
+    auto draws = [&](int64_t k, int64_t steps) {
+        if (!s->ls.bath_on || (k - 1) % per != 0) return hipSuccess;
+        const int64_t K = std::min(per, L - (k - 1));
+        const int first = k == 1 ? 1 : 0;
+        return lion::launch_noise(s->d, (int)(2 * (k - steps) + 1 - first), (int)(2 * K) + first, st);
+    };
+    e = draws(1, 0);
+    if (e != hipSuccess) return e;
     if (rows_active(s)) {
         // one launch per step; positions alternate between the two buffers and
         // the last step of the chunk leaves them in the first
-        e = lion::launch_drift(s->d, s->ls.cool_on, st);
+        e = lion::launch_drift(s->d, s->ls.cool_on, 0, st);
         for (int64_t k = 0; k < L && e == hipSuccess; ++k) {
             const bool last = k + 1 == L;
-            e = lion::launch_rows(s->d, s->precision, s->ls,
-                                  last ? lion::kModeEnd : lion::kModeEndDrift, (int)k,
-                                  (int)(k & 1), last, st);
+            if (k > 0) e = draws(k + 1, 0);
+            if (e == hipSuccess)
+                e = lion::launch_rows(s->d, s->precision, s->ls,
+                                      last ? lion::kModeEnd : lion::kModeEndDrift, (int)k,
+                                      (int)(k & 1), last, bath_at(k + 1), st);
         }
         if (e == hipSuccess) e = lion::launch_counter_add(s->d, L, st);
         return e;
@@ -364,7 +409,7 @@ hipError_t enqueue_chunk(lion_sim* s, int64_t L, hipStream_t st) {
         e = lion::launch_rigid_wrench(s->d, false, st);
         if (e != hipSuccess) return e;
     }
-    e = lion::launch_drift(s->d, s->ls.cool_on, st);
+    e = lion::launch_drift(s->d, s->ls.cool_on, 0, st);
     if (e != hipSuccess) return e;
     if (rigid) {
         e = lion::launch_rigid_drift(s->d, st);
@@ -372,10 +417,11 @@ hipError_t enqueue_chunk(lion_sim* s, int64_t L, hipStream_t st) {
         if (e != hipSuccess) return e;
     }
     for (int64_t k = 0; k < L; ++k) {
-        e = lion::launch_pair(s->d, s->precision, s->ls, true, st);
+        if (k > 0) e = draws(k + 1, k);  // the pair kernel counts the steps
+        if (e == hipSuccess) e = lion::launch_pair(s->d, s->precision, s->ls, true, st);
         if (e != hipSuccess) return e;
         const int mode = (k + 1 < L) ? lion::kModeEndDrift : lion::kModeEnd;
-        e = lion::launch_update(s->d, s->precision, s->ls, mode, true, st);
+        e = lion::launch_update(s->d, s->precision, s->ls, mode, true, bath_at(k + 1), st);
         if (e != hipSuccess) return e;
         if (rigid) {
             e = lion::launch_rigid_wrench(s->d, true, st);
@@ -430,10 +476,15 @@ int run_chunk(lion_sim* s, int64_t L) {
 
 // Whether the cooling kernels are needed by the current beams, baths and time
 // average (the launch graphs hold kernels built with or without them).
-bool cooling_on(const lion_sim* s) {
-    bool on = s->avg_window > 0;
-    for (const auto& B : s->beams) on = on || B.gamma > 0.0;
+bool baths_on(const lion_sim* s) {
+    bool on = false;
     for (const auto& T : s->baths) on = on || T.tau > 0.0;
+    return on;
+}
+
+bool cooling_on(const lion_sim* s) {
+    bool on = s->avg_window > 0 || baths_on(s);
+    for (const auto& B : s->beams) on = on || B.gamma > 0.0;
     return on;
 }
 
@@ -445,7 +496,7 @@ hipError_t enqueue_min_chunk(lion_sim* s, int64_t K, hipStream_t st) {
         if (e == hipSuccess) e = lion::launch_min_move(s->d, s->precision, st);
         if (e == hipSuccess) e = lion::launch_pair(s->d, s->precision, s->ls, false, st);
         if (e == hipSuccess)
-            e = lion::launch_update(s->d, s->precision, s->ls, lion::kModeAccel, false, st);
+            e = lion::launch_update(s->d, s->precision, s->ls, lion::kModeAccel, false, 0, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -560,6 +611,10 @@ int create_common(lion_sim** out, int32_t n_traps, const int64_t* n_per_trap, in
     d.minpart = (double*)(base + L.minpart);
     d.src2 = L.src2 == SIZE_MAX ? nullptr : (double4*)(base + L.src2);
     d.srcm2 = L.srcm2 == SIZE_MAX ? nullptr : (lion::MixedSrc*)(base + L.srcm2);
+    d.noise_c = (double*)(base + L.noise_c);
+    d.noise = (double*)(base + L.noise);
+    d.noise_stride = noise_stride_for(n);
+    d.noise_h = noise_half_steps(n);
     d.nbodies = 0;  // set by lion_set_rigid_bodies
     d.rigid = nullptr;
     d.rb = nullptr;
@@ -1100,12 +1155,8 @@ int lion_prepare_step(lion_sim* s, int64_t nsteps) {
     if (nsteps < 0) return fail(s, LION_ERR_ARG, "nsteps must be >= 0");
     if (nsteps == 0 || s->cfg.use_graph == 2) return LION_OK;
     LION_HIP(s, hipSetDevice(s->device));
-    const bool on = cooling_on(s);
-    if (on != s->ls.cool_on) {
-        LION_HIP(s, hipStreamSynchronize(s->stream));  // no launch of a graph still pending
-        clear_graphs(s);
-        s->ls.cool_on = on;
-    }
+    int rc_cool = switch_cooling(s, cooling_on(s), baths_on(s));
+    if (rc_cool) return rc_cool;
     const int64_t S = chunk_len(s);
     hipGraphExec_t ex = nullptr;
     if (nsteps >= S) {
@@ -1442,8 +1493,7 @@ int lion_time_batch_kernel(lion_sim* s, int32_t reps, int32_t nsteps, double dt,
     }
     if (hipEventRecord(e0, st) != hipSuccess) rc = fail(s, LION_ERR_HIP, "hipEventRecord failed");
     for (int r = 0; r < reps && rc == LION_OK; ++r) {
-        if (lion::launch_batch(s->d, s->precision, s->n_traps, s->max_trap, s->ls, nsteps, 0, st) != hipSuccess ||
-            lion::launch_counter_add(s->d, nsteps, st) != hipSuccess)
+        if (enqueue_one_workgroup(s, nsteps, st) != hipSuccess)
             rc = fail(s, LION_ERR_HIP, "batch kernel timing launch failed");
     }
     if (rc == LION_OK && hipEventRecord(e1, st) != hipSuccess) rc = fail(s, LION_ERR_HIP, "hipEventRecord failed");

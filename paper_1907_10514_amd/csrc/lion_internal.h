@@ -161,6 +161,10 @@ struct DevState {
     int32_t* flags;   // [4] diagnostics (non-finite count)
     CoolDev* cool;    // beams, baths and the velocity time average
     int32_t* species; // [n_pad] species label per ion (default 0)
+    double* noise_c;  // [noise_stride] bath factor per ion and half-step
+    double* noise;    // [noise_h][3][noise_stride] bath kicks of the half-steps ahead
+    int64_t noise_stride;
+    int noise_h;      // half-steps the table holds (>= 3)
     double* vacc;     // [3][n_pad] velocity sums of the open averaging window
     double* vavg;     // [3][n_pad] average of the last completed window
     MinDev* minst;       // minimisation state
@@ -199,6 +203,7 @@ struct LaunchShape {
     bool cool_on;     // a beam, bath or time average is on: the kernels built with them run
     double uniform_q;  // every ion's charge in units of e when all are equal, else 0
     int sym_masked;    // pair-once kernels with the per-pair body test (bodies share tiles)
+    bool bath_on;      // a bath is on: launch_noise goes ahead of the steps
     int rows;          // one launch per step (k_rows) for the single trap
     int rows_tr;       // targets per workgroup of that launch: 2, 4 or 8
 };
@@ -214,11 +219,18 @@ constexpr int64_t kSymDefaultIons = 8192;
 constexpr int64_t kSymDefaultIonsMixed = 8192;
 
 // Kernel launchers (lion_kernels.hip).  All return hipSuccess or the launch error.
-hipError_t launch_drift(const DevState& s, bool cool_on, hipStream_t st);
+// Bath kicks of half_steps (<= s.noise_h) half-steps into the table, from the
+// half-step 2 (steps completed before the launch) + g0 on; half-step 2 s + h is
+// half h of the run-wide step s (from 1).
+hipError_t launch_noise(const DevState& s, int g0, int half_steps, hipStream_t st);
+// bath_idx: table index of the step's first half (launch_drift) or of the second
+// half of the step that ends (launch_update, launch_rows; the first half of the
+// next step follows it).
+hipError_t launch_drift(const DevState& s, bool cool_on, int bath_idx, hipStream_t st);
 hipError_t launch_pair(const DevState& s, int precision, const LaunchShape& ls, bool count_step,
                        hipStream_t st);
 hipError_t launch_update(const DevState& s, int precision, const LaunchShape& ls, int mode,
-                         bool use_counter, hipStream_t st);
+                         bool use_counter, int bath_idx, hipStream_t st);
 hipError_t launch_pack_mixed(const DevState& s, hipStream_t st);
 // Device arrays x, y, z, charge (C), mass (kg) of s.n ions into s.src, s.srcm
 // (if set), s.qm, s.qe (zero charge up to s.n_pad) and T into s.traps[0].
@@ -227,6 +239,8 @@ hipError_t launch_pack_inputs(const double* x, const double* y, const double* z,
                               const TrapDev& T, hipStream_t st);
 // Message returned by lion_last_error(NULL) (calls without a handle).
 void set_handle_free_error(const std::string& msg);
+// Steps of a batch (or a lone trap in one workgroup); with a bath on, the table
+// holds the 2 nsteps half-steps from index 0.
 hipError_t launch_batch(const DevState& s, int precision, int n_traps, int max_trap,
                         const LaunchShape& ls, int nsteps, int mode_first, hipStream_t st);
 hipError_t launch_batch_accel(const DevState& s, int precision, int n_traps, int max_trap,
@@ -254,7 +268,8 @@ int eigh_device(void* h, double* A, int m, double* W, double* E, int* info, bool
 // launch: positions read from buffer parity_in (0: src/srcm, 1: src2/srcm2);
 // drifted positions written to the other buffer, or with home_out to buffer 0.
 hipError_t launch_rows(const DevState& s, int precision, const LaunchShape& ls, int mode,
-                       int k_in_chunk, int parity_in, bool home_out, hipStream_t st);
+                       int k_in_chunk, int parity_in, bool home_out, int bath_idx,
+                       hipStream_t st);
 hipError_t launch_counter_add(const DevState& s, int64_t k, hipStream_t st);
 // Energies of all traps: *out is the device address of {kinetic (J), sum over
 // pairs of q_i q_j / r_ij (e^2/m), static trap energy (J)}.

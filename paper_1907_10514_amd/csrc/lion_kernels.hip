@@ -265,11 +265,11 @@ __device__ __forceinline__ void bath_normals(uint64_t seed, int64_t ion, int64_t
     z2 = r2 * cos(2.0 * kPi * u4);
 }
 
-// The cooling and averaging switches, read once per launch: they cannot change
+// The beams and averaging switches, read once per launch: they cannot change
 // during one, and re-reading them after every barrier of an in-kernel step
 // loop costs more than the step's arithmetic for small traps.
 struct CoolRef {
-    const CoolDev* C;
+    const BeamDev* beams;
     int nb, nt, W;
     int64_t origin;
 };
@@ -277,57 +277,99 @@ struct CoolRef {
 // X = false: a kernel built with beams, baths and time averages compiled out
 // (all switches constant zero), launched while none of them is on.
 template <bool X>
-__device__ __forceinline__ CoolRef cool_switches(const CoolDev* __restrict__ C);
-
-__device__ __forceinline__ CoolRef load_cool(const CoolDev* __restrict__ C) {
-    CoolRef r;
-    r.C = C;
-    r.nb = C ? C->nbeams : 0;
-    r.nt = C ? C->nbaths : 0;
-    r.W = C ? C->avg_window : 0;
-    r.origin = C ? C->avg_origin : 0;
-    return r;
-}
-
-template <bool X>
 __device__ __forceinline__ CoolRef cool_switches(const CoolDev* __restrict__ C) {
     if constexpr (X) {
-        return load_cool(C);
+        return CoolRef{C->beams, C->nbeams, C->nbaths, C->avg_window, C->avg_origin};
     } else {
         return CoolRef{nullptr, 0, 0, 0, 0};
     }
 }
 
-// Velocity half-step: isotropic damping f, then beams, then baths (index order).
-__device__ __forceinline__ void velocity_half(const CoolRef& R, int64_t ion,
-                                              int32_t species, double mass, double f,
-                                              int64_t step, int half, double& u, double& v,
+// The baths of one ion in one velocity half-step as v <- c v + (nx, ny, nz).
+struct BathMap {
+    double c = 1.0, nx = 0.0, ny = 0.0, nz = 0.0;
+};
+
+// The maps of a sequence of half-steps, filled by k_noise ahead of the kernels
+// that step the ions: draws depend on the seed, ion and step only, so they need
+// not sit on a step's dependent chain.
+struct BathTable {
+    const double* __restrict__ c;  // [stride] factor per ion
+    const double* __restrict__ n;  // [half-steps][3][stride] kicks
+    int64_t stride;
+    __device__ __forceinline__ BathMap load(const CoolRef& R, int64_t ion, int idx) const {
+        BathMap m;
+        if (R.nt > 0) {
+            const double* p = n + (int64_t)(3 * idx) * stride + ion;
+            m.c = c[ion];
+            m.nx = p[0];
+            m.ny = p[stride];
+            m.nz = p[2 * stride];
+        }
+        return m;
+    }
+};
+
+// Velocity half-step: isotropic damping f, then beams, then baths.
+__device__ __forceinline__ void velocity_half(const CoolRef& R, int32_t species, double f,
+                                              const BathMap& B, double& u, double& v,
                                               double& w) {
 #pragma clang fp contract(off)
     u = f * u;
     v = f * v;
     w = f * w;
-    const int nb = R.nb, nt = R.nt;
-    if (nb == 0 && nt == 0) return;
-    const CoolDev* __restrict__ C = R.C;
-    for (int b = 0; b < nb; ++b) {
-        const BeamDev B = C->beams[b];
-        if (!B.on || (B.species >= 0 && B.species != species)) continue;
-        const double d = (1.0 - B.f) * (B.kx * u + B.ky * v + B.kz * w);
-        u = u - d * B.kx;
-        v = v - d * B.ky;
-        w = w - d * B.kz;
+    for (int b = 0; b < R.nb; ++b) {
+        const BeamDev b_ = R.beams[b];
+        if (!b_.on || (b_.species >= 0 && b_.species != species)) continue;
+        const double d = (1.0 - b_.f) * (b_.kx * u + b_.ky * v + b_.kz * w);
+        u = u - d * b_.kx;
+        v = v - d * b_.ky;
+        w = w - d * b_.kz;
     }
+    if (R.nt > 0) {
+        u = B.c * u + B.nx;
+        v = B.c * v + B.ny;
+        w = B.c * w + B.nz;
+    }
+}
+
+// Fills the bath table for the half-steps 2 (step_base + *counter) + g0 + idx,
+// idx = blockIdx.y (half-step 2 s + h is half h of the run-wide step s), one
+// thread per ion.  Bound by FP64 issue of log, sqrt, sin and cos and spread over
+// the whole chip: 100 ions x 400 half-steps take about as long as one launch.
+// With the draws inside the stepping kernels each step waited for two of them:
+// 100 ions, one bath, one beam and a time average 8.3 us a step against 3.6 now
+// (2.7 without cooling); 600 ions 11.0 against 7.2, 16000 ions 89 against 86.
+__global__ __launch_bounds__(256) void k_noise(const double* __restrict__ mass,
+                                               const int32_t* __restrict__ species, int64_t n,
+                                               int64_t stride, const CoolDev* __restrict__ C,
+                                               const int64_t* __restrict__ counter, int g0,
+                                               double* __restrict__ factor,
+                                               double* __restrict__ kicks) {
+#pragma clang fp contract(off)
+    const int64_t ion = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (ion >= n) return;
+    const int64_t h = 2 * (C->step_base + *counter) + g0 + blockIdx.y;
+    const int32_t sp = species[ion];
+    const double m = mass[ion];
+    const int nt = C->nbaths;
+    BathMap B;
     for (int c = 0; c < nt; ++c) {
         const BathDev T = C->baths[c];
-        if (!T.on || (T.species >= 0 && T.species != species)) continue;
-        const double sig = sqrt(T.kt / mass * T.omc2);
+        if (!T.on || (T.species >= 0 && T.species != sp)) continue;
+        const double sig = sqrt(T.kt / m * T.omc2);
         double z0, z1, z2;
-        bath_normals(T.seed, ion, step, c, half, z0, z1, z2);
-        u = T.c1 * u + sig * z0;
-        v = T.c1 * v + sig * z1;
-        w = T.c1 * w + sig * z2;
+        bath_normals(T.seed, ion, h >> 1, c, (int)(h & 1), z0, z1, z2);
+        B.nx = T.c1 * B.nx + sig * z0;
+        B.ny = T.c1 * B.ny + sig * z1;
+        B.nz = T.c1 * B.nz + sig * z2;
+        B.c = T.c1 * B.c;
     }
+    double* p = kicks + (int64_t)(3 * blockIdx.y) * stride + ion;
+    p[0] = B.nx;
+    p[stride] = B.ny;
+    p[2 * stride] = B.nz;
+    if (blockIdx.y == 0) factor[ion] = B.c;
 }
 
 // Velocity time average over windows of W steps: the velocity at the end of
@@ -356,15 +398,37 @@ __device__ __forceinline__ void time_average(const CoolRef& R, int64_t i,
     }
 }
 
-// First half of a step: velocity half-step (damping, beams, baths), half kick,
-// drift.  `step` numbers steps from 1 over the whole run.
-__device__ __forceinline__ void half_step_drift(const TrapDev& T, const CoolRef& C,
-                                                int64_t ion, int32_t species, double mass,
-                                                int64_t step, double& x, double& y, double& z,
-                                                double& vx, double& vy, double& vz, double ax,
-                                                double ay, double az) {
+// The same average inside a kernel that runs many steps, with the open window's
+// sums in registers: steps of the window done when `done` run-wide steps are
+// complete, and one step's velocity added (closes: it is the window's last).
+__device__ __forceinline__ int window_phase(const CoolRef& R, int64_t done) {
+    const int64_t p = (done - R.origin) % R.W;
+    return (int)(p < 0 ? p + R.W : p);
+}
+
+__device__ __forceinline__ void window_add(const CoolRef& R, bool closes, int64_t i,
+                                           int64_t n_pad, double* __restrict__ avg, double u,
+                                           double v, double w, double& s0, double& s1,
+                                           double& s2) {
 #pragma clang fp contract(off)
-    velocity_half(C, ion, species, mass, T.f, step, 0, vx, vy, vz);
+    s0 = s0 + u;
+    s1 = s1 + v;
+    s2 = s2 + w;
+    if (!closes) return;
+    avg[i] = s0 / (double)R.W;
+    avg[n_pad + i] = s1 / (double)R.W;
+    avg[2 * n_pad + i] = s2 / (double)R.W;
+    s0 = s1 = s2 = 0.0;
+}
+
+// First half of a step: velocity half-step (damping, beams, baths), half kick,
+// drift.
+__device__ __forceinline__ void half_step_drift(const TrapDev& T, const CoolRef& C,
+                                                int32_t species, const BathMap& B, double& x,
+                                                double& y, double& z, double& vx, double& vy,
+                                                double& vz, double ax, double ay, double az) {
+#pragma clang fp contract(off)
+    velocity_half(C, species, T.f, B, vx, vy, vz);
     vx = vx + T.h * ax;
     vy = vy + T.h * ay;
     vz = vz + T.h * az;
@@ -374,15 +438,14 @@ __device__ __forceinline__ void half_step_drift(const TrapDev& T, const CoolRef&
 }
 
 // Second half of a step: half kick with the new acceleration, velocity half-step.
-__device__ __forceinline__ void end_kick(const TrapDev& T, const CoolRef& C,
-                                         int64_t ion, int32_t species, double mass, int64_t step,
-                                         double& vx, double& vy, double& vz, double ax, double ay,
+__device__ __forceinline__ void end_kick(const TrapDev& T, const CoolRef& C, int32_t species,
+                                         const BathMap& B, double& vx, double& vy, double& vz, double ax, double ay,
                                          double az) {
 #pragma clang fp contract(off)
     vx = vx + T.h * ax;
     vy = vy + T.h * ay;
     vz = vz + T.h * az;
-    velocity_half(C, ion, species, mass, T.f, step, 1, vx, vy, vz);
+    velocity_half(C, species, T.f, B, vx, vy, vz);
 }
 
 // ------------------------------------------------------------------ kernels
@@ -396,22 +459,20 @@ __global__ __launch_bounds__(256) void k_drift(double4* __restrict__ src,
                                                const double* __restrict__ ay,
                                                const double* __restrict__ az,
                                                const double* __restrict__ qe,
-                                               const double* __restrict__ mass,
                                                const int32_t* __restrict__ species,
                                                const TrapDev* __restrict__ traps,
                                                const CoolDev* __restrict__ cool,
-                                               const int64_t* __restrict__ counter,
+                                               const BathTable bath, int bath_idx,
                                                const int32_t* __restrict__ rb, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     if (rb && rb[i] >= 0) return;  // rigid-body members move with their body
     const TrapDev T = traps[0];
-    const int64_t step = cool->step_base + *counter + 1;
+    const CoolRef cr = cool_switches<X>(cool);
     double4 p = src[i];
     double u = vx[i], v = vy[i], w = vz[i];
-    half_step_drift(T, cool_switches<X>(cool), i, species[i], mass[i], step, p.x, p.y, p.z, u,
-                    v, w, ax[i], ay[i],
-                    az[i]);
+    half_step_drift(T, cr, species[i], bath.load(cr, i, bath_idx), p.x, p.y, p.z, u, v, w, ax[i],
+                    ay[i], az[i]);
     src[i] = p;
     vx[i] = u;
     vy[i] = v;
@@ -1267,7 +1328,7 @@ void k_pair_f64_sym(const double4* __restrict__ src, const double* __restrict__ 
 // The per-ion inputs of the end of a step.
 struct IonIn {
     double4 p;  // position (w: the FP64 source weight, carried along)
-    double u, v, w, qm, qe, mass;
+    double u, v, w, qm, qe;
     int32_t sp;
 };
 
@@ -1277,7 +1338,6 @@ __device__ __forceinline__ IonIn load_ion(int64_t i, const double4* src_in,
                                           const double* __restrict__ vz,
                                           const double* __restrict__ qm,
                                           const double* __restrict__ qe,
-                                          const double* __restrict__ mass,
                                           const int32_t* __restrict__ species) {
     IonIn r;
     r.p = src_in[i];
@@ -1286,7 +1346,6 @@ __device__ __forceinline__ IonIn load_ion(int64_t i, const double4* src_in,
     r.w = vz[i];
     r.qm = qm[i];
     r.qe = qe[i];
-    r.mass = mass[i];
     r.sp = species[i];
     return r;
 }
@@ -1296,13 +1355,15 @@ __device__ __forceinline__ IonIn load_ion(int64_t i, const double4* src_in,
 // (mode kModeEnd) the closing half kick with damping, or (kModeEndDrift) also
 // the first half of the next step, whose position goes to src_out;
 // kModeAccel stores the acceleration only.  kc is the call's step counter
-// after this step (numbers the cooling draws).
+// after this step; b1 and b0 are the baths of this step's second half and of
+// the next step's first.
 template <bool X>
 __device__ __forceinline__ void end_step_vals(
     int mode, int64_t i, int64_t kc, const TrapDev& T, double c, double Sx, double Sy,
-    double Sz, IonIn in, double4* src_out, MixedSrc* __restrict__ srcm_out,
-    double* __restrict__ vx, double* __restrict__ vy, double* __restrict__ vz,
-    double* __restrict__ ax, double* __restrict__ ay, double* __restrict__ az, int64_t n_pad,
+    double Sz, IonIn in, const CoolRef& cr, const BathMap& b1, const BathMap& b0,
+    double4* src_out, MixedSrc* __restrict__ srcm_out, double* __restrict__ vx,
+    double* __restrict__ vy, double* __restrict__ vz, double* __restrict__ ax,
+    double* __restrict__ ay, double* __restrict__ az, int64_t n_pad,
     const CoolDev* __restrict__ cool, double* __restrict__ vacc, double* __restrict__ vavg) {
     double4 p = in.p;
     double a_x, a_y, a_z;
@@ -1311,14 +1372,12 @@ __device__ __forceinline__ void end_step_vals(
     ay[i] = a_y;
     az[i] = a_z;
     if (mode == kModeAccel) return;
-    const int64_t step = cool->step_base + kc;  // the step this epilogue completes
     double u = in.u, v = in.v, w = in.w;
-    const CoolRef cr = cool_switches<X>(cool);
-    end_kick(T, cr, i, in.sp, in.mass, step, u, v, w, a_x, a_y, a_z);
-    time_average(cr, i, n_pad, step, vacc, vavg, u, v, w);
+    end_kick(T, cr, in.sp, b1, u, v, w, a_x, a_y, a_z);
+    if constexpr (X)  // of the step this epilogue completes
+        time_average(cr, i, n_pad, cool->step_base + kc, vacc, vavg, u, v, w);
     if (mode == kModeEndDrift) {
-        half_step_drift(T, cr, i, in.sp, in.mass, step + 1, p.x, p.y, p.z, u, v, w, a_x, a_y,
-                        a_z);
+        half_step_drift(T, cr, in.sp, b0, p.x, p.y, p.z, u, v, w, a_x, a_y, a_z);
         src_out[i] = p;
         if (srcm_out) srcm_out[i] = make_src(p.x, p.y, p.z, in.qe);
     }
@@ -1336,14 +1395,17 @@ __device__ __forceinline__ void end_step_ion(
     double* __restrict__ vx, double* __restrict__ vy, double* __restrict__ vz,
     double* __restrict__ ax, double* __restrict__ ay, double* __restrict__ az,
     const double* __restrict__ qm, const double* __restrict__ qe,
-    const double* __restrict__ mass, const int32_t* __restrict__ species, int64_t n_pad,
-    const CoolDev* __restrict__ cool, double* __restrict__ vacc, double* __restrict__ vavg,
+    const int32_t* __restrict__ species, int64_t n_pad, const CoolDev* __restrict__ cool,
+    const BathTable& bath, int bath_idx, double* __restrict__ vacc, double* __restrict__ vavg,
     const int32_t* __restrict__ rb) {
-    const IonIn in = load_ion(i, src_in, vx, vy, vz, qm, qe, mass, species);
+    const IonIn in = load_ion(i, src_in, vx, vy, vz, qm, qe, species);
+    const CoolRef cr = cool_switches<X>(cool);
+    const BathMap b1 = bath.load(cr, i, bath_idx);
+    const BathMap b0 = mode == kModeEndDrift ? bath.load(cr, i, bath_idx + 1) : BathMap{};
     const double c = T.ps != 0.0 ? 0.0 : cos(T.omega * t);
     const int m = (mode != kModeAccel && rb && rb[i] >= 0) ? kModeAccel : mode;
-    end_step_vals<X>(m, i, kc, T, c, Sx, Sy, Sz, in, src_out, srcm_out, vx, vy, vz, ax, ay, az,
-                     n_pad, cool, vacc, vavg);
+    end_step_vals<X>(m, i, kc, T, c, Sx, Sy, Sz, in, cr, b1, b0, src_out, srcm_out, vx, vy, vz,
+                     ax, ay, az, n_pad, cool, vacc, vavg);
 }
 
 // Per-ion epilogue of a step (or a plain force evaluation): reduce the slice
@@ -1360,13 +1422,13 @@ __global__ __launch_bounds__(64 * UW) void k_update(double4* __restrict__ src,
                                                 double* __restrict__ ay, double* __restrict__ az,
                                                 const double* __restrict__ qm,
                                                 const double* __restrict__ qe,
-                                                const double* __restrict__ mass,
                                                 const int32_t* __restrict__ species,
                                                 const PT* __restrict__ part, int j_split,
                                                 int64_t n, int64_t n_pad, double field_scale,
                                                 const TrapDev* __restrict__ traps,
                                                 const CoolDev* __restrict__ cool,
                                                 const int64_t* __restrict__ counter,
+                                                const BathTable bath, int bath_idx,
                                                 double* __restrict__ vacc,
                                                 double* __restrict__ vavg,
                                                 const int32_t* __restrict__ rb) {
@@ -1403,8 +1465,8 @@ __global__ __launch_bounds__(64 * UW) void k_update(double4* __restrict__ src,
     const TrapDev T = traps[0];
     const double t = counter ? T.t_start + (double)(*counter) * T.dt : T.t_start;
     end_step_ion<X>(MODE, i, counter ? *counter : 0, T, t, Sx * field_scale, Sy * field_scale,
-                    Sz * field_scale, src, src, srcm, vx, vy, vz, ax, ay, az, qm, qe, mass,
-                    species, n_pad, cool, vacc, vavg, rb);
+                    Sz * field_scale, src, src, srcm, vx, vy, vz, ax, ay, az, qm, qe, species,
+                    n_pad, cool, bath, bath_idx, vacc, vavg, rb);
 }
 
 // ---------------------------------------------- one launch per step (mid-size traps)
@@ -1424,10 +1486,11 @@ struct RowsArgs {
     const MixedSrc* srcm_in;
     MixedSrc* srcm_out;
     double *vx, *vy, *vz, *ax, *ay, *az;
-    const double *qm, *qe, *mass;
+    const double *qm, *qe;
     const int32_t* species;
     const TrapDev* traps;
     const CoolDev* cool;
+    BathTable bath;
     const int64_t* counter;  // the call's step counter at the start of the chunk
     double *vacc, *vavg;
     int64_t n, n_pad;
@@ -1440,7 +1503,8 @@ __device__ __forceinline__ double wave_sum(double v) {
 }
 
 template <int PREC, int TR, bool X>
-__global__ __launch_bounds__(kRowsBlock) void k_rows(const RowsArgs A, int mode, int k_in_chunk) {
+__global__ __launch_bounds__(kRowsBlock) void k_rows(const RowsArgs A, int mode, int k_in_chunk,
+                                                     int bath_idx) {
     __shared__ double red[kRowsBlock / 64][3 * TR];
     const int64_t n = A.n;
     const int64_t i0 = (int64_t)blockIdx.x * TR;
@@ -1453,7 +1517,13 @@ __global__ __launch_bounds__(kRowsBlock) void k_rows(const RowsArgs A, int mode,
     const bool own = tid < TR && i0 + tid < n;
     IonIn me{};
     if (own)
-        me = load_ion(i0 + tid, A.src_in, A.vx, A.vy, A.vz, A.qm, A.qe, A.mass, A.species);
+        me = load_ion(i0 + tid, A.src_in, A.vx, A.vy, A.vz, A.qm, A.qe, A.species);
+    const CoolRef cr = cool_switches<X>(A.cool);
+    BathMap b1, b0;
+    if (own && counted) {
+        b1 = A.bath.load(cr, i0 + tid, bath_idx);
+        if (mode == kModeEndDrift) b0 = A.bath.load(cr, i0 + tid, bath_idx + 1);
+    }
     double sx[TR], sy[TR], sz[TR];
 #pragma unroll
     for (int k = 0; k < TR; ++k) sx[k] = sy[k] = sz[k] = 0.0;
@@ -1561,8 +1631,9 @@ __global__ __launch_bounds__(kRowsBlock) void k_rows(const RowsArgs A, int mode,
     }
     const double fs = PREC == 0 ? 1.0 : kMixedFieldScale;
     const int64_t i = i0 + k;
-    end_step_vals<X>(mode, i, kc, T, crf, Sx * fs, Sy * fs, Sz * fs, me, A.src_out, A.srcm_out,
-                     A.vx, A.vy, A.vz, A.ax, A.ay, A.az, A.n_pad, A.cool, A.vacc, A.vavg);
+    end_step_vals<X>(mode, i, kc, T, crf, Sx * fs, Sy * fs, Sz * fs, me, cr, b1, b0, A.src_out,
+                     A.srcm_out, A.vx, A.vy, A.vz, A.ax, A.ay, A.az, A.n_pad, A.cool, A.vacc,
+                     A.vavg);
     // the last step of a launch sequence leaves the positions in the home buffer
     if (mode == kModeEnd && A.src_out != A.src_in) {
         A.src_out[i] = me.p;
@@ -2062,10 +2133,10 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
                                                  double* __restrict__ az,
                                                  const double* __restrict__ qm,
                                                  const double* __restrict__ qe,
-                                                 const double* __restrict__ mass,
                                                  const int32_t* __restrict__ species,
                                                  const TrapDev* __restrict__ traps,
                                                  const CoolDev* __restrict__ cool,
+                                                 const BathTable bath,
                                                  const int64_t* __restrict__ offsets,
                                                  const int32_t* __restrict__ order,
                                                  const int64_t* __restrict__ counter,
@@ -2140,8 +2211,19 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
     const int wje = min(wjb + wlen, m16);
 
     double x[KMAX], y[KMAX], z[KMAX], u[KMAX], v[KMAX], w[KMAX], a0[KMAX], a1[KMAX], a2[KMAX];
-    double q_m[KMAX], q_e[KMAX], m_i[KMAX];
+    double q_m[KMAX], q_e[KMAX];
     int32_t sp[KMAX];
+    // with cooling: the beams and each owner's velocity sums of the open averaging
+    // window in LDS, the baths of the next half-step loaded ahead of it
+    __shared__ BeamDev beams[X ? kMaxBeams : 1];
+    __shared__ double sums[X ? 3 : 1][X ? KMAX * BLOCK : 1];
+    BathMap bath_next[X ? KMAX : 1];
+    CoolRef cr = cool_switches<X>(cool);
+    if constexpr (X) {
+        if (tid < cr.nb) beams[tid] = cr.beams[tid];
+        cr.beams = beams;
+        __syncthreads();
+    }
 #pragma unroll
     for (int k = 0; k < KMAX; ++k) {
         const int il = slot + IS * k;
@@ -2158,12 +2240,15 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
             a2[k] = az[o + il];
             q_m[k] = qm[o + il];
             q_e[k] = qe[o + il];
-            m_i[k] = mass[o + il];
             sp[k] = species[o + il];
+            if constexpr (X) {
+                if (cr.W > 0)
+                    for (int c = 0; c < 3; ++c) sums[c][k * BLOCK + tid] = vacc[c * n_pad + o + il];
+                if (!accel_only) bath_next[k] = bath.load(cr, o + il, 0);
+            }
         } else {
             x[k] = y[k] = z[k] = u[k] = v[k] = w[k] = a0[k] = a1[k] = a2[k] = 0.0;
             q_m[k] = q_e[k] = 0.0;
-            m_i[k] = 1.0;
             sp[k] = 0;
         }
     }
@@ -2172,8 +2257,8 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
     const int wjr0 = min(wjb, m), wjr1 = min(wje, m);
 
     const int total = accel_only ? 1 : nsteps;
-    const int64_t step0 = cool->step_base + k0 + 1;  // run-wide number of the first step
-    const CoolRef cr = cool_switches<X>(cool);
+    // steps of the open averaging window completed so far
+    int in_window = X && cr.W > 0 ? window_phase(cr, cool->step_base + k0) : 0;
     for (int step = 0; step < total; ++step) {
         if (step % kRf == 0 && T.ps == 0.0 && tid < kRf && step + tid < total) {
             // read after the barrier below
@@ -2186,9 +2271,11 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
         for (int k = 0; k < KMAX; ++k) {
             const int il = slot + IS * k;
             if (owner && il < m) {
-                if (!accel_only)
-                    half_step_drift(T, cr, o + il, sp[k], m_i[k], step0 + step, x[k], y[k],
-                                    z[k], u[k], v[k], w[k], a0[k], a1[k], a2[k]);
+                if (!accel_only) {
+                    half_step_drift(T, cr, sp[k], bath_next[X ? k : 0], x[k], y[k], z[k], u[k],
+                                    v[k], w[k], a0[k], a1[k], a2[k]);
+                    if constexpr (X) bath_next[k] = bath.load(cr, o + il, 2 * step + 1);
+                }
                 if constexpr (PREC == 0) {
                     lds[il] = make_double4(x[k], y[k], z[k], 1.5 * q_e[k]);
                 } else if constexpr (PREC == 1) {
@@ -2288,13 +2375,20 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
                 trap_accel_c(T, crf, q_m[k], x[k], y[k], z[k], Sx[k], Sy[k], Sz[k], a0[k],
                              a1[k], a2[k]);
                 if (!accel_only) {
-                    end_kick(T, cr, o + il, sp[k], m_i[k], step0 + step, u[k], v[k], w[k],
-                             a0[k], a1[k], a2[k]);
-                    time_average(cr, o + il, n_pad, step0 + step, vacc, vavg, u[k], v[k],
-                                 w[k]);
+                    end_kick(T, cr, sp[k], bath_next[X ? k : 0], u[k], v[k], w[k], a0[k],
+                             a1[k], a2[k]);
+                    if constexpr (X) {
+                        if (step + 1 < total)
+                            bath_next[k] = bath.load(cr, o + il, 2 * step + 2);
+                        const int at = k * BLOCK + tid;
+                        if (cr.W > 0)
+                            window_add(cr, in_window + 1 == cr.W, o + il, n_pad, vavg, u[k],
+                                       v[k], w[k], sums[0][at], sums[1][at], sums[2][at]);
+                    }
                 }
             }
         }
+        if constexpr (X) in_window = in_window + 1 == cr.W ? 0 : in_window + 1;
     }
 #pragma unroll
     for (int k = 0; k < KMAX; ++k) {
@@ -2307,6 +2401,10 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
             ax[o + il] = a0[k];
             ay[o + il] = a1[k];
             az[o + il] = a2[k];
+            if constexpr (X) {
+                if (cr.W > 0 && !accel_only)
+                    for (int c = 0; c < 3; ++c) vacc[c * n_pad + o + il] = sums[c][k * BLOCK + tid];
+            }
         }
     }
 }
@@ -2332,10 +2430,10 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
                                              double* __restrict__ ay, double* __restrict__ az,
                                              const double* __restrict__ qm,
                                              const double* __restrict__ qe,
-                                             const double* __restrict__ mass,
                                              const int32_t* __restrict__ species,
                                              const TrapDev* __restrict__ traps,
                                              const CoolDev* __restrict__ cool,
+                                             const BathTable bath,
                                              const int64_t* __restrict__ offsets,
                                              const int32_t* __restrict__ order,
                                              const int64_t* __restrict__ counter,
@@ -2355,11 +2453,21 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
     const bool owner = part == 0 && ti < m;
     const TrapDev T = traps[tr];
     const int64_t k0 = *counter;
-    const int64_t step0 = cool->step_base + k0 + 1;  // run-wide number of the first step
-    const CoolRef cr = cool_switches<X>(cool);
+    // with cooling: the beams in LDS, the baths of the next half-step loaded ahead
+    __shared__ BeamDev beams[X ? kMaxBeams : 1];
+    CoolRef cr = cool_switches<X>(cool);
+    if constexpr (X) {
+        if (lane < cr.nb) beams[lane] = cr.beams[lane];
+        cr.beams = beams;
+        __syncthreads();
+    }
+    // steps of the open averaging window completed so far
+    int in_window = X && cr.W > 0 ? window_phase(cr, cool->step_base + k0) : 0;
+    double sum0 = 0.0, sum1 = 0.0, sum2 = 0.0;
+    BathMap bath_next;
     const int64_t ion = o + min(ti, m - 1);
     double x = 0.0, y = 0.0, z = 0.0, u = 0.0, v = 0.0, w = 0.0, a0 = 0.0, a1 = 0.0, a2 = 0.0;
-    double q_m = 0.0, q_e = 0.0, m_i = 1.0;
+    double q_m = 0.0, q_e = 0.0;
     int32_t sp = 0;
     if (owner) {
         const double4 p = src[ion];
@@ -2374,8 +2482,15 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
         a2 = az[ion];
         q_m = qm[ion];
         q_e = qe[ion];
-        m_i = mass[ion];
         sp = species[ion];
+        if constexpr (X) {
+            if (cr.W > 0) {
+                sum0 = vacc[ion];
+                sum1 = vacc[n_pad + ion];
+                sum2 = vacc[2 * n_pad + ion];
+            }
+            if (!accel_only) bath_next = bath.load(cr, ion, 0);
+        }
     }
     const int total = accel_only ? 1 : nsteps;
     for (int step = 0; step < total; ++step) {
@@ -2385,9 +2500,10 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
             rf[(step / kRf) & 1][lane] = cos(T.omega * tq);
         }
         if (owner) {
-            if (!accel_only)
-                half_step_drift(T, cr, ion, sp, m_i, step0 + step, x, y, z, u, v, w, a0, a1,
-                                a2);
+            if (!accel_only) {
+                half_step_drift(T, cr, sp, bath_next, x, y, z, u, v, w, a0, a1, a2);
+                if constexpr (X) bath_next = bath.load(cr, ion, 2 * step + 1);
+            }
             if constexpr (PREC == 0) {
                 lds[ti] = make_double4(x, y, z, 1.5 * q_e);
             } else if constexpr (PREC == 1) {
@@ -2447,10 +2563,16 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
             const double crf = T.ps == 0.0 ? rf[(step / kRf) & 1][step % kRf] : 0.0;
             trap_accel_c(T, crf, q_m, x, y, z, Sx, Sy, Sz, a0, a1, a2);
             if (!accel_only) {
-                end_kick(T, cr, ion, sp, m_i, step0 + step, u, v, w, a0, a1, a2);
-                time_average(cr, ion, n_pad, step0 + step, vacc, vavg, u, v, w);
+                end_kick(T, cr, sp, bath_next, u, v, w, a0, a1, a2);
+                if constexpr (X) {
+                    if (step + 1 < total) bath_next = bath.load(cr, ion, 2 * step + 2);
+                    if (cr.W > 0)
+                        window_add(cr, in_window + 1 == cr.W, ion, n_pad, vavg, u, v, w, sum0,
+                                   sum1, sum2);
+                }
             }
         }
+        if constexpr (X) in_window = in_window + 1 == cr.W ? 0 : in_window + 1;
         // every lane is past its reads of the source stream and the cos table
         __syncthreads();
     }
@@ -2462,6 +2584,13 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
         ax[ion] = a0;
         ay[ion] = a1;
         az[ion] = a2;
+        if constexpr (X) {
+            if (cr.W > 0 && !accel_only) {
+                vacc[ion] = sum0;
+                vacc[n_pad + ion] = sum1;
+                vacc[2 * n_pad + ion] = sum2;
+            }
+        }
     }
 }
 
@@ -2620,7 +2749,7 @@ __global__ __launch_bounds__(256) void k_rigid_wrench(RigidDev* __restrict__ bod
         vx[i] = u;
         vy[i] = v;
         vz[i] = w;
-        time_average(load_cool(cool), i, n_pad, step, vacc, vavg, u, v, w);
+        time_average(cool_switches<true>(cool), i, n_pad, step, vacc, vavg, u, v, w);
     }
 }
 
@@ -2861,6 +2990,10 @@ __global__ __launch_bounds__(256) void k_hessian(const double4* __restrict__ src
 
 inline unsigned blocks_for(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
+inline BathTable bath_table(const DevState& s) {
+    return BathTable{s.noise_c, s.noise, s.noise_stride};
+}
+
 inline int n64_of(int64_t n) { return (int)((n + 63) & ~int64_t(63)); }
 
 inline BodyMask body_mask(const DevState& s) {
@@ -2908,8 +3041,8 @@ hipError_t batch_launch(const DevState& s, int n_traps, int max_trap, int nsteps
                         int accel_only, double uq, int tpt, hipStream_t st) {
     const size_t stream_bytes = (size_t)max_trap * sizeof(double4);
     k_batch<PREC, BLOCK, X><<<n_traps, BLOCK, stream_bytes, st>>>(s.src, s.vx, s.vy, s.vz, s.ax, s.ay,
-                                                       s.az, s.qm, s.qe, s.mass, s.species,
-                                                       s.traps, s.cool, s.offsets, s.order,
+                                                       s.az, s.qm, s.qe, s.species, s.traps,
+                                                       s.cool, bath_table(s), s.offsets, s.order,
                                                        s.counter, s.vacc, s.vavg, s.n_pad,
                                                        nsteps, accel_only, uq, tpt);
     return hipGetLastError();
@@ -2919,8 +3052,8 @@ template <int PREC, int P, int W, bool X>
 hipError_t wave_launch_p(const DevState& s, int n_traps, int nsteps, int accel_only,
                          hipStream_t st) {
     k_wave<PREC, P, W, X><<<n_traps, 64 * W, 0, st>>>(s.src, s.vx, s.vy, s.vz, s.ax, s.ay, s.az,
-                                                      s.qm, s.qe, s.mass, s.species, s.traps,
-                                                      s.cool, s.offsets, s.order, s.counter,
+                                                      s.qm, s.qe, s.species, s.traps, s.cool,
+                                                      bath_table(s), s.offsets, s.order, s.counter,
                                                       s.vacc, s.vavg, s.n_pad, nsteps,
                                                       accel_only);
     return hipGetLastError();
@@ -2987,15 +3120,21 @@ hipError_t batch_dispatch(const DevState& s, int n_traps, int max_trap, int bloc
 
 }  // namespace
 
-hipError_t launch_drift(const DevState& s, bool cool_on, hipStream_t st) {
+hipError_t launch_drift(const DevState& s, bool cool_on, int bath_idx, hipStream_t st) {
     if (cool_on)
         k_drift<true><<<blocks_for(s.n, 256), 256, 0, st>>>(
-            s.src, s.srcm, s.vx, s.vy, s.vz, s.ax, s.ay, s.az, s.qe, s.mass, s.species, s.traps,
-            s.cool, s.counter, s.rb, s.n);
+            s.src, s.srcm, s.vx, s.vy, s.vz, s.ax, s.ay, s.az, s.qe, s.species, s.traps, s.cool,
+            bath_table(s), bath_idx, s.rb, s.n);
     else
         k_drift<false><<<blocks_for(s.n, 256), 256, 0, st>>>(
-            s.src, s.srcm, s.vx, s.vy, s.vz, s.ax, s.ay, s.az, s.qe, s.mass, s.species, s.traps,
-            s.cool, s.counter, s.rb, s.n);
+            s.src, s.srcm, s.vx, s.vy, s.vz, s.ax, s.ay, s.az, s.qe, s.species, s.traps, s.cool,
+            bath_table(s), bath_idx, s.rb, s.n);
+    return hipGetLastError();
+}
+
+hipError_t launch_noise(const DevState& s, int g0, int half_steps, hipStream_t st) {
+    k_noise<<<dim3(blocks_for(s.n, 256), half_steps), 256, 0, st>>>(
+        s.mass, s.species, s.n, s.noise_stride, s.cool, s.counter, g0, s.noise_c, s.noise);
     return hipGetLastError();
 }
 
@@ -3124,51 +3263,53 @@ hipError_t launch_pair(const DevState& s, int precision, const LaunchShape& ls, 
 
 template <int MODE, int UW, typename PT>
 void update_launch(const DevState& s, const LaunchShape& ls, double scale, MixedSrc* srcm,
-                   const int64_t* ctr, hipStream_t st) {
+                   const int64_t* ctr, int bath_idx, hipStream_t st) {
     const unsigned g = blocks_for(s.n, 64);  // 64 ions per block of UW waves
     const PT* part = reinterpret_cast<const PT*>(s.part);
     if (ls.cool_on && MODE != kModeAccel)
         k_update<MODE, UW, true, PT><<<g, 64 * UW, 0, st>>>(
-            s.src, srcm, s.vx, s.vy, s.vz, s.ax, s.ay, s.az, s.qm, s.qe, s.mass, s.species,
-            part, ls.j_split, s.n, s.n_pad, scale, s.traps, s.cool, ctr, s.vacc, s.vavg, s.rb);
+            s.src, srcm, s.vx, s.vy, s.vz, s.ax, s.ay, s.az, s.qm, s.qe, s.species, part,
+            ls.j_split, s.n, s.n_pad, scale, s.traps, s.cool, ctr, bath_table(s), bath_idx,
+            s.vacc, s.vavg, s.rb);
     else
         k_update<MODE, UW, false, PT><<<g, 64 * UW, 0, st>>>(
-            s.src, srcm, s.vx, s.vy, s.vz, s.ax, s.ay, s.az, s.qm, s.qe, s.mass, s.species,
-            part, ls.j_split, s.n, s.n_pad, scale, s.traps, s.cool, ctr, s.vacc, s.vavg, s.rb);
+            s.src, srcm, s.vx, s.vy, s.vz, s.ax, s.ay, s.az, s.qm, s.qe, s.species, part,
+            ls.j_split, s.n, s.n_pad, scale, s.traps, s.cool, ctr, bath_table(s), bath_idx,
+            s.vacc, s.vavg, s.rb);
 }
 
 template <int MODE, typename PT>
 void update_dispatch_t(const DevState& s, const LaunchShape& ls, double scale, MixedSrc* srcm,
-                       const int64_t* ctr, hipStream_t st) {
+                       const int64_t* ctr, int bath_idx, hipStream_t st) {
     if (ls.update_waves == 16)
-        update_launch<MODE, 16, PT>(s, ls, scale, srcm, ctr, st);
+        update_launch<MODE, 16, PT>(s, ls, scale, srcm, ctr, bath_idx, st);
     else if (ls.update_waves == 8)
-        update_launch<MODE, 8, PT>(s, ls, scale, srcm, ctr, st);
+        update_launch<MODE, 8, PT>(s, ls, scale, srcm, ctr, bath_idx, st);
     else
-        update_launch<MODE, 4, PT>(s, ls, scale, srcm, ctr, st);
+        update_launch<MODE, 4, PT>(s, ls, scale, srcm, ctr, bath_idx, st);
 }
 
 // The pair kernels of the FP32 + FP64-run mode leave FP32 partials, those of
 // the FP64 and compensated modes FP64 ones.
 template <int MODE>
 void update_dispatch(const DevState& s, const LaunchShape& ls, double scale, MixedSrc* srcm,
-                     const int64_t* ctr, hipStream_t st, bool f32_partials) {
+                     const int64_t* ctr, int bath_idx, hipStream_t st, bool f32_partials) {
     if (f32_partials)
-        update_dispatch_t<MODE, float>(s, ls, scale, srcm, ctr, st);
+        update_dispatch_t<MODE, float>(s, ls, scale, srcm, ctr, bath_idx, st);
     else
-        update_dispatch_t<MODE, double>(s, ls, scale, srcm, ctr, st);
+        update_dispatch_t<MODE, double>(s, ls, scale, srcm, ctr, bath_idx, st);
 }
 
 hipError_t launch_update(const DevState& s, int precision, const LaunchShape& ls, int mode,
-                         bool use_counter, hipStream_t st) {
+                         bool use_counter, int bath_idx, hipStream_t st) {
     const double scale = precision == 0 ? 1.0 : kMixedFieldScale;
     const int64_t* ctr = use_counter ? s.counter : nullptr;
     MixedSrc* srcm = precision == 0 ? nullptr : s.srcm;
     const bool f32 = precision == 1;
     switch (mode) {
-        case kModeAccel: update_dispatch<kModeAccel>(s, ls, scale, srcm, ctr, st, f32); break;
-        case kModeEnd: update_dispatch<kModeEnd>(s, ls, scale, srcm, ctr, st, f32); break;
-        default: update_dispatch<kModeEndDrift>(s, ls, scale, srcm, ctr, st, f32); break;
+        case kModeAccel: update_dispatch<kModeAccel>(s, ls, scale, srcm, ctr, bath_idx, st, f32); break;
+        case kModeEnd: update_dispatch<kModeEnd>(s, ls, scale, srcm, ctr, bath_idx, st, f32); break;
+        default: update_dispatch<kModeEndDrift>(s, ls, scale, srcm, ctr, bath_idx, st, f32); break;
     }
     return hipGetLastError();
 }
@@ -3245,30 +3386,31 @@ hipError_t launch_batch_accel(const DevState& s, int precision, int n_traps, int
 namespace {
 
 template <int PREC, int TR>
-hipError_t rows_launch(const RowsArgs& A, bool cool_on, int mode, int k, hipStream_t st) {
+hipError_t rows_launch(const RowsArgs& A, bool cool_on, int mode, int k, int bath_idx,
+                       hipStream_t st) {
     const unsigned g = (unsigned)((A.n + TR - 1) / TR);
     if (cool_on && mode != kModeAccel)
-        k_rows<PREC, TR, true><<<g, kRowsBlock, 0, st>>>(A, mode, k);
+        k_rows<PREC, TR, true><<<g, kRowsBlock, 0, st>>>(A, mode, k, bath_idx);
     else
-        k_rows<PREC, TR, false><<<g, kRowsBlock, 0, st>>>(A, mode, k);
+        k_rows<PREC, TR, false><<<g, kRowsBlock, 0, st>>>(A, mode, k, 0);
     return hipGetLastError();
 }
 
 template <int PREC>
 hipError_t rows_dispatch(const RowsArgs& A, int tr, bool cool_on, int mode, int k,
-                         hipStream_t st) {
+                         int bath_idx, hipStream_t st) {
     switch (tr) {
-        case 1: return rows_launch<PREC, 1>(A, cool_on, mode, k, st);
-        case 2: return rows_launch<PREC, 2>(A, cool_on, mode, k, st);
-        case 8: return rows_launch<PREC, 8>(A, cool_on, mode, k, st);
-        default: return rows_launch<PREC, 4>(A, cool_on, mode, k, st);
+        case 1: return rows_launch<PREC, 1>(A, cool_on, mode, k, bath_idx, st);
+        case 2: return rows_launch<PREC, 2>(A, cool_on, mode, k, bath_idx, st);
+        case 8: return rows_launch<PREC, 8>(A, cool_on, mode, k, bath_idx, st);
+        default: return rows_launch<PREC, 4>(A, cool_on, mode, k, bath_idx, st);
     }
 }
 
 }  // namespace
 
 hipError_t launch_rows(const DevState& s, int precision, const LaunchShape& ls, int mode,
-                       int k_in_chunk, int parity_in, bool home_out, hipStream_t st) {
+                       int k_in_chunk, int parity_in, bool home_out, int bath_idx, hipStream_t st) {
     if (!s.src2 || (precision != 0 && (!s.srcm || !s.srcm2))) return hipErrorInvalidValue;
     RowsArgs A{};
     double4* buf[2] = {s.src, s.src2};
@@ -3285,19 +3427,19 @@ hipError_t launch_rows(const DevState& s, int precision, const LaunchShape& ls, 
     A.az = s.az;
     A.qm = s.qm;
     A.qe = s.qe;
-    A.mass = s.mass;
     A.species = s.species;
     A.traps = s.traps;
     A.cool = s.cool;
+    A.bath = bath_table(s);
     A.counter = s.counter;
     A.vacc = s.vacc;
     A.vavg = s.vavg;
     A.n = s.n;
     A.n_pad = s.n_pad;
     switch (precision) {
-        case 0: return rows_dispatch<0>(A, ls.rows_tr, ls.cool_on, mode, k_in_chunk, st);
-        case 2: return rows_dispatch<2>(A, ls.rows_tr, ls.cool_on, mode, k_in_chunk, st);
-        default: return rows_dispatch<1>(A, ls.rows_tr, ls.cool_on, mode, k_in_chunk, st);
+        case 0: return rows_dispatch<0>(A, ls.rows_tr, ls.cool_on, mode, k_in_chunk, bath_idx, st);
+        case 2: return rows_dispatch<2>(A, ls.rows_tr, ls.cool_on, mode, k_in_chunk, bath_idx, st);
+        default: return rows_dispatch<1>(A, ls.rows_tr, ls.cool_on, mode, k_in_chunk, bath_idx, st);
     }
 }
 

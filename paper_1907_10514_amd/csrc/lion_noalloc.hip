@@ -134,7 +134,7 @@ extern "C" int lion_accel_noalloc(int64_t n, const double* x, const double* y, c
     hipStream_t st = (hipStream_t)hip_stream;
     hipError_t e = lion::launch_pack_inputs(x, y, z, charges_C, masses_kg, d, T, st);
     if (e == hipSuccess) e = lion::launch_pair(d, precision, ls, false, st);
-    if (e == hipSuccess) e = lion::launch_update(d, precision, ls, lion::kModeAccel, false, st);
+    if (e == hipSuccess) e = lion::launch_update(d, precision, ls, lion::kModeAccel, false, 0, st);
     if (e != hipSuccess) return fail(LION_ERR_HIP, hipGetErrorString(e));
     return LION_OK;
 }
