@@ -488,9 +488,19 @@ bool cooling_on(const lion_sim* s) {
     return on;
 }
 
+bool min_rows_active(const lion_sim* s) {
+    return !s->has_bodies && lion::min_path(s->d) == lion::MinPath::kRows;
+}
+
 // K minimisation iterations: reduce + stopping test, move, forces at the new
 // positions (a graph per K, parameters read from device memory).
 hipError_t enqueue_min_chunk(lion_sim* s, int64_t K, hipStream_t st) {
+    if (min_rows_active(s)) {
+        hipError_t e = hipSuccess;
+        for (int64_t k = 0; k < K && e == hipSuccess; ++k)
+            e = lion::launch_min_rows(s->d, s->precision, (int)(k & 1), true, st);
+        return e;
+    }
     for (int64_t k = 0; k < K; ++k) {
         hipError_t e = lion::launch_min_reduce(s->d, st);
         if (e == hipSuccess) e = lion::launch_min_move(s->d, s->precision, st);
@@ -1284,23 +1294,45 @@ int lion_minimize(lion_sim* s, double dt, double dmax, double ftol, int64_t max_
         return fail(s, LION_ERR_UNSUPPORTED,
                     "minimisation needs a time-independent trap (pseudopotential trap or no rf)");
     LION_HIP(s, hipSetDevice(s->device));
-    int rc = refresh_accel(s);  // forces at the current positions, trap clock fixed
-    if (rc) return rc;
     lion::MinDev m{};
     m.dt = dt;
     m.dmax = dmax;
     m.ftol = ftol;
     m.max_iter = max_iter;
     hipStream_t st = s->stream;
+    int rc = LION_OK;
+    if (!s->has_bodies && lion::min_path(s->d) == lion::MinPath::kOne) {
+        // many iterations per launch, the starting forces included
+        const int64_t per_launch = 2000;
+        for (bool first = true; first || !m.done; first = false) {
+            LION_HIP(s, lion::launch_min_one(s->d, s->precision, m, first, per_launch, st));
+            LION_HIP(s, hipMemcpyAsync(&m, s->d.minst, sizeof(m), hipMemcpyDeviceToHost, st));
+            LION_HIP(s, hipStreamSynchronize(st));
+        }
+        if (s->d.srcm) LION_HIP(s, lion::launch_pack_mixed(s->d, st));
+        if (iterations) *iterations = m.iterations;
+        if (fmax) *fmax = m.fmax;
+        return LION_OK;
+    }
+    const bool rows = min_rows_active(s);
     LION_HIP(s, hipMemcpyAsync(s->d.minst, &m, sizeof(m), hipMemcpyHostToDevice, st));
-    const int64_t K = 50;
+    if (rows) {
+        LION_HIP(s, lion::launch_min_rows(s->d, s->precision, 0, false, st));
+    } else {
+        rc = refresh_accel(s);  // forces at the current positions, trap clock fixed
+        if (rc) return rc;
+    }
     for (;;) {
-        rc = run_min_chunk(s, K);
+        // up to 50 iterations and the last test; an even count, as one launch per
+        // iteration alternates two buffers
+        const int64_t left = max_iter - m.iterations + 1;
+        rc = run_min_chunk(s, left >= 50 ? 50 : left + (left & 1));
         if (rc) return rc;
         LION_HIP(s, hipMemcpyAsync(&m, s->d.minst, sizeof(m), hipMemcpyDeviceToHost, st));
         LION_HIP(s, hipStreamSynchronize(st));
         if (m.done) break;
     }
+    if (rows && s->d.srcm) LION_HIP(s, lion::launch_pack_mixed(s->d, st));
     if (iterations) *iterations = m.iterations;
     if (fmax) *fmax = m.fmax;
     return LION_OK;

@@ -250,6 +250,19 @@ hipError_t launch_rigid_drift(const DevState& s, hipStream_t st);
 hipError_t launch_rigid_place(const DevState& s, int precision, hipStream_t st);
 hipError_t launch_min_reduce(const DevState& s, hipStream_t st);
 hipError_t launch_min_move(const DevState& s, int precision, hipStream_t st);
+// How lion_minimize runs its iterations: inside one workgroup, one launch each, or
+// (large traps, rigid-body masks) the pair kernels with separate reductions.
+enum class MinPath { kOne, kRows, kLaunches };
+// One workgroup up to here (us an iteration: 160 ions 7.0 against 8.0 with a launch each).
+constexpr int64_t kMinOneIons = 160;
+MinPath min_path(const DevState& s);
+// Up to `iters` iterations; `first`: parameters from init and forces at the current
+// positions before them, else s.minst goes on.  s.minst holds the state after.
+hipError_t launch_min_one(const DevState& s, int precision, const MinDev& init, bool first,
+                          int64_t iters, hipStream_t st);
+// One iteration (move) reading side `from` (0: the handle's arrays) and writing the
+// other, or (!move) the forces and sums that the first starts from, on side 0.
+hipError_t launch_min_rows(const DevState& s, int precision, int from, bool move, hipStream_t st);
 hipError_t launch_hessian(const DevState& s, const TrapDev& T, double* D, hipStream_t st);
 // Eigenvalues (ascending, into W) and optionally eigenvectors (into A's
 // columns) of the symmetric m x m matrix A (upper triangle read) with

@@ -2929,6 +2929,400 @@ __global__ __launch_bounds__(256) void k_min_move(double4* __restrict__ src,
     if (srcm) srcm[i] = make_src(p.x, p.y, p.z, qe[i]);
 }
 
+// One trap of at most kMaxTrap ions in one or a few kernels.  Both keep the
+// order of the kernels above: reduce and test, move, forces.
+
+struct MinArgs {
+    double4* src[2];       // positions, alternating (k_min_one: [0] only)
+    double *vx, *vy, *vz;
+    double *ax[2], *ay[2], *az[2];
+    const double *qm, *qe, *mass;
+    const TrapDev* traps;
+    MinDev* ms[2];         // state before and after an iteration
+    double* part[2];       // per workgroup {v.F, F.F, max |F|}
+    int64_t n;
+};
+
+// Largest of the values of a wave in every lane.
+__device__ __forceinline__ double wave_max(double v) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off));
+    return v;
+}
+
+// v.F, F.F and |F| of one ion.
+__device__ __forceinline__ void min_terms(double m, double ax, double ay, double az, double vx,
+                                          double vy, double vz, double& P, double& FF,
+                                          double& fm) {
+#pragma clang fp contract(off)
+    const double fx = m * ax, fy = m * ay, fz = m * az;
+    P = vx * fx + vy * fy + vz * fz;
+    FF = fx * fx + fy * fy + fz * fz;
+    fm = sqrt(FF);
+}
+
+// One ion's move (as k_min_move).
+__device__ __forceinline__ void min_move_ion(double coef, double dt, double dmax, double m,
+                                             double ax, double ay, double az, double& u,
+                                             double& v, double& w, double& x, double& y,
+                                             double& z) {
+#pragma clang fp contract(off)
+    u = coef * (m * ax) + dt * ax;
+    v = coef * (m * ay) + dt * ay;
+    w = coef * (m * az) + dt * az;
+    const double step = dt * sqrt(u * u + v * v + w * w);
+    if (step > dmax) {
+        const double r = dmax / step;
+        u = u * r;
+        v = v * r;
+        w = w * r;
+    }
+    x = x + dt * u;
+    y = y + dt * v;
+    z = z + dt * w;
+}
+
+template <int PREC>
+__device__ __forceinline__ typename BatchSrc<PREC>::T make_pair_src(double x, double y, double z,
+                                                                    double qe) {
+    if constexpr (PREC == 0)
+        return make_double4(x, y, z, 1.5 * qe);
+    else if constexpr (PREC == 1)
+        return make_batch_src(x, y, z, qe);
+    else
+        return make_src(x, y, z, qe);
+}
+
+// Up to `iters` iterations of one trap inside one workgroup: the owners' state in
+// registers, the source stream and all reductions in LDS.  Latency and, from about
+// 100 ions, FP64 issue of one CU bound it: 2.9 us an iteration at 20 ions, 4.4 at
+// 100, 5.4 at 128, where five launches took 17 to 19.  IS owner slots (one per ion)
+// times JP source parts fill the block; at least four sources per part and at most
+// 16 parts, as the owners add the parts in a dependent chain (20 ions: 51 parts of
+// one source 5.7 us an iteration).
+constexpr int kMinOne = 1024;
+
+template <int PREC>
+__global__ __launch_bounds__(kMinOne) void k_min_one(const MinArgs A, MinDev init, int first,
+                                                     int64_t iters) {
+    using S = typename BatchSrc<PREC>::T;
+    extern __shared__ double4 lds_stream[];
+    S* lds = reinterpret_cast<S*>(lds_stream);
+    __shared__ double red[3][kMinOne];
+    __shared__ double wred[kMinOne / 64][3];
+    const int m = (int)A.n, tid = threadIdx.x;
+    const int IS = m, JP = min(min((int)blockDim.x / IS, 16), (m + 3) / 4);
+    const int slot = tid % IS, part = tid / IS;
+    const bool active = part < JP, own = tid < m;
+    const int len = (m + JP - 1) / JP;
+    const int jb = min(part * len, m), je = min(jb + len, m);
+    const int waves = (m + 63) / 64;  // that hold owners
+    const TrapDev T = A.traps[0];
+    const MinDev M = first ? init : *A.ms[0];
+    double x = 0, y = 0, z = 0, u = 0, v = 0, w = 0, a0 = 0, a1 = 0, a2 = 0;
+    double qm = 0, qe = 0, mass = 0;
+    if (own) {
+        const double4 p = A.src[0][tid];
+        x = p.x;
+        y = p.y;
+        z = p.z;
+        u = A.vx[tid];
+        v = A.vy[tid];
+        w = A.vz[tid];
+        a0 = A.ax[0][tid];
+        a1 = A.ay[0][tid];
+        a2 = A.az[0][tid];
+        qm = A.qm[tid];
+        qe = A.qe[tid];
+        mass = A.mass[tid];
+    }
+    int64_t it = M.iterations, left = iters;
+    double P = 0, FF = 0, fmx = 0;
+    bool forces = first, done = false;  // the first launch starts with the forces
+    for (;;) {
+        if (forces) {
+            if (own) lds[tid] = make_pair_src<PREC>(x, y, z, qe);
+            __syncthreads();
+            double sx[4], sy[4], sz[4];
+            if (active) {
+                batch_pairs_multi<PREC, 1, false>(lds, m, slot, 0, jb, je, 0.0, sx, sy, sz);
+                red[0][tid] = sx[0];
+                red[1][tid] = sy[0];
+                red[2][tid] = sz[0];
+            }
+            __syncthreads();
+            if (own) {
+                double Sx = sx[0], Sy = sy[0], Sz = sz[0];
+                for (int p = 1; p < JP; ++p) {
+                    Sx += red[0][slot + p * IS];
+                    Sy += red[1][slot + p * IS];
+                    Sz += red[2][slot + p * IS];
+                }
+                trap_accel_c(T, 0.0, qm, x, y, z, Sx, Sy, Sz, a0, a1, a2);
+            }
+        }
+        forces = true;
+        // v.F, F.F and max |F|: over each wave, then the waves in order
+        if (tid < 64 * waves) {
+            double p_, f_, g_;
+            min_terms(mass, a0, a1, a2, u, v, w, p_, f_, g_);
+            p_ = wave_sum(p_);
+            f_ = wave_sum(f_);
+            g_ = wave_max(g_);
+            if ((tid & 63) == 0) {
+                wred[tid >> 6][0] = p_;
+                wred[tid >> 6][1] = f_;
+                wred[tid >> 6][2] = g_;
+            }
+        }
+        __syncthreads();
+        P = FF = fmx = 0.0;
+        for (int k = 0; k < waves; ++k) {
+            P += wred[k][0];
+            FF += wred[k][1];
+            fmx = fmax(fmx, wred[k][2]);
+        }
+        done = fmx <= M.ftol || it >= M.max_iter;
+        if (done || left == 0) break;  // the same in every thread
+        --left;
+        ++it;
+        if (own) {
+            const double coef = (P > 0.0 && FF > 0.0) ? P / FF : 0.0;
+            min_move_ion(coef, M.dt, M.dmax, mass, a0, a1, a2, u, v, w, x, y, z);
+        }
+    }
+    if (own) {
+        A.src[0][tid] = make_double4(x, y, z, 1.5 * qe);
+        A.vx[tid] = u;
+        A.vy[tid] = v;
+        A.vz[tid] = w;
+        A.ax[0][tid] = a0;
+        A.ay[0][tid] = a1;
+        A.az[0][tid] = a2;
+    }
+    if (tid == 0) {
+        MinDev o = M;
+        o.P = P;
+        o.FF = FF;
+        o.fmax = fmx;
+        o.iterations = it;
+        o.done = done ? 1 : 0;
+        *A.ms[0] = o;
+    }
+}
+
+// One iteration per launch: workgroup g owns the TR ions [g TR, g TR + TR) and
+// moves every ion for itself (a few per thread, cheaper than a launch) into LDS,
+// where its pair sums read them; it stores its own ions, their accelerations and
+// its share of the sums that the next launch reduces.  All of that alternates
+// between two buffers (side `from` is read), as other workgroups still read the
+// old; once the stopping test has passed, a launch only hands its ions on.  Bound
+// by launch latency and the chain reduce, move, pairs, reduce: 8.0 us an iteration
+// at 161 ions, 9.1 at 512, 11.8 at 1024, where five launches took 19.8 to 21.6.
+constexpr int kMinRows = 512;
+constexpr int kMinRowsMax = 2048;  // ions whose source stream fits 64 KiB of LDS
+
+template <int PREC, int TR>
+__global__ __launch_bounds__(kMinRows) void k_min_rows(const MinArgs A, int from, int move) {
+    using S = typename BatchSrc<PREC>::T;
+    extern __shared__ double4 lds_stream[];
+    S* lds = reinterpret_cast<S*>(lds_stream);
+    constexpr int kW = kMinRows / 64;
+    __shared__ double red[kW][3 * TR > 3 ? 3 * TR : 3];
+    __shared__ double own_pos[TR][3], own_vel[TR][3];
+    const int n = (int)A.n, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int to = move ? from ^ 1 : from;
+    const int i0 = (int)blockIdx.x * TR, i = i0 + tid;
+    const bool own = tid < TR && i < n;
+    const TrapDev T = A.traps[0];
+    MinDev M = *A.ms[from];
+    // this thread's ions, loaded ahead of the reduction
+    constexpr int NI = TR <= 2 ? 1 : TR / 2;  // kMinRows NI >= 256 TR >= n
+    double4 p_in[NI];
+    double a_in[NI][3], m_in[NI], q_in[NI];
+#pragma unroll
+    for (int k = 0; k < NI; ++k) {
+        const int j = min(tid + k * kMinRows, n - 1);
+        p_in[k] = A.src[from][j];
+        a_in[k][0] = A.ax[from][j];
+        a_in[k][1] = A.ay[from][j];
+        a_in[k][2] = A.az[from][j];
+        m_in[k] = A.mass[j];
+        q_in[k] = A.qe[j];
+    }
+    double qm = 0.0, qe = 0.0, mass = 0.0;
+    if (own) {
+        qm = A.qm[i];
+        qe = A.qe[i];
+        mass = A.mass[i];
+    }
+    double coef = 0.0;
+    if (move) {
+        // the sums at the current positions, in a fixed order
+        double P = 0.0, FF = 0.0, fm = 0.0;
+        for (int b = tid; b < (int)gridDim.x; b += kMinRows) {
+            P += A.part[from][3 * b];
+            FF += A.part[from][3 * b + 1];
+            fm = fmax(fm, A.part[from][3 * b + 2]);
+        }
+        P = wave_sum(P);
+        FF = wave_sum(FF);
+        fm = wave_max(fm);
+        if (lane == 0) {
+            red[wave][0] = P;
+            red[wave][1] = FF;
+            red[wave][2] = fm;
+        }
+        __syncthreads();
+        P = FF = fm = 0.0;
+        for (int k = 0; k < kW; ++k) {
+            P += red[k][0];
+            FF += red[k][1];
+            fm = fmax(fm, red[k][2]);
+        }
+        M.P = P;
+        M.FF = FF;
+        M.fmax = fm;
+        M.done = (fm <= M.ftol || M.iterations >= M.max_iter) ? 1 : 0;
+        coef = (P > 0.0 && FF > 0.0) ? P / FF : 0.0;
+        if (!M.done) M.iterations += 1;
+    }
+    if (move && blockIdx.x == 0 && tid == 0) *A.ms[to] = M;
+    if (move && M.done) {
+        if (own) {
+            A.src[to][i] = A.src[from][i];
+            A.ax[to][i] = A.ax[from][i];
+            A.ay[to][i] = A.ay[from][i];
+            A.az[to][i] = A.az[from][i];
+        }
+        if (tid < 3) A.part[to][3 * blockIdx.x + tid] = A.part[from][3 * blockIdx.x + tid];
+        return;  // the same in every thread of the launch
+    }
+#pragma unroll
+    for (int k = 0; k < NI; ++k) {
+        const int j = tid + k * kMinRows;
+        if (j >= n) break;
+        double x = p_in[k].x, y = p_in[k].y, z = p_in[k].z, u = 0.0, v = 0.0, w = 0.0;
+        const bool mine = j >= i0 && j < i0 + TR;
+        if (move) {
+            min_move_ion(coef, M.dt, M.dmax, m_in[k], a_in[k][0], a_in[k][1], a_in[k][2], u, v,
+                         w, x, y, z);
+        } else if (mine) {
+            u = A.vx[j];
+            v = A.vy[j];
+            w = A.vz[j];
+        }
+        lds[j] = make_pair_src<PREC>(x, y, z, q_in[k]);
+        if (mine) {
+            own_pos[j - i0][0] = x;
+            own_pos[j - i0][1] = y;
+            own_pos[j - i0][2] = z;
+            own_vel[j - i0][0] = u;
+            own_vel[j - i0][1] = v;
+            own_vel[j - i0][2] = w;
+        }
+    }
+    __syncthreads();
+    double sx[TR], sy[TR], sz[TR];
+#pragma unroll
+    for (int k = 0; k < TR; ++k) sx[k] = sy[k] = sz[k] = 0.0;
+    if constexpr (PREC == 2) {
+        float fx[TR], fy[TR], fz[TR], cx[TR], cy[TR], cz[TR];
+        FF t[TR];
+#pragma unroll
+        for (int k = 0; k < TR; ++k) {
+            const MixedSrc q = lds[min(i0 + k, n - 1)];
+            t[k] = FF{q.xh, q.yh, q.zh, q.xl, q.yl, q.zl};
+            fx[k] = fy[k] = fz[k] = cx[k] = cy[k] = cz[k] = 0.0f;
+        }
+        for (int j = tid; j < n; j += kMinRows) {
+            const MixedSrc q = lds[j];
+#pragma unroll
+            for (int k = 0; k < TR; ++k) {
+                float tx, ty, tz;
+                pair_f32_terms(q, t[k], tx, ty, tz);
+                kahan_add(tx, fx[k], cx[k]);
+                kahan_add(ty, fy[k], cy[k]);
+                kahan_add(tz, fz[k], cz[k]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < TR; ++k) {
+            sx[k] = (double)fx[k] - (double)cx[k];
+            sy[k] = (double)fy[k] - (double)cy[k];
+            sz[k] = (double)fz[k] - (double)cz[k];
+        }
+    } else {
+        double tx[TR], ty[TR], tz[TR];
+#pragma unroll
+        for (int k = 0; k < TR; ++k) {
+            const S q = lds[min(i0 + k, n - 1)];
+            tx[k] = q.x;
+            ty[k] = q.y;
+            tz[k] = q.z;
+        }
+        for (int j = tid; j < n; j += kMinRows) {
+            const S q = lds[j];
+#pragma unroll
+            for (int k = 0; k < TR; ++k) {
+                if constexpr (PREC == 0) {
+                    pair_f64(q, tx[k], ty[k], tz[k], sx[k], sy[k], sz[k]);
+                } else {  // at most four sources per thread: each term into FP64
+                    float px, py, pz;
+                    batch_pair_f32<false>(q, tx[k], ty[k], tz[k], px, py, pz);
+                    sx[k] += (double)px;
+                    sy[k] += (double)py;
+                    sz[k] += (double)pz;
+                }
+            }
+        }
+    }
+    __syncthreads();  // the reduction above is read
+#pragma unroll
+    for (int k = 0; k < TR; ++k) {
+        const double X = wave_sum(sx[k]), Y = wave_sum(sy[k]), Z = wave_sum(sz[k]);
+        if (lane == 0) {
+            red[wave][3 * k] = X;
+            red[wave][3 * k + 1] = Y;
+            red[wave][3 * k + 2] = Z;
+        }
+    }
+    __syncthreads();
+    if (wave > 0) return;
+    double P = 0.0, FF = 0.0, fm = 0.0;
+    if (own) {
+        double Sx = red[0][3 * tid], Sy = red[0][3 * tid + 1], Sz = red[0][3 * tid + 2];
+        for (int k = 1; k < kW; ++k) {
+            Sx += red[k][3 * tid];
+            Sy += red[k][3 * tid + 1];
+            Sz += red[k][3 * tid + 2];
+        }
+        const double fs = PREC == 0 ? 1.0 : kMixedFieldScale;
+        const double x = own_pos[tid][0], y = own_pos[tid][1], z = own_pos[tid][2];
+        const double u = own_vel[tid][0], v = own_vel[tid][1], w = own_vel[tid][2];
+        double a0, a1, a2;
+        trap_accel_c(T, 0.0, qm, x, y, z, Sx * fs, Sy * fs, Sz * fs, a0, a1, a2);
+        min_terms(mass, a0, a1, a2, u, v, w, P, FF, fm);
+        if (move) {
+            A.src[to][i] = make_double4(x, y, z, 1.5 * qe);
+            A.vx[i] = u;
+            A.vy[i] = v;
+            A.vz[i] = w;
+        }
+        A.ax[to][i] = a0;
+        A.ay[to][i] = a1;
+        A.az[to][i] = a2;
+    }
+    P = wave_sum(P);
+    FF = wave_sum(FF);
+    fm = wave_max(fm);
+    if (tid == 0) {
+        A.part[to][3 * blockIdx.x] = P;
+        A.part[to][3 * blockIdx.x + 1] = FF;
+        A.part[to][3 * blockIdx.x + 2] = fm;
+    }
+}
+
 // ------------------------------------------------------------ normal modes
 
 // Mass-weighted Hessian of the static potential, one 3x3 block (i, j) per
@@ -3356,6 +3750,83 @@ hipError_t launch_min_move(const DevState& s, int precision, hipStream_t st) {
     MixedSrc* srcm = precision == 0 ? nullptr : s.srcm;
     k_min_move<<<blocks_for(s.n, 256), 256, 0, st>>>(s.src, srcm, s.vx, s.vy, s.vz, s.ax, s.ay,
                                                      s.az, s.mass, s.qe, s.n, s.minst);
+    return hipGetLastError();
+}
+
+namespace {
+
+MinArgs min_args(const DevState& s) {
+    MinArgs A{};
+    A.src[0] = s.src;
+    A.vx = s.vx;
+    A.vy = s.vy;
+    A.vz = s.vz;
+    A.ax[0] = s.ax;
+    A.ay[0] = s.ay;
+    A.az[0] = s.az;
+    A.qm = s.qm;
+    A.qe = s.qe;
+    A.mass = s.mass;
+    A.traps = s.traps;
+    A.ms[0] = s.minst;
+    A.n = s.n;
+    return A;
+}
+
+template <int PREC>
+void min_rows_dispatch(const MinArgs& A, int tr, int from, int move, hipStream_t st) {
+    const unsigned g = blocks_for(A.n, tr);
+    const size_t lds = (size_t)A.n * sizeof(double4);
+    switch (tr) {
+        case 1: k_min_rows<PREC, 1><<<g, kMinRows, lds, st>>>(A, from, move); break;
+        case 2: k_min_rows<PREC, 2><<<g, kMinRows, lds, st>>>(A, from, move); break;
+        case 4: k_min_rows<PREC, 4><<<g, kMinRows, lds, st>>>(A, from, move); break;
+        default: k_min_rows<PREC, 8><<<g, kMinRows, lds, st>>>(A, from, move); break;
+    }
+}
+
+}  // namespace
+
+MinPath min_path(const DevState& s) {
+    if (s.n <= kMinOneIons) return MinPath::kOne;
+    if (s.n > kMinRowsMax || !s.src2 || !s.part) return MinPath::kLaunches;
+    return MinPath::kRows;
+}
+
+hipError_t launch_min_one(const DevState& s, int precision, const MinDev& init, bool first,
+                          int64_t iters, hipStream_t st) {
+    if (s.n > kMinOneIons) return hipErrorInvalidValue;
+    const MinArgs A = min_args(s);
+    const size_t lds = (size_t)s.n * sizeof(double4);
+    const int block = s.n <= 32 ? 256 : (s.n <= 64 ? 512 : kMinOne);
+    switch (precision) {
+        case 0: k_min_one<0><<<1, block, lds, st>>>(A, init, first, iters); break;
+        case 2: k_min_one<2><<<1, block, lds, st>>>(A, init, first, iters); break;
+        default: k_min_one<1><<<1, block, lds, st>>>(A, init, first, iters); break;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_min_rows(const DevState& s, int precision, int from, bool move,
+                           hipStream_t st) {
+    // one workgroup per CU: 1, 2, 4 or 8 ions each
+    const int tr = s.n <= 256 ? 1 : (s.n <= 512 ? 2 : (s.n <= 1024 ? 4 : 8));
+    MinArgs A = min_args(s);
+    // the second buffers live where the pair kernels keep their partial sums
+    // (three slices of n_pad ions or more above 128 ions)
+    double* p = s.part;
+    A.src[1] = s.src2;
+    A.ax[1] = p;
+    A.ay[1] = p + s.n_pad;
+    A.az[1] = p + 2 * s.n_pad;
+    A.part[0] = p + 3 * s.n_pad;
+    A.part[1] = p + 6 * s.n_pad;
+    A.ms[1] = reinterpret_cast<MinDev*>(p + 9 * s.n_pad - 16);
+    switch (precision) {
+        case 0: min_rows_dispatch<0>(A, tr, from, move, st); break;
+        case 2: min_rows_dispatch<2>(A, tr, from, move, st); break;
+        default: min_rows_dispatch<1>(A, tr, from, move, st); break;
+    }
     return hipGetLastError();
 }
 
