@@ -254,7 +254,8 @@ size_t lion_normal_modes_workspace_bytes(lion_sim *sim);
  * FP64, in dev_work (caller-owned device memory, 256-byte aligned, at least
  * lion_normal_modes_workspace_bytes(sim) bytes); rocSOLVER's dsyevd
  * diagonalises it on the GPU, with its scratch memory taken from the tail of
- * dev_work (rocblas_set_workspace: rocBLAS allocates nothing for it).  Outputs
+ * dev_work (rocblas_set_workspace: rocBLAS allocates nothing for it); without
+ * modes and up to 170 ions, HIP kernels of this library find the frequencies.  Outputs
  * (host): omega2 [3n] squared angular frequencies, ascending (rad^2/s^2); modes
  * [3n * 3n] or NULL: column k (stride 3n, column-major) is the mass-weighted
  * eigenvector of omega2[k], component 3i + axis.  A minimum of the potential

@@ -53,6 +53,7 @@ struct lion_sim {
     size_t body_off[5] = {0, 0, 0, 0, 0};
     bool tile_bodies = false;  // every 256-ion tile holds ions of one body only, or none
     std::map<std::pair<int64_t, int>, hipGraphExec_t> graphs;  // (chunk length, kind)
+    size_t eigh_bytes[2] = {SIZE_MAX, SIZE_MAX};  // its scratch, without / with vectors
     void* eigh = nullptr;  // rocBLAS handle of the normal-mode solver (created on first use)
     std::string err;
 };
@@ -788,6 +789,20 @@ size_t modes_fixed_bytes(int64_t n) {
     return align_up(m * m * 8) + 2 * align_up(m * 8) + align_up(sizeof(int));
 }
 
+// Bytes the eigen-solver library wants for this handle's matrix, asked once per
+// handle (the query costs tens of microseconds).
+int solver_scratch(lion_sim* s, bool vectors, double* A, double* W, double* E, int* info,
+                   size_t* bytes, std::string& err) {
+    size_t& known = s->eigh_bytes[vectors ? 1 : 0];
+    if (known == SIZE_MAX &&
+        lion::eigh_scratch_bytes(s->eigh, (int)(3 * s->n), vectors, A, W, E, info, &known, err) != 0) {
+        known = SIZE_MAX;
+        return -1;
+    }
+    *bytes = known;
+    return 0;
+}
+
 int modes_handle(lion_sim* s) {
     if (s->eigh) return LION_OK;
     std::string err;
@@ -1221,13 +1236,12 @@ int lion_compute_accel(lion_sim* s, double* ax, double* ay, double* az) {
 size_t lion_normal_modes_workspace_bytes(lion_sim* s) {
     if (check_handle(s) || s->n < 1 || 3 * s->n > 2147483647 / (3 * s->n)) return 0;
     if (hipSetDevice(s->device) != hipSuccess || modes_handle(s) != LION_OK) return 0;
-    const int m = (int)(3 * s->n);
     // sizes only: the solver is asked in query mode, with device addresses of
     // the handle's own workspace standing in for the arrays
     double* any = (double*)s->ws;
     size_t scratch = 0;
     std::string err;
-    if (lion::eigh_scratch_bytes(s->eigh, m, true, any, any, any, (int*)s->ws, &scratch, err) != 0) {
+    if (solver_scratch(s, true, any, any, any, (int*)s->ws, &scratch, err) != 0) {
         s->err = err;
         return 0;
     }
@@ -1260,7 +1274,7 @@ int lion_normal_modes(lion_sim* s, void* dev_work, size_t bytes, double* omega2,
     int* info = (int*)(base + align_up((size_t)m * m * 8) + 2 * align_up((size_t)m * 8));
     std::string err;
     size_t scratch = 0;
-    if (lion::eigh_scratch_bytes(s->eigh, m, modes != nullptr, A, W, E, info, &scratch, err) != 0)
+    if (solver_scratch(s, modes != nullptr, A, W, E, info, &scratch, err) != 0)
         return fail(s, LION_ERR_HIP, err);
     if (bytes < fixed + scratch)
         return fail(s, LION_ERR_WORKSPACE,
@@ -1268,6 +1282,16 @@ int lion_normal_modes(lion_sim* s, void* dev_work, size_t bytes, double* omega2,
                         " bytes (lion_normal_modes_workspace_bytes), got " + std::to_string(bytes));
     hipStream_t st = s->stream;
     LION_HIP(s, lion::launch_hessian(s->d, T, A, st));
+    // frequencies alone: the kernels here up to order kEigenMax, the library above it
+    // and for the modes themselves
+    if (!modes && m <= lion::kEigenMax && bytes - fixed >= lion::eigenvalues_scratch_bytes(m)) {
+        LION_HIP(s, lion::launch_eigenvalues(A, m, W, E, base + fixed, st));
+        LION_HIP(s, hipMemcpyAsync(omega2, W, (size_t)m * 8, hipMemcpyDeviceToHost, st));
+        LION_HIP(s, hipStreamSynchronize(st));
+        // neighbours that agree to rounding may come out in either order
+        for (int k = 1; k < m; ++k) omega2[k] = std::max(omega2[k], omega2[k - 1]);
+        return LION_OK;
+    }
     if (lion::eigh_device(s->eigh, A, m, W, E, info, modes != nullptr, base + fixed,
                           bytes - fixed, st, err) != 0)
         return fail(s, LION_ERR_HIP, err);

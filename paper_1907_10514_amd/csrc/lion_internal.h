@@ -277,6 +277,14 @@ int eigh_scratch_bytes(void* h, int m, bool vectors, double* A, double* W, doubl
                        size_t* bytes, std::string& err);
 int eigh_device(void* h, double* A, int m, double* W, double* E, int* info, bool vectors,
                 void* scratch, size_t scratch_bytes, hipStream_t st, std::string& err);
+// Eigenvalues alone (ascending up to rounding, into W) of a symmetric m x m matrix,
+// m <= kEigenMax, by the kernels of lion_eigen.hip; A is overwritten, E is m doubles,
+// scratch eigenvalues_scratch_bytes(m).  NaN throughout for a matrix that is not
+// finite.
+constexpr int kEigenMax = 512;
+size_t eigenvalues_scratch_bytes(int m);
+hipError_t launch_eigenvalues(double* A, int m, double* W, double* E, void* scratch,
+                              hipStream_t st);
 // One step (or, with kModeAccel, one force evaluation) of one trap in a single
 // launch: positions read from buffer parity_in (0: src/srcm, 1: src2/srcm2);
 // drifted positions written to the other buffer, or with home_out to buffer 0.

@@ -35,6 +35,7 @@
 #include <algorithm>
 
 #include "lion_internal.h"
+#include "lion_wave.h"
 
 namespace lion {
 namespace {
@@ -1495,12 +1496,6 @@ struct RowsArgs {
     double *vacc, *vavg;
     int64_t n, n_pad;
 };
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-    return v;
-}
 
 template <int PREC, int TR, bool X>
 __global__ __launch_bounds__(kRowsBlock) void k_rows(const RowsArgs A, int mode, int k_in_chunk,
@@ -3325,61 +3320,68 @@ __global__ __launch_bounds__(kMinRows) void k_min_rows(const MinArgs A, int from
 
 // ------------------------------------------------------------ normal modes
 
-// Mass-weighted Hessian of the static potential, one 3x3 block (i, j) per
-// thread, written row-major into D (3n x 3n).  Off-diagonal blocks:
-// k_e Q_i Q_j (delta/r^3 - 3 r r^T / r^5) / sqrt(M_i M_j), r = x_i - x_j.
-// Diagonal blocks: minus the sum of those over j (ascending j), plus the trap
-// curvature (pseudopotential and dc), divided by M_i.
-__global__ __launch_bounds__(256) void k_hessian(const double4* __restrict__ src,
-                                                 const double* __restrict__ qe,
-                                                 const double* __restrict__ mass, int64_t n,
-                                                 TrapDev T, double* __restrict__ D) {
+// Mass-weighted Hessian of the static potential, row-major into D (3n x 3n): one
+// workgroup per ion i, its threads take the 3x3 blocks (i, j).  Off-diagonal blocks:
+// k_e Q_i Q_j (delta/r^3 - 3 r r^T / r^5) / sqrt(M_i M_j), r = x_i - x_j.  Diagonal
+// block: minus the sum of those over j in ascending order (one thread per entry, from
+// LDS), plus the trap curvature (pseudopotential and dc), divided by M_i.  With one
+// thread per diagonal block, walking all ions, 64 ions took 45 us.
+constexpr int kHessBlock = 128;
+
+__global__ __launch_bounds__(kHessBlock) void k_hessian(const double4* __restrict__ src,
+                                                        const double* __restrict__ qe,
+                                                        const double* __restrict__ mass,
+                                                        int64_t n, TrapDev T,
+                                                        double* __restrict__ D) {
 #pragma clang fp contract(off)
-    const int64_t j = (int64_t)blockIdx.x * 16 + threadIdx.x % 16;
-    const int64_t i = (int64_t)blockIdx.y * 16 + threadIdx.x / 16;
-    if (i >= n || j >= n) return;
-    const int64_t m = 3 * n;
+    __shared__ double blk[9][kHessBlock + 1], sum[9];
+    const int64_t i = blockIdx.x, m = 3 * n;
+    const int tid = threadIdx.x;
     const double ke = 1.0 / (4.0 * kPi * kEps0);
     const double4 pi = src[i];
-    const double Qi = qe[i] * kElementaryCharge;
-    if (i != j) {
-        const double4 pj = src[j];
-        const double r[3] = {pi.x - pj.x, pi.y - pj.y, pi.z - pj.z};
-        const double r2 = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
-        const double w = 1.0 / sqrt(mass[i] * mass[j]);
-        double inv_r3 = 0.0, inv_r5 = 0.0, c = 0.0;
-        if (r2 != 0.0) {
-            const double inv_r = 1.0 / sqrt(r2);
-            inv_r3 = inv_r * inv_r * inv_r;
-            inv_r5 = inv_r3 * inv_r * inv_r;
-            c = ke * Qi * (qe[j] * kElementaryCharge);
+    const double Qi = qe[i] * kElementaryCharge, mi = mass[i];
+    double mine = 0.0;  // entry tid < 9 of the diagonal block
+    for (int64_t j0 = 0; j0 < n; j0 += kHessBlock) {
+        const int64_t j = j0 + tid;
+        if (j < n) {
+            const double4 pj = src[j];
+            const double r[3] = {pi.x - pj.x, pi.y - pj.y, pi.z - pj.z};
+            const double r2 = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
+            const double w = 1.0 / sqrt(mi * mass[j]);
+            double inv_r3 = 0.0, inv_r5 = 0.0, c = 0.0;
+            if (r2 != 0.0) {  // not itself nor an ion at the same place
+                const double inv_r = 1.0 / sqrt(r2);
+                inv_r3 = inv_r * inv_r * inv_r;
+                inv_r5 = inv_r3 * inv_r * inv_r;
+                c = ke * Qi * (qe[j] * kElementaryCharge);
+            }
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    const double h = c * ((a == b ? inv_r3 : 0.0) - 3.0 * r[a] * r[b] * inv_r5);
+                    blk[3 * a + b][tid] = h;
+                    if (j != i) D[(3 * i + a) * m + 3 * j + b] = h * w;
+                }
         }
-        for (int a = 0; a < 3; ++a)
-            for (int b = 0; b < 3; ++b)
-                D[(3 * i + a) * m + 3 * j + b] =
-                    c * ((a == b ? inv_r3 : 0.0) - 3.0 * r[a] * r[b] * inv_r5) * w;
-        return;
+        __syncthreads();
+        if (tid < 9) {
+            const int cnt = (int)min((int64_t)kHessBlock, n - j0);
+            for (int k = 0; k < cnt; ++k) mine -= blk[tid][k];
+        }
+        __syncthreads();
     }
-    double diag[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-    for (int64_t k = 0; k < n; ++k) {
-        if (k == i) continue;
-        const double4 pk = src[k];
-        const double r[3] = {pi.x - pk.x, pi.y - pk.y, pi.z - pk.z};
-        const double r2 = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
-        if (r2 == 0.0) continue;
-        const double inv_r = 1.0 / sqrt(r2);
-        const double inv_r3 = inv_r * inv_r * inv_r, inv_r5 = inv_r3 * inv_r * inv_r;
-        const double c = ke * Qi * (qe[k] * kElementaryCharge);
-        for (int a = 0; a < 3; ++a)
-            for (int b = 0; b < 3; ++b)
-                diag[a][b] -= c * ((a == b ? inv_r3 : 0.0) - 3.0 * r[a] * r[b] * inv_r5);
-    }
-    const double qm = Qi / mass[i];
+    if (tid < 9) sum[tid] = mine;
+    __syncthreads();
+    if (tid > 0) return;
+    double diag[3][3];
+    for (int k = 0; k < 9; ++k) diag[k / 3][k % 3] = sum[k];
+    const double qm = Qi / mi;
     diag[0][0] += Qi * qm * T.ps - Qi * T.a_dc;
     diag[1][1] += Qi * qm * T.ps - Qi * T.a_dc;
     diag[2][2] += 2.0 * Qi * T.a_dc;
     for (int a = 0; a < 3; ++a)
-        for (int b = 0; b < 3; ++b) D[(3 * i + a) * m + 3 * i + b] = diag[a][b] / mass[i];
+        for (int b = 0; b < 3; ++b) D[(3 * i + a) * m + 3 * i + b] = diag[a][b] / mi;
 }
 
 inline unsigned blocks_for(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
@@ -3831,8 +3833,7 @@ hipError_t launch_min_rows(const DevState& s, int precision, int from, bool move
 }
 
 hipError_t launch_hessian(const DevState& s, const TrapDev& T, double* D, hipStream_t st) {
-    const unsigned g = blocks_for(s.n, 16);
-    k_hessian<<<dim3(g, g), 256, 0, st>>>(s.src, s.qe, s.mass, s.n, T, D);
+    k_hessian<<<(unsigned)s.n, kHessBlock, 0, st>>>(s.src, s.qe, s.mass, s.n, T, D);
     return hipGetLastError();
 }
 
