@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <numeric>
 #include <string>
 #include <vector>
@@ -54,6 +55,8 @@ struct lion_sim {
     bool tile_bodies = false;  // every 256-ion tile holds ions of one body only, or none
     std::map<std::pair<int64_t, int>, hipGraphExec_t> graphs;  // (chunk length, kind)
     size_t eigh_bytes[2] = {SIZE_MAX, SIZE_MAX};  // its scratch, without / with vectors
+    std::vector<TrapDev> traps_up;    // what the device holds (batches)
+    hipEvent_t stage_ev[2] = {nullptr, nullptr};  // the halves of the staging memory
     void* eigh = nullptr;  // rocBLAS handle of the normal-mode solver (created on first use)
     std::string err;
 };
@@ -251,9 +254,153 @@ void clear_graphs(lion_sim* s) {
     s->graphs.clear();
 }
 
+// Pinned host memory through which states and results pass.  Allocating it costs some
+// hundred microseconds, so blocks of one size outlive the calls: a call leases one
+// for itself (each thread its own), at most kStageKept idle ones are kept, and all go
+// with the last handle.  A half of a block takes kStageIons ions of a state; larger
+// states go in pieces that alternate between the halves, so that the host copies one
+// while the device moves the next.
+constexpr int64_t kStageIons = 8192;
+constexpr size_t kStageKept = 4;
+std::mutex g_stage_mutex;
+std::vector<double*> g_stage_idle;
+int g_handles = 0;
+
+void stage_trim(size_t keep) {  // with the mutex held
+    while (g_stage_idle.size() > keep) {
+        (void)hipHostFree(g_stage_idle.back());
+        g_stage_idle.pop_back();
+    }
+}
+
+void count_handle(int by) {
+    std::lock_guard<std::mutex> lock(g_stage_mutex);
+    g_handles += by;
+    if (g_handles == 0) stage_trim(0);
+}
+
+class Stage {
+public:
+    explicit Stage(hipStream_t st) : stream_(st) {
+        {
+            std::lock_guard<std::mutex> lock(g_stage_mutex);
+            if (!g_stage_idle.empty()) {
+                p_ = g_stage_idle.back();
+                g_stage_idle.pop_back();
+            }
+        }
+        if (!p_)
+            status_ = hipHostMalloc((void**)&p_, 2 * 6 * kStageIons * sizeof(double), hipHostMallocPortable);
+    }
+    Stage(const Stage&) = delete;
+    Stage& operator=(const Stage&) = delete;
+    ~Stage() {
+        if (status_ != hipSuccess) return;
+        if (busy_) (void)hipStreamSynchronize(stream_);  // an error came before the call's own
+        std::lock_guard<std::mutex> lock(g_stage_mutex);
+        g_stage_idle.push_back(p_);
+        stage_trim(g_handles > 0 ? kStageKept : 0);
+    }
+    hipError_t status() const { return status_; }
+    double* half(int h) { return p_ + h * 6 * kStageIons; }
+    void idle() { busy_ = false; }  // the stream has been waited for
+
+private:
+    hipStream_t stream_;
+    double* p_ = nullptr;
+    hipError_t status_ = hipSuccess;
+    bool busy_ = true;
+};
+
+int stage_events(lion_sim* s) {
+    for (auto& e : s->stage_ev)
+        if (!e && s->n > kStageIons) LION_HIP(s, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    return LION_OK;
+}
+
+// Rows of all ions from the device (pos gives x, y, z when set, then a, b, c) into the
+// host arrays `to`, skipping those that are NULL.  Synchronises.
+int export_rows(lion_sim* s, const double4* pos, const double* a, const double* b,
+                const double* c, double* const* to) {
+    Stage stage(s->stream);
+    LION_HIP(s, stage.status());
+    int rc = stage_events(s);
+    if (rc) return rc;
+    const int rows = pos ? 6 : 3;
+    const int64_t n = s->n, piece = kStageIons, pieces = (n + piece - 1) / piece;
+    auto launch = [&](int64_t p) {
+        const hipError_t e = lion::launch_export(pos, a, b, c, p * piece, std::min(piece, n - p * piece),
+                                                 stage.half((int)(p & 1)), s->stream);
+        return e != hipSuccess || pieces == 1 ? e : hipEventRecord(s->stage_ev[p & 1], s->stream);
+    };
+    for (int64_t p = 0; p < std::min<int64_t>(2, pieces); ++p) LION_HIP(s, launch(p));
+    // fresh pages of large host arrays are faulted in (contents kept) while the device
+    // still works: 65536 ions after two steps, 400 us that would follow the wait
+    if (n * sizeof(double) >= (1 << 16))
+        for (int r = 0; r < rows; ++r)
+            for (int64_t i = 0; to[r] && i < n; i += 4096 / sizeof(double)) {
+                volatile double* q = to[r] + i;
+                *q = *q;
+            }
+    for (int64_t p = 0; p < pieces; ++p) {
+        if (pieces == 1)
+            LION_HIP(s, hipStreamSynchronize(s->stream));
+        else
+            LION_HIP(s, hipEventSynchronize(s->stage_ev[p & 1]));
+        const int64_t cnt = std::min(piece, n - p * piece);
+        for (int r = 0; r < rows; ++r)
+            if (to[r])
+                std::memcpy(to[r] + p * piece, stage.half((int)(p & 1)) + r * cnt, cnt * sizeof(double));
+        if (p + 2 < pieces) LION_HIP(s, launch(p + 2));
+    }
+    stage.idle();
+    return LION_OK;
+}
+
+// The six host rows of a state onto the device (queued; the caller synchronises).
+int import_state(lion_sim* s, Stage& stage, const double* const* from) {
+    int rc = stage_events(s);
+    if (rc) return rc;
+    const int64_t n = s->n, piece = kStageIons, pieces = (n + piece - 1) / piece;
+    for (int64_t p = 0; p < pieces; ++p) {
+        const int64_t cnt = std::min(piece, n - p * piece);
+        double* half = stage.half((int)(p & 1));
+        if (p >= 2) LION_HIP(s, hipEventSynchronize(s->stage_ev[p & 1]));
+        for (int r = 0; r < 6; ++r)
+            std::memcpy(half + r * cnt, from[r] + p * piece, cnt * sizeof(double));
+        LION_HIP(s, lion::launch_import(s->d, half, p * piece, cnt, s->stream));
+        if (pieces > 1) LION_HIP(s, hipEventRecord(s->stage_ev[p & 1], s->stream));
+    }
+    return LION_OK;
+}
+
 int upload_traps(lion_sim* s) {
     LION_HIP(s, hipMemcpyAsync(s->d.traps, s->traps.data(), s->traps.size() * sizeof(TrapDev),
                                hipMemcpyHostToDevice, s->stream));
+    s->traps_up = s->traps;
+    return LION_OK;
+}
+
+// Traps, cooling switches and step counter at the start of a call.  A batch whose
+// traps differ from the device's only by one common clock takes no copy either.
+int begin_call(lion_sim* s) {
+    if (!s->batched) {
+        LION_HIP(s, lion::launch_begin(s->d, &s->traps[0], 0.0, 0, s->cool, s->stream));
+        return LION_OK;
+    }
+    bool clock_only = s->traps_up.size() == s->traps.size();
+    const double t = s->traps[0].t_start;
+    for (size_t k = 0; k < s->traps.size() && clock_only; ++k) {
+        const TrapDev &a = s->traps[k], &b = s->traps_up[k];
+        clock_only = a.a_rf == b.a_rf && a.omega == b.omega && a.a_dc == b.a_dc && a.f == b.f &&
+                     a.dt == b.dt && a.h == b.h && a.ps == b.ps && a.t_start == t;
+    }
+    if (!clock_only) {
+        int rc = upload_traps(s);
+        if (rc) return rc;
+    }
+    LION_HIP(s, lion::launch_begin(s->d, nullptr, t, clock_only ? s->n_traps : 0, s->cool, s->stream));
+    if (clock_only) s->traps_up = s->traps;
     return LION_OK;
 }
 
@@ -269,8 +416,8 @@ int switch_cooling(lion_sim* s, bool on, bool baths) {
 }
 
 // Half-step factors of the beams and baths for step size dt, and the run-wide
-// step count, into device memory.  Uses one dt for every trap (the first).
-int upload_cooling(lion_sim* s, double dt) {
+// step count, into the handle's mirror.  Uses one dt for every trap (the first).
+int prepare_cooling(lion_sim* s, double dt) {
     const double h = 0.5 * dt;
     lion::CoolDev& C = s->cool;
     C.nbeams = C.nbaths = 0;
@@ -300,11 +447,7 @@ int upload_cooling(lion_sim* s, double dt) {
     C.avg_window = s->avg_window;
     C.avg_origin = s->avg_origin;
     const bool on = C.nbeams > 0 || C.nbaths > 0 || C.avg_window > 0;
-    int rc = switch_cooling(s, on, C.nbaths > 0);
-    if (rc) return rc;
-    LION_HIP(s, hipMemcpyAsync(s->d.cool, &s->cool, sizeof(lion::CoolDev), hipMemcpyHostToDevice,
-                               s->stream));
-    return LION_OK;
+    return switch_cooling(s, on, C.nbaths > 0);
 }
 
 // A single trap stepped inside one workgroup (the batched kernel with one trap).
@@ -330,10 +473,9 @@ int64_t chunk_len(const lion_sim* s) {
 // the handle (so a trap stepped inside one workgroup gets them from that kernel).
 int refresh_accel(lion_sim* s) {
     for (int k = 0; k < s->n_traps; ++k) s->traps[k].t_start = s->t_now[k];
-    int rc = upload_traps(s);
+    int rc = begin_call(s);
     if (rc) return rc;
     if (s->batched || small_path_active(s)) {
-        LION_HIP(s, hipMemsetAsync(s->d.counter, 0, sizeof(int64_t), s->stream));
         LION_HIP(s, lion::launch_batch_accel(s->d, s->precision, s->n_traps, s->max_trap, s->ls,
                                              s->stream));
         return LION_OK;
@@ -348,32 +490,31 @@ int refresh_accel(lion_sim* s) {
     return LION_OK;
 }
 
-// L steps of the kernels that step a trap inside one workgroup, as many per
-// launch as the bath table holds half-steps of.
-hipError_t enqueue_one_workgroup(lion_sim* s, int64_t L, hipStream_t st) {
+// Traps that step inside one workgroup each: a chunk is one launch (and the bath
+// draws), which no graph makes cheaper.
+bool one_workgroup(const lion_sim* s) { return s->batched || small_path_active(s); }
+
+// L steps of those kernels after k0 of the call, as many per launch as the bath table
+// holds half-steps of.
+hipError_t enqueue_one_workgroup(lion_sim* s, int64_t L, int64_t k0, hipStream_t st) {
     const int64_t most = s->ls.bath_on ? s->d.noise_h / 2 : L;
     hipError_t e = hipSuccess;
     for (int64_t done = 0; done < L && e == hipSuccess;) {
         const int64_t K = std::min(most, L - done);
-        if (s->ls.bath_on) e = lion::launch_noise(s->d, 2, (int)(2 * K), st);
+        if (s->ls.bath_on)
+            e = lion::launch_noise(s->d, false, 2 * (k0 + done) + 2, (int)(2 * K), st);
         if (e == hipSuccess)
-            e = lion::launch_batch(s->d, s->precision, s->n_traps, s->max_trap, s->ls, (int)K, 0, st);
-        if (e == hipSuccess) e = lion::launch_counter_add(s->d, K, st);
+            e = lion::launch_batch(s->d, s->precision, s->n_traps, s->max_trap, s->ls, (int)K,
+                                   k0 + done, st);
         done += K;
     }
     return e;
 }
 
-// Kernels of one chunk of L steps on stream st.
+// Kernels of one chunk of L steps of a trap that takes several workgroups, on
+// stream st.
 hipError_t enqueue_chunk(lion_sim* s, int64_t L, hipStream_t st) {
     hipError_t e = hipSuccess;
-    if (s->batched) return enqueue_one_workgroup(s, L, st);
-    if (small_path_active(s)) {
-        // the whole trap inside one workgroup
-        e = enqueue_one_workgroup(s, L, st);
-        if (e == hipSuccess && s->d.srcm) e = lion::launch_pack_mixed(s->d, st);
-        return e;
-    }
     const bool rigid = s->d.nbodies > 0;
     // bath table: the first block holds the drift's half-step and those of the
     // steps that follow, later blocks whole steps; step k (from 1) ends with its
@@ -386,7 +527,7 @@ hipError_t enqueue_chunk(lion_sim* s, int64_t L, hipStream_t st) {
         if (!s->ls.bath_on || (k - 1) % per != 0) return hipSuccess;
         const int64_t K = std::min(per, L - (k - 1));
         const int first = k == 1 ? 1 : 0;
-        return lion::launch_noise(s->d, (int)(2 * (k - steps) + 1 - first), (int)(2 * K) + first, st);
+        return lion::launch_noise(s->d, true, 2 * (k - steps) + 1 - first, (int)(2 * K) + first, st);
     };
     e = draws(1, 0);
     if (e != hipSuccess) return e;
@@ -463,7 +604,11 @@ int chunk_graph(lion_sim* s, int64_t L, hipGraphExec_t* out) {
     return LION_OK;
 }
 
-int run_chunk(lion_sim* s, int64_t L) {
+int run_chunk(lion_sim* s, int64_t L, int64_t k0) {
+    if (one_workgroup(s)) {
+        LION_HIP(s, enqueue_one_workgroup(s, L, k0, s->stream));
+        return LION_OK;
+    }
     if (s->cfg.use_graph == 2) {
         LION_HIP(s, enqueue_chunk(s, L, s->stream));
         return LION_OK;
@@ -656,7 +801,8 @@ int create_common(lion_sim** out, int32_t n_traps, const int64_t* n_per_trap, in
 
     // per-ion constants
     const int64_t np = d.n_pad;
-    std::vector<double> qm(np, 0.0), qe(np, 0.0), mass(np, 0.0);
+    std::vector<double> constants(3 * np, 0.0);  // qm, qe, mass: consecutive on the device too
+    double *qm = constants.data(), *qe = qm + np, *mass = qe + np;
     std::vector<int32_t> trap_of(np, 0);
     for (int k = 0; k < n_traps; ++k)
         for (int64_t i = s->offsets[k]; i < s->offsets[k + 1]; ++i) trap_of[i] = k;
@@ -682,22 +828,19 @@ int create_common(lion_sim** out, int32_t n_traps, const int64_t* n_per_trap, in
     std::vector<double4> zero_src(np, make_double4(0, 0, 0, 0));
     for (int64_t i = 0; i < n; ++i) zero_src[i].w = 1.5 * qe[i];
     hipStream_t st = s->stream;
-    bool ok = hipMemcpyAsync(d.qm, qm.data(), np * 8, hipMemcpyHostToDevice, st) == hipSuccess &&
-              hipMemcpyAsync(d.qe, qe.data(), np * 8, hipMemcpyHostToDevice, st) == hipSuccess &&
-              hipMemcpyAsync(d.mass, mass.data(), np * 8, hipMemcpyHostToDevice, st) == hipSuccess &&
+    // np is a multiple of 1024, so that arrays of doubles follow each other without gaps
+    bool ok = d.ax == d.vx + 3 * np && d.qe == d.qm + np && d.mass == d.qe + np &&
+              d.vavg == d.vacc + 3 * np &&
+              hipMemcpyAsync(d.qm, qm, 3 * np * 8, hipMemcpyHostToDevice, st) == hipSuccess &&
               hipMemcpyAsync(d.trap_of, trap_of.data(), np * 4, hipMemcpyHostToDevice, st) == hipSuccess &&
               hipMemcpyAsync(d.offsets, s->offsets.data(), (n_traps + 1) * 8, hipMemcpyHostToDevice, st) == hipSuccess &&
               hipMemcpyAsync(d.order, order.data(), n_traps * 4, hipMemcpyHostToDevice, st) == hipSuccess &&
               hipMemcpyAsync(d.src, zero_src.data(), np * sizeof(double4), hipMemcpyHostToDevice, st) == hipSuccess &&
-              hipMemsetAsync(d.vx, 0, 3 * np * 8, st) == hipSuccess &&
-              hipMemsetAsync(d.ax, 0, 3 * np * 8, st) == hipSuccess &&
-              hipMemsetAsync(d.counter, 0, 8, st) == hipSuccess &&
+              hipMemsetAsync(d.vx, 0, 6 * np * 8, st) == hipSuccess &&
               hipMemsetAsync(d.flags, 0, 16, st) == hipSuccess &&
               hipMemsetAsync(d.species, 0, np * 4, st) == hipSuccess &&
-              hipMemsetAsync(d.vacc, 0, 3 * np * 8, st) == hipSuccess &&
-              hipMemsetAsync(d.vavg, 0, 3 * np * 8, st) == hipSuccess &&
-              hipMemcpyAsync(d.cool, &s->cool, sizeof(lion::CoolDev), hipMemcpyHostToDevice, st) == hipSuccess &&
-              hipMemcpyAsync(d.traps, s->traps.data(), n_traps * sizeof(TrapDev), hipMemcpyHostToDevice, st) == hipSuccess;
+              hipMemsetAsync(d.vacc, 0, 6 * np * 8, st) == hipSuccess &&
+              (n_traps == 1 || upload_traps(s) == LION_OK) && begin_call(s) == LION_OK;
     if (ok && d.srcm) ok = lion::launch_pack_mixed(d, st) == hipSuccess;
     if (ok) ok = hipStreamSynchronize(st) == hipSuccess;
     if (!ok) {
@@ -705,6 +848,7 @@ int create_common(lion_sim** out, int32_t n_traps, const int64_t* n_per_trap, in
         return bail(fail(s, LION_ERR_HIP, "device initialisation failed"));
     }
     g_create_err.clear();
+    count_handle(1);
     *out = s;
     return LION_OK;
 }
@@ -853,25 +997,22 @@ int lion_set_state(lion_sim* s, const double* x, const double* y, const double* 
     if (check_handle(s)) return LION_ERR_ARG;
     if (!x || !y || !z || !vx || !vy || !vz) return fail(s, LION_ERR_ARG, "state array is NULL");
     if (!is_fin(t)) return fail(s, LION_ERR_ARG, "t not finite");
-    const int64_t n = s->n, np = s->d.n_pad;
-    std::vector<double4> src(np, make_double4(0, 0, 0, 0));
-    for (int64_t i = 0; i < n; ++i) {
+    const double* rows[6] = {x, y, z, vx, vy, vz};
+    for (int64_t i = 0; i < s->n; ++i)
         if (!is_fin(x[i]) || !is_fin(y[i]) || !is_fin(z[i]) || !is_fin(vx[i]) || !is_fin(vy[i]) ||
             !is_fin(vz[i]))
             return fail(s, LION_ERR_ARG, "state of ion " + std::to_string(i) + " not finite");
-        src[i] = make_double4(x[i], y[i], z[i], 1.5 * (s->charge[i] / lion::kElementaryCharge));
-    }
     LION_HIP(s, hipSetDevice(s->device));
     hipStream_t st = s->stream;
-    LION_HIP(s, hipMemcpyAsync(s->d.src, src.data(), np * sizeof(double4), hipMemcpyHostToDevice, st));
-    LION_HIP(s, hipMemcpyAsync(s->d.vx, vx, n * 8, hipMemcpyHostToDevice, st));
-    LION_HIP(s, hipMemcpyAsync(s->d.vy, vy, n * 8, hipMemcpyHostToDevice, st));
-    LION_HIP(s, hipMemcpyAsync(s->d.vz, vz, n * 8, hipMemcpyHostToDevice, st));
-    if (s->d.srcm) LION_HIP(s, lion::launch_pack_mixed(s->d, st));
+    Stage stage(st);
+    LION_HIP(s, stage.status());
+    int rc = import_state(s, stage, rows);
+    if (rc) return rc;
     std::fill(s->t_now.begin(), s->t_now.end(), t);
-    int rc = refresh_accel(s);
+    rc = refresh_accel(s);
     if (rc) return rc;
     LION_HIP(s, hipStreamSynchronize(st));
+    stage.idle();
     s->state_set = true;
     if (s->rigid_on) return rigid_setup(s);
     return LION_OK;
@@ -1107,12 +1248,11 @@ int lion_get_time_average(lion_sim* s, double* vx, double* vy, double* vz,
     if (s->avg_window <= 0) return fail(s, LION_ERR_STATE, "time averaging is off");
     const int64_t done = s->steps_done - s->avg_origin;
     if (done < s->avg_window) return fail(s, LION_ERR_STATE, "no averaging window completed yet");
-    const int64_t n = s->n, np = s->d.n_pad;
+    const int64_t np = s->d.n_pad;
     LION_HIP(s, hipSetDevice(s->device));
-    LION_HIP(s, hipMemcpyAsync(vx, s->d.vavg, n * 8, hipMemcpyDeviceToHost, s->stream));
-    LION_HIP(s, hipMemcpyAsync(vy, s->d.vavg + np, n * 8, hipMemcpyDeviceToHost, s->stream));
-    LION_HIP(s, hipMemcpyAsync(vz, s->d.vavg + 2 * np, n * 8, hipMemcpyDeviceToHost, s->stream));
-    LION_HIP(s, hipStreamSynchronize(s->stream));
+    double* const to[3] = {vx, vy, vz};
+    const int rc = export_rows(s, nullptr, s->d.vavg, s->d.vavg + np, s->d.vavg + 2 * np, to);
+    if (rc) return rc;
     *window_end_step = s->avg_origin + (done / s->avg_window) * s->avg_window;
     return LION_OK;
 }
@@ -1140,24 +1280,24 @@ static int step_common(lion_sim* s, int64_t nsteps, const double* dts) {
         T.f = std::exp(-(T.gamma * dts[k]) * 0.5);
         T.t_start = s->t_now[k];
     }
-    int rc = upload_traps(s);
-    if (rc) return rc;
     bool cooling = false;
     for (const auto& B : s->beams) cooling = cooling || B.gamma > 0.0;
     for (const auto& T : s->baths) cooling = cooling || T.tau > 0.0;
     for (int k = 1; k < s->n_traps && cooling; ++k)
         if (dts[k] != dts[0])
             return fail(s, LION_ERR_UNSUPPORTED, "cooling beams and baths need one dt for all traps");
-    rc = upload_cooling(s, dts[0]);
+    int rc = prepare_cooling(s, dts[0]);
+    if (rc == LION_OK) rc = begin_call(s);
     if (rc) return rc;
-    LION_HIP(s, hipMemsetAsync(s->d.counter, 0, sizeof(int64_t), s->stream));
     const int64_t S = chunk_len(s);
     for (int64_t done = 0; done < nsteps;) {
         const int64_t L = std::min(S, nsteps - done);
-        rc = run_chunk(s, L);
+        rc = run_chunk(s, L, done);
         if (rc) return rc;
         done += L;
     }
+    // the one-workgroup kernels leave the FP32 stream of a single trap behind
+    if (small_path_active(s) && s->d.srcm) LION_HIP(s, lion::launch_pack_mixed(s->d, s->stream));
     for (int k = 0; k < s->n_traps; ++k) s->t_now[k] = s->traps[k].t_start + (double)nsteps * dts[k];
     s->steps_done += nsteps;
     return LION_OK;
@@ -1178,7 +1318,7 @@ int lion_step_batch(lion_sim* s, int64_t nsteps, const double* dt_per_trap) {
 int lion_prepare_step(lion_sim* s, int64_t nsteps) {
     if (check_handle(s)) return LION_ERR_ARG;
     if (nsteps < 0) return fail(s, LION_ERR_ARG, "nsteps must be >= 0");
-    if (nsteps == 0 || s->cfg.use_graph == 2) return LION_OK;
+    if (nsteps == 0 || s->cfg.use_graph == 2 || one_workgroup(s)) return LION_OK;
     LION_HIP(s, hipSetDevice(s->device));
     int rc_cool = switch_cooling(s, cooling_on(s), baths_on(s));
     if (rc_cool) return rc_cool;
@@ -1199,20 +1339,10 @@ int lion_get_state(const lion_sim* cs, double* x, double* y, double* z, double* 
                    double* vz, double* t) {
     lion_sim* s = const_cast<lion_sim*>(cs);
     if (check_handle(s)) return LION_ERR_ARG;
-    const int64_t n = s->n;
     LION_HIP(s, hipSetDevice(s->device));
-    std::vector<double4> src(n);
-    hipStream_t st = s->stream;
-    LION_HIP(s, hipMemcpyAsync(src.data(), s->d.src, n * sizeof(double4), hipMemcpyDeviceToHost, st));
-    if (vx) LION_HIP(s, hipMemcpyAsync(vx, s->d.vx, n * 8, hipMemcpyDeviceToHost, st));
-    if (vy) LION_HIP(s, hipMemcpyAsync(vy, s->d.vy, n * 8, hipMemcpyDeviceToHost, st));
-    if (vz) LION_HIP(s, hipMemcpyAsync(vz, s->d.vz, n * 8, hipMemcpyDeviceToHost, st));
-    LION_HIP(s, hipStreamSynchronize(st));
-    for (int64_t i = 0; i < n; ++i) {
-        if (x) x[i] = src[i].x;
-        if (y) y[i] = src[i].y;
-        if (z) z[i] = src[i].z;
-    }
+    double* const to[6] = {x, y, z, vx, vy, vz};
+    const int rc = export_rows(s, s->d.src, s->d.vx, s->d.vy, s->d.vz, to);
+    if (rc) return rc;
     if (t) *t = s->t_now[0];
     return LION_OK;
 }
@@ -1224,13 +1354,8 @@ int lion_compute_accel(lion_sim* s, double* ax, double* ay, double* az) {
     LION_HIP(s, hipSetDevice(s->device));
     int rc = refresh_accel(s);
     if (rc) return rc;
-    const int64_t n = s->n;
-    hipStream_t st = s->stream;
-    LION_HIP(s, hipMemcpyAsync(ax, s->d.ax, n * 8, hipMemcpyDeviceToHost, st));
-    LION_HIP(s, hipMemcpyAsync(ay, s->d.ay, n * 8, hipMemcpyDeviceToHost, st));
-    LION_HIP(s, hipMemcpyAsync(az, s->d.az, n * 8, hipMemcpyDeviceToHost, st));
-    LION_HIP(s, hipStreamSynchronize(st));
-    return LION_OK;
+    double* const to[3] = {ax, ay, az};
+    return export_rows(s, nullptr, s->d.ax, s->d.ay, s->d.az, to);
 }
 
 size_t lion_normal_modes_workspace_bytes(lion_sim* s) {
@@ -1328,11 +1453,15 @@ int lion_minimize(lion_sim* s, double dt, double dmax, double ftol, int64_t max_
     if (!s->has_bodies && lion::min_path(s->d) == lion::MinPath::kOne) {
         // many iterations per launch, the starting forces included
         const int64_t per_launch = 2000;
+        Stage stage(st);
+        LION_HIP(s, stage.status());
         for (bool first = true; first || !m.done; first = false) {
-            LION_HIP(s, lion::launch_min_one(s->d, s->precision, m, first, per_launch, st));
-            LION_HIP(s, hipMemcpyAsync(&m, s->d.minst, sizeof(m), hipMemcpyDeviceToHost, st));
+            LION_HIP(s, lion::launch_min_one(s->d, s->precision, m, first, per_launch,
+                                             (lion::MinDev*)stage.half(0), st));
             LION_HIP(s, hipStreamSynchronize(st));
+            m = *(const lion::MinDev*)stage.half(0);
         }
+        stage.idle();
         if (s->d.srcm) LION_HIP(s, lion::launch_pack_mixed(s->d, st));
         if (iterations) *iterations = m.iterations;
         if (fmax) *fmax = m.fmax;
@@ -1367,11 +1496,12 @@ int lion_get_energy(lion_sim* s, double* kinetic, double* coulomb, double* dc_tr
     if (!s->state_set) return fail(s, LION_ERR_STATE, "lion_set_state has not been called");
     LION_HIP(s, hipSetDevice(s->device));
     hipStream_t st = s->stream;
-    double* sums = nullptr;
-    double e[3] = {0.0, 0.0, 0.0};
-    LION_HIP(s, lion::launch_energy(s->d, s->n_traps, &sums, st));
-    LION_HIP(s, hipMemcpyAsync(e, sums, sizeof(e), hipMemcpyDeviceToHost, st));
+    Stage stage(st);
+    LION_HIP(s, stage.status());
+    LION_HIP(s, lion::launch_energy(s->d, s->n_traps, stage.half(0), st));
     LION_HIP(s, hipStreamSynchronize(st));
+    stage.idle();
+    const double* e = stage.half(0);
     const double ke_e2 = lion::kElementaryCharge * lion::kElementaryCharge / (4.0 * lion::kPi * lion::kEps0);
     if (kinetic) *kinetic = e[0];
     if (coulomb) *coulomb = ke_e2 * e[1];
@@ -1420,8 +1550,11 @@ void lion_destroy(lion_sim* s) {
     (void)hipStreamSynchronize(s->stream);
     clear_graphs(s);
     lion::eigh_handle_destroy(s->eigh);  // after the synchronisation: no solver work pending
+    for (auto& e : s->stage_ev)
+        if (e) (void)hipEventDestroy(e);
     if (s->capture) (void)hipStreamDestroy(s->capture);
     delete s;
+    count_handle(-1);
 }
 
 int lion_set_kernel_config(lion_sim* s, const lion_kernel_config* c) {
@@ -1535,12 +1668,10 @@ int lion_time_batch_kernel(lion_sim* s, int32_t reps, int32_t nsteps, double dt,
         T.f = std::exp(-(T.gamma * dt) * 0.5);
         T.t_start = s->t_now[k];
     }
-    rc = upload_traps(s);
-    if (rc) return rc;
-    rc = upload_cooling(s, dt);
+    rc = prepare_cooling(s, dt);
+    if (rc == LION_OK) rc = begin_call(s);
     if (rc) return rc;
     hipStream_t st = s->stream;
-    LION_HIP(s, hipMemsetAsync(s->d.counter, 0, sizeof(int64_t), st));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     LION_HIP(s, hipEventCreate(&e0));
     if (hipEventCreate(&e1) != hipSuccess) {
@@ -1549,7 +1680,7 @@ int lion_time_batch_kernel(lion_sim* s, int32_t reps, int32_t nsteps, double dt,
     }
     if (hipEventRecord(e0, st) != hipSuccess) rc = fail(s, LION_ERR_HIP, "hipEventRecord failed");
     for (int r = 0; r < reps && rc == LION_OK; ++r) {
-        if (enqueue_one_workgroup(s, nsteps, st) != hipSuccess)
+        if (enqueue_one_workgroup(s, nsteps, (int64_t)r * nsteps, st) != hipSuccess)
             rc = fail(s, LION_ERR_HIP, "batch kernel timing launch failed");
     }
     if (rc == LION_OK && hipEventRecord(e1, st) != hipSuccess) rc = fail(s, LION_ERR_HIP, "hipEventRecord failed");

@@ -220,9 +220,21 @@ constexpr int64_t kSymDefaultIonsMixed = 8192;
 
 // Kernel launchers (lion_kernels.hip).  All return hipSuccess or the launch error.
 // Bath kicks of half_steps (<= s.noise_h) half-steps into the table, from the
-// half-step 2 (steps completed before the launch) + g0 on; half-step 2 s + h is
-// half h of the run-wide step s (from 1).
-hipError_t launch_noise(const DevState& s, int g0, int half_steps, hipStream_t st);
+// half-step 2 (run-wide steps before the call, plus s.counter's with use_counter) + g0
+// on; half-step 2 s + h is half h of the run-wide step s (from 1).
+hipError_t launch_noise(const DevState& s, bool use_counter, int64_t g0, int half_steps,
+                        hipStream_t st);
+// The start of a call: counter 0, cooling switches, and the trap of a single-trap
+// handle or (n_traps > 0) the common clock of a batch's first n_traps traps.
+hipError_t launch_begin(const DevState& s, const TrapDev* one_trap, double t_start, int n_traps,
+                        const CoolDev& cool, hipStream_t st);
+// Ions [i0, i0 + cnt) of pos (x, y, z; or NULL) and of a, b, c as rows of cnt doubles
+// into `out`, and of a state's six rows at `in` into s; out and in are pinned host
+// memory.
+hipError_t launch_export(const double4* pos, const double* a, const double* b, const double* c,
+                         int64_t i0, int64_t cnt, double* out, hipStream_t st);
+hipError_t launch_import(const DevState& s, const double* in, int64_t i0, int64_t cnt,
+                         hipStream_t st);
 // bath_idx: table index of the step's first half (launch_drift) or of the second
 // half of the step that ends (launch_update, launch_rows; the first half of the
 // next step follows it).
@@ -240,9 +252,9 @@ hipError_t launch_pack_inputs(const double* x, const double* y, const double* z,
 // Message returned by lion_last_error(NULL) (calls without a handle).
 void set_handle_free_error(const std::string& msg);
 // Steps of a batch (or a lone trap in one workgroup); with a bath on, the table
-// holds the 2 nsteps half-steps from index 0.
+// holds the 2 nsteps half-steps from index 0.  k0: steps of the call done before.
 hipError_t launch_batch(const DevState& s, int precision, int n_traps, int max_trap,
-                        const LaunchShape& ls, int nsteps, int mode_first, hipStream_t st);
+                        const LaunchShape& ls, int nsteps, int64_t k0, hipStream_t st);
 hipError_t launch_batch_accel(const DevState& s, int precision, int n_traps, int max_trap,
                               const LaunchShape& ls, hipStream_t st);
 hipError_t launch_rigid_wrench(const DevState& s, bool end_kick, hipStream_t st);
@@ -257,9 +269,10 @@ enum class MinPath { kOne, kRows, kLaunches };
 constexpr int64_t kMinOneIons = 160;
 MinPath min_path(const DevState& s);
 // Up to `iters` iterations; `first`: parameters from init and forces at the current
-// positions before them, else s.minst goes on.  s.minst holds the state after.
+// positions before them, else s.minst goes on.  s.minst and *out (pinned host memory)
+// hold the state after.
 hipError_t launch_min_one(const DevState& s, int precision, const MinDev& init, bool first,
-                          int64_t iters, hipStream_t st);
+                          int64_t iters, MinDev* out, hipStream_t st);
 // One iteration (move) reading side `from` (0: the handle's arrays) and writing the
 // other, or (!move) the forces and sums that the first starts from, on side 0.
 hipError_t launch_min_rows(const DevState& s, int precision, int from, bool move, hipStream_t st);
@@ -292,9 +305,9 @@ hipError_t launch_rows(const DevState& s, int precision, const LaunchShape& ls, 
                        int k_in_chunk, int parity_in, bool home_out, int bath_idx,
                        hipStream_t st);
 hipError_t launch_counter_add(const DevState& s, int64_t k, hipStream_t st);
-// Energies of all traps: *out is the device address of {kinetic (J), sum over
-// pairs of q_i q_j / r_ij (e^2/m), static trap energy (J)}.
-hipError_t launch_energy(const DevState& s, int n_traps, double** out, hipStream_t st);
+// Energies of all traps into out (pinned host memory): kinetic (J), sum over pairs of
+// q_i q_j / r_ij (e^2/m), static trap energy (J).
+hipError_t launch_energy(const DevState& s, int n_traps, double* out, hipStream_t st);
 hipError_t launch_check_finite(const DevState& s, hipStream_t st);
 // Counts ions beyond r_lost (m) of the trap centre, or non-finite, into flags[1].
 hipError_t launch_count_lost(const DevState& s, double r_lost, hipStream_t st);

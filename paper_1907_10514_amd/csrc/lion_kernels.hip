@@ -334,7 +334,7 @@ __device__ __forceinline__ void velocity_half(const CoolRef& R, int32_t species,
     }
 }
 
-// Fills the bath table for the half-steps 2 (step_base + *counter) + g0 + idx,
+// Fills the bath table for the half-steps 2 (step_base [+ *counter]) + g0 + idx,
 // idx = blockIdx.y (half-step 2 s + h is half h of the run-wide step s), one
 // thread per ion.  Bound by FP64 issue of log, sqrt, sin and cos and spread over
 // the whole chip: 100 ions x 400 half-steps take about as long as one launch.
@@ -344,13 +344,14 @@ __device__ __forceinline__ void velocity_half(const CoolRef& R, int32_t species,
 __global__ __launch_bounds__(256) void k_noise(const double* __restrict__ mass,
                                                const int32_t* __restrict__ species, int64_t n,
                                                int64_t stride, const CoolDev* __restrict__ C,
-                                               const int64_t* __restrict__ counter, int g0,
+                                               const int64_t* __restrict__ counter,
+                                               int64_t g0,
                                                double* __restrict__ factor,
                                                double* __restrict__ kicks) {
 #pragma clang fp contract(off)
     const int64_t ion = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (ion >= n) return;
-    const int64_t h = 2 * (C->step_base + *counter) + g0 + blockIdx.y;
+    const int64_t h = 2 * (C->step_base + (counter ? *counter : 0)) + g0 + blockIdx.y;
     const int32_t sp = species[ion];
     const double m = mass[ion];
     const int nt = C->nbaths;
@@ -479,6 +480,67 @@ __global__ __launch_bounds__(256) void k_drift(double4* __restrict__ src,
     vy[i] = v;
     vz[i] = w;
     if (srcm) srcm[i] = make_src(p.x, p.y, p.z, qe[i]);
+}
+
+// The start of a call: the step counter to zero, the cooling switches, and the trap of
+// a single-trap handle (one_trap) or the common clock of a batch (n_traps > 0), all by
+// value.  One launch instead of two copies and a fill, each of which costs about as
+// much as the 20 steps of 8 ions that follow.
+__global__ __launch_bounds__(256) void k_begin(const TrapDev T, int one_trap, double t_start,
+                                               int n_traps, TrapDev* __restrict__ traps,
+                                               const CoolDev C, CoolDev* __restrict__ cool,
+                                               int64_t* __restrict__ counter) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *counter = 0;
+        *cool = C;
+        if (one_trap) traps[0] = T;
+    }
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k < n_traps) traps[k].t_start = t_start;
+}
+
+// Ions [i0, i0 + cnt) of up to six arrays (pos gives the first three when set) into
+// rows of `out`, which is host memory: the writes cross the bus as they are made.
+struct ExportArgs {
+    const double4* pos;
+    const double* f[3];
+    int64_t i0, cnt;
+    double* out;
+};
+
+__global__ __launch_bounds__(256) void k_export(const ExportArgs A) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= A.cnt) return;
+    double* o = A.out + i;
+    if (A.pos) {
+        const double4 p = A.pos[A.i0 + i];
+        o[0] = p.x;
+        o[A.cnt] = p.y;
+        o[2 * A.cnt] = p.z;
+        o += 3 * A.cnt;
+    }
+    o[0] = A.f[0][A.i0 + i];
+    o[A.cnt] = A.f[1][A.i0 + i];
+    o[2 * A.cnt] = A.f[2][A.i0 + i];
+}
+
+// The reverse for a new state: rows x, y, z, vx, vy, vz of ions [i0, i0 + cnt) from
+// host memory into the source streams and the velocities.
+__global__ __launch_bounds__(256) void k_import(const double* __restrict__ in, int64_t i0,
+                                                int64_t cnt, const double* __restrict__ qe,
+                                                double4* __restrict__ src,
+                                                MixedSrc* __restrict__ srcm,
+                                                double* __restrict__ vx, double* __restrict__ vy,
+                                                double* __restrict__ vz) {
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (k >= cnt) return;
+    const int64_t i = i0 + k;
+    const double x = in[k], y = in[cnt + k], z = in[2 * cnt + k], q = qe[i];
+    src[i] = make_double4(x, y, z, 1.5 * q);
+    if (srcm) srcm[i] = make_src(x, y, z, q);
+    vx[i] = in[3 * cnt + k];
+    vy[i] = in[4 * cnt + k];
+    vz[i] = in[5 * cnt + k];
 }
 
 // Inputs of the allocation-free force evaluation in the layout of the pair and
@@ -1647,7 +1709,7 @@ __global__ void k_counter_add(int64_t* counter, int64_t k) {
 // against a tile of 256 sources, 64 of them per wave, read through scalar
 // loads; the blocks stride over the units of the upper triangle of tiles.
 // Bound by FP64 VALU issue (15 operations and a quarter-rate v_rsq_f64 per
-// pair).  A lion_get_energy call at 16384 ions takes 117 us, against 3926 us with
+// pair).  A lion_get_energy call at 16384 ions takes 106 us, against 3926 us with
 // one thread per ion walking all sources and the sums on the host.  Sums within a thread's unit are plain FP64 (at most 128 terms), all
 // others carry a compensation, in a fixed order.
 
@@ -2134,8 +2196,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
                                                  const BathTable bath,
                                                  const int64_t* __restrict__ offsets,
                                                  const int32_t* __restrict__ order,
-                                                 const int64_t* __restrict__ counter,
-                                                 double* __restrict__ vacc,
+                                                 int64_t k0, double* __restrict__ vacc,
                                                  double* __restrict__ vavg, int64_t n_pad,
                                                  int nsteps, int accel_only, double uq,
                                                  int tpt_req) {
@@ -2185,7 +2246,6 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
     const int jb = min(jpart * jlen, send);
     const int je = min(jb + jlen, send);
     const TrapDev T = traps[tr];
-    const int64_t k0 = *counter;
     // a lone trap (the small-trap path) is latency-bound: one target per thread
     // below kBatchTpt4 ions saves the extra reduction rounds
     const int tpt2_from = gridDim.x == 1 ? kBatchTpt4 : kBatchTpt2;
@@ -2431,8 +2491,7 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
                                              const BathTable bath,
                                              const int64_t* __restrict__ offsets,
                                              const int32_t* __restrict__ order,
-                                             const int64_t* __restrict__ counter,
-                                             double* __restrict__ vacc,
+                                             int64_t k0, double* __restrict__ vacc,
                                              double* __restrict__ vavg, int64_t n_pad,
                                              int nsteps, int accel_only) {
     using S = typename BatchSrc<PREC>::T;
@@ -2447,7 +2506,6 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
     const int ti = lane / P, part = lane - ti * P;
     const bool owner = part == 0 && ti < m;
     const TrapDev T = traps[tr];
-    const int64_t k0 = *counter;
     // with cooling: the beams in LDS, the baths of the next half-step loaded ahead
     __shared__ BeamDev beams[X ? kMaxBeams : 1];
     CoolRef cr = cool_switches<X>(cool);
@@ -2934,6 +2992,7 @@ struct MinArgs {
     const double *qm, *qe, *mass;
     const TrapDev* traps;
     MinDev* ms[2];         // state before and after an iteration
+    MinDev* out;           // k_min_one: the state again, in host memory
     double* part[2];       // per workgroup {v.F, F.F, max |F|}
     int64_t n;
 };
@@ -3103,6 +3162,7 @@ __global__ __launch_bounds__(kMinOne) void k_min_one(const MinArgs A, MinDev ini
         o.iterations = it;
         o.done = done ? 1 : 0;
         *A.ms[0] = o;
+        *A.out = o;
     }
 }
 
@@ -3434,22 +3494,22 @@ hipError_t pair_mixed_dispatch_l(const DevState& s, const LaunchShape& ls, int64
 
 template <int PREC, int BLOCK, bool X>
 hipError_t batch_launch(const DevState& s, int n_traps, int max_trap, int nsteps,
-                        int accel_only, double uq, int tpt, hipStream_t st) {
+                        int accel_only, int64_t k0, double uq, int tpt, hipStream_t st) {
     const size_t stream_bytes = (size_t)max_trap * sizeof(double4);
     k_batch<PREC, BLOCK, X><<<n_traps, BLOCK, stream_bytes, st>>>(s.src, s.vx, s.vy, s.vz, s.ax, s.ay,
                                                        s.az, s.qm, s.qe, s.species, s.traps,
                                                        s.cool, bath_table(s), s.offsets, s.order,
-                                                       s.counter, s.vacc, s.vavg, s.n_pad,
+                                                       k0, s.vacc, s.vavg, s.n_pad,
                                                        nsteps, accel_only, uq, tpt);
     return hipGetLastError();
 }
 
 template <int PREC, int P, int W, bool X>
-hipError_t wave_launch_p(const DevState& s, int n_traps, int nsteps, int accel_only,
+hipError_t wave_launch_p(const DevState& s, int n_traps, int nsteps, int accel_only, int64_t k0,
                          hipStream_t st) {
     k_wave<PREC, P, W, X><<<n_traps, 64 * W, 0, st>>>(s.src, s.vx, s.vy, s.vz, s.ax, s.ay, s.az,
                                                       s.qm, s.qe, s.species, s.traps, s.cool,
-                                                      bath_table(s), s.offsets, s.order, s.counter,
+                                                      bath_table(s), s.offsets, s.order, k0,
                                                       s.vacc, s.vavg, s.n_pad, nsteps,
                                                       accel_only);
     return hipGetLastError();
@@ -3467,12 +3527,12 @@ inline int wave_parts(int max_trap) {
 
 template <int PREC, bool X>
 hipError_t wave_launch(const DevState& s, int n_traps, int max_trap, int nsteps, int accel_only,
-                       hipStream_t st) {
+                       int64_t k0, hipStream_t st) {
     switch (wave_parts(max_trap)) {
-        case 8: return wave_launch_p<PREC, 8, 1, X>(s, n_traps, nsteps, accel_only, st);
-        case 4: return wave_launch_p<PREC, 4, 1, X>(s, n_traps, nsteps, accel_only, st);
-        case 2: return wave_launch_p<PREC, 2, 1, X>(s, n_traps, nsteps, accel_only, st);
-        default: return wave_launch_p<PREC, 1, 1, X>(s, n_traps, nsteps, accel_only, st);
+        case 8: return wave_launch_p<PREC, 8, 1, X>(s, n_traps, nsteps, accel_only, k0, st);
+        case 4: return wave_launch_p<PREC, 4, 1, X>(s, n_traps, nsteps, accel_only, k0, st);
+        case 2: return wave_launch_p<PREC, 2, 1, X>(s, n_traps, nsteps, accel_only, k0, st);
+        default: return wave_launch_p<PREC, 1, 1, X>(s, n_traps, nsteps, accel_only, k0, st);
     }
 }
 
@@ -3481,37 +3541,37 @@ hipError_t wave_launch(const DevState& s, int n_traps, int max_trap, int nsteps,
 constexpr int kWaveMultiIons = 48;
 template <int PREC, bool X>
 hipError_t wave_launch_multi(const DevState& s, int n_traps, int block, int nsteps,
-                             int accel_only, hipStream_t st) {
+                             int accel_only, int64_t k0, hipStream_t st) {
     switch (block) {
-        case 1024: return wave_launch_p<PREC, 8, 16, X>(s, n_traps, nsteps, accel_only, st);
-        case 512: return wave_launch_p<PREC, 8, 8, X>(s, n_traps, nsteps, accel_only, st);
-        default: return wave_launch_p<PREC, 8, 4, X>(s, n_traps, nsteps, accel_only, st);
+        case 1024: return wave_launch_p<PREC, 8, 16, X>(s, n_traps, nsteps, accel_only, k0, st);
+        case 512: return wave_launch_p<PREC, 8, 8, X>(s, n_traps, nsteps, accel_only, k0, st);
+        default: return wave_launch_p<PREC, 8, 4, X>(s, n_traps, nsteps, accel_only, k0, st);
     }
 }
 
 template <int PREC, bool X>
 hipError_t batch_dispatch_x(const DevState& s, int n_traps, int max_trap, int block, int nsteps,
-                            int accel_only, double uq, int tpt, hipStream_t st) {
+                            int accel_only, int64_t k0, double uq, int tpt, hipStream_t st) {
     // traps of at most 48 ions and block / 8: the wave kernel on block / 64 waves
     // (us per step FP64 / FP32 pairs against the batched kernel: 20 ions 0.88 / 0.99
     // against 1.15 / 1.30, 32 ions 1.02 / 1.13 against 1.32 / 1.48, 48 ions 1.31 /
     // 1.39 against 1.50 / 1.49; 64 ions 1.64 / 1.63 against 1.63 / 1.52 and 100
     // ions 3.29 / 3.03 against 2.72 / 2.35, so larger traps keep the batched kernel)
     if (block != 64 && 8 * max_trap <= block && max_trap <= kWaveMultiIons)
-        return wave_launch_multi<PREC, X>(s, n_traps, block, nsteps, accel_only, st);
+        return wave_launch_multi<PREC, X>(s, n_traps, block, nsteps, accel_only, k0, st);
     switch (block) {
-        case 64: return wave_launch<PREC, X>(s, n_traps, max_trap, nsteps, accel_only, st);
-        case 512: return batch_launch<PREC, 512, X>(s, n_traps, max_trap, nsteps, accel_only, uq, tpt, st);
-        case 1024: return batch_launch<PREC, 1024, X>(s, n_traps, max_trap, nsteps, accel_only, uq, tpt, st);
-        default: return batch_launch<PREC, 256, X>(s, n_traps, max_trap, nsteps, accel_only, uq, tpt, st);
+        case 64: return wave_launch<PREC, X>(s, n_traps, max_trap, nsteps, accel_only, k0, st);
+        case 512: return batch_launch<PREC, 512, X>(s, n_traps, max_trap, nsteps, accel_only, k0, uq, tpt, st);
+        case 1024: return batch_launch<PREC, 1024, X>(s, n_traps, max_trap, nsteps, accel_only, k0, uq, tpt, st);
+        default: return batch_launch<PREC, 256, X>(s, n_traps, max_trap, nsteps, accel_only, k0, uq, tpt, st);
     }
 }
 
 template <int PREC>
 hipError_t batch_dispatch(const DevState& s, int n_traps, int max_trap, int block, int nsteps, int accel_only,
-                          bool cool_on, double uq, int tpt, hipStream_t st) {
-    return cool_on ? batch_dispatch_x<PREC, true>(s, n_traps, max_trap, block, nsteps, accel_only, uq, tpt, st)
-                   : batch_dispatch_x<PREC, false>(s, n_traps, max_trap, block, nsteps, accel_only, uq, tpt, st);
+                          int64_t k0, bool cool_on, double uq, int tpt, hipStream_t st) {
+    return cool_on ? batch_dispatch_x<PREC, true>(s, n_traps, max_trap, block, nsteps, accel_only, k0, uq, tpt, st)
+                   : batch_dispatch_x<PREC, false>(s, n_traps, max_trap, block, nsteps, accel_only, k0, uq, tpt, st);
 }
 
 }  // namespace
@@ -3528,9 +3588,11 @@ hipError_t launch_drift(const DevState& s, bool cool_on, int bath_idx, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_noise(const DevState& s, int g0, int half_steps, hipStream_t st) {
+hipError_t launch_noise(const DevState& s, bool use_counter, int64_t g0, int half_steps,
+                        hipStream_t st) {
     k_noise<<<dim3(blocks_for(s.n, 256), half_steps), 256, 0, st>>>(
-        s.mass, s.species, s.n, s.noise_stride, s.cool, s.counter, g0, s.noise_c, s.noise);
+        s.mass, s.species, s.n, s.noise_stride, s.cool, use_counter ? s.counter : nullptr, g0,
+        s.noise_c, s.noise);
     return hipGetLastError();
 }
 
@@ -3796,9 +3858,10 @@ MinPath min_path(const DevState& s) {
 }
 
 hipError_t launch_min_one(const DevState& s, int precision, const MinDev& init, bool first,
-                          int64_t iters, hipStream_t st) {
+                          int64_t iters, MinDev* out, hipStream_t st) {
     if (s.n > kMinOneIons) return hipErrorInvalidValue;
-    const MinArgs A = min_args(s);
+    MinArgs A = min_args(s);
+    A.out = out;
     const size_t lds = (size_t)s.n * sizeof(double4);
     const int block = s.n <= 32 ? 256 : (s.n <= 64 ? 512 : kMinOne);
     switch (precision) {
@@ -3838,20 +3901,20 @@ hipError_t launch_hessian(const DevState& s, const TrapDev& T, double* D, hipStr
 }
 
 hipError_t launch_batch(const DevState& s, int precision, int n_traps, int max_trap,
-                        const LaunchShape& ls, int nsteps, int, hipStream_t st) {
+                        const LaunchShape& ls, int nsteps, int64_t k0, hipStream_t st) {
     switch (precision) {
-        case 0: return batch_dispatch<0>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, ls.cool_on, ls.uniform_q, ls.batch_tpt, st);
-        case 2: return batch_dispatch<2>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, ls.cool_on, ls.uniform_q, ls.batch_tpt, st);
-        default: return batch_dispatch<1>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, ls.cool_on, ls.uniform_q, ls.batch_tpt, st);
+        case 0: return batch_dispatch<0>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, k0, ls.cool_on, ls.uniform_q, ls.batch_tpt, st);
+        case 2: return batch_dispatch<2>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, k0, ls.cool_on, ls.uniform_q, ls.batch_tpt, st);
+        default: return batch_dispatch<1>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, k0, ls.cool_on, ls.uniform_q, ls.batch_tpt, st);
     }
 }
 
 hipError_t launch_batch_accel(const DevState& s, int precision, int n_traps, int max_trap,
                               const LaunchShape& ls, hipStream_t st) {
     switch (precision) {
-        case 0: return batch_dispatch<0>(s, n_traps, max_trap, ls.batch_block, 0, 1, false, ls.uniform_q, ls.batch_tpt, st);
-        case 2: return batch_dispatch<2>(s, n_traps, max_trap, ls.batch_block, 0, 1, false, ls.uniform_q, ls.batch_tpt, st);
-        default: return batch_dispatch<1>(s, n_traps, max_trap, ls.batch_block, 0, 1, false, ls.uniform_q, ls.batch_tpt, st);
+        case 0: return batch_dispatch<0>(s, n_traps, max_trap, ls.batch_block, 0, 1, 0, false, ls.uniform_q, ls.batch_tpt, st);
+        case 2: return batch_dispatch<2>(s, n_traps, max_trap, ls.batch_block, 0, 1, 0, false, ls.uniform_q, ls.batch_tpt, st);
+        default: return batch_dispatch<1>(s, n_traps, max_trap, ls.batch_block, 0, 1, 0, false, ls.uniform_q, ls.batch_tpt, st);
     }
 }
 
@@ -3915,23 +3978,43 @@ hipError_t launch_rows(const DevState& s, int precision, const LaunchShape& ls, 
     }
 }
 
+hipError_t launch_begin(const DevState& s, const TrapDev* one_trap, double t_start, int n_traps,
+                        const CoolDev& cool, hipStream_t st) {
+    const unsigned g = std::max(1u, blocks_for(n_traps, 256));
+    k_begin<<<g, 256, 0, st>>>(one_trap ? *one_trap : TrapDev{}, one_trap ? 1 : 0, t_start,
+                               n_traps, s.traps, cool, s.cool, s.counter);
+    return hipGetLastError();
+}
+
+hipError_t launch_export(const double4* pos, const double* a, const double* b, const double* c,
+                         int64_t i0, int64_t cnt, double* out, hipStream_t st) {
+    k_export<<<blocks_for(cnt, 256), 256, 0, st>>>(ExportArgs{pos, {a, b, c}, i0, cnt, out});
+    return hipGetLastError();
+}
+
+hipError_t launch_import(const DevState& s, const double* in, int64_t i0, int64_t cnt,
+                         hipStream_t st) {
+    k_import<<<blocks_for(cnt, 256), 256, 0, st>>>(in, i0, cnt, s.qe, s.src, s.srcm, s.vx, s.vy,
+                                                   s.vz);
+    return hipGetLastError();
+}
+
 hipError_t launch_counter_add(const DevState& s, int64_t k, hipStream_t st) {
     k_counter_add<<<1, 64, 0, st>>>(s.counter, k);
     return hipGetLastError();
 }
 
-hipError_t launch_energy(const DevState& s, int n_traps, double** out, hipStream_t st) {
+hipError_t launch_energy(const DevState& s, int n_traps, double* out, hipStream_t st) {
     // blocks: one per unit (per trap of a batch), as many as fit 16 to a CU and
     // as the scratch array holds partial sums of
     const int64_t nb = (s.n + kEnergyTile - 1) / kEnergyTile;
     const int64_t want = n_traps == 1 ? nb * (nb + 1) : n_traps;
-    const int64_t g = std::max<int64_t>(1, std::min<int64_t>({want, 4096, (s.n_pad - 3) / 6}));
-    *out = s.scratch + 6 * g;
+    const int64_t g = std::max<int64_t>(1, std::min<int64_t>({want, 4096, s.n_pad / 6}));
     k_energy<<<(unsigned)g, 256, 0, st>>>(s.src, s.vx, s.vy, s.vz, s.qe, s.qm, s.mass, s.traps,
                                           s.trap_of, s.offsets, n_traps, s.n, s.scratch);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_energy_final<<<1, 256, 0, st>>>(s.scratch, (int)g, *out);
+    k_energy_final<<<1, 256, 0, st>>>(s.scratch, (int)g, out);
     return hipGetLastError();
 }
 
