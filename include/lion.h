@@ -389,15 +389,17 @@ typedef struct {
                              targets; positions alternate between two buffers); 2: the pair
                              kernel, then the epilogue.  Handles with body exclusion or
                              rigid bodies take 2.  Built-in: 1 for N <= LION_ONE_LAUNCH_IONS
-                             when the all-pairs kernels are selected, else 2                  */
+                             (..._FP32 for FP32 pairs) when the all-pairs kernels are
+                             selected, else 2                                                 */
 } lion_kernel_config;
 
 /* Ion count up to which a single trap is stepped inside one workgroup by default. */
 #define LION_SMALL_TRAP_IONS 128
 
 /* Ion count up to which a single trap on the multi-workgroup kernels takes one
- * launch per step by default. */
-#define LION_ONE_LAUNCH_IONS 2048
+ * launch per step by default: FP64, and the FP32 pair modes. */
+#define LION_ONE_LAUNCH_IONS 4096
+#define LION_ONE_LAUNCH_IONS_FP32 2048
 
 int lion_set_kernel_config(lion_sim *sim, const lion_kernel_config *cfg);
 int lion_get_kernel_config(const lion_sim *sim, lion_kernel_config *cfg);
@@ -423,13 +425,14 @@ int lion_time_batch_kernel(lion_sim *sim, int32_t reps, int32_t nsteps, double d
  * parameters, full rf field, no bodies) at time t, from the same all-pairs
  * kernels: a_i = (Q_i/M_i)(E_c,i + E_ext(r_i, t)).  No handle, no workspace:
  * x, y, z (m), charges_C, masses_kg and the outputs ax, ay, az are device
- * arrays of n doubles owned by the caller; the packed source streams, Q/M,
- * the trap and the per-slice partial sums live in one 8 MiB device array of
- * the library (a file-scope __device__ array, its address taken once per
- * device on the first call there, held until the process ends).  Hence
- * 1 <= n <= 65536 (else LION_ERR_ARG, before any device work), and calls on
- * one GPU share that array: calls that overlap on one GPU (other streams,
- * other threads) race and must be ordered by the caller.  Runs on hip_stream
+ * arrays of n doubles owned by the caller.  In FP64 up to 5120 ions one launch
+ * goes from the inputs to the outputs; else, or where an output overlaps an input,
+ * the packed source streams, Q/M, the trap and the per-slice partial sums live
+ * in one 8 MiB device array of the library (a file-scope __device__ array, its
+ * address taken once per device on the first call there, held until the
+ * process ends).  Hence 1 <= n <= 65536 (else LION_ERR_ARG, before any device
+ * work), and calls on one GPU share that array: calls that overlap on one GPU
+ * (other streams, other threads) race and must be ordered by the caller.  Runs on hip_stream
  * (NULL: the default stream) and returns once queued; calls no hipMalloc,
  * hipFree or allocating library routine.  NULL pointers, a bad trap (as
  * lion_set_trap), a non-finite t or an unknown precision -> LION_ERR_ARG;

@@ -225,15 +225,18 @@ void default_shape(lion_sim* s) {
     // epilogue: 4 waves per 64 ions unless set (8 and 16 measured no faster)
     ls.update_waves = s->cfg.update_waves > 0 ? s->cfg.update_waves : 4;
     // one launch per step: asked for, or built in up to LION_ONE_LAUNCH_IONS on the
-    // all-pairs kernels (FP64, us per step against the pair kernel + epilogue: 200
-    // ions 3.7 / 6.0, 1024 ions 4.9 / 6.3, 2048 ions 7.3 / 8.2); one target per
-    // workgroup up to 1024 ions, two above (2048 ions: 8.7 against 7.3 us)
+    // all-pairs kernels: FP64 as far as all workgroups are resident at once (us per step
+    // against the pair kernel + epilogue: 200 ions 3.5 / 6.2, 4096 ions 13.2 / 16.5, 4600
+    // ions 19.0 / 18.6); FP32 pairs, which gain little there (4096 ions 12.9 / 13.2, 4600
+    // ions 17.9 / 14.7), up to 2048.  One target per workgroup up to one per CU, then two,
+    // and from 1536 ions four (us per step with 1 / 2 / 4, FP64: 1024 ions 4.50 / 3.89 /
+    // 4.24, 2048 ions 8.29 / 6.29 / 6.11, 4000 ions 21.4 / 15.4 / 13.2)
     ls.rows = (!s->batched && (s->cfg.step_launches == 1 ||
                                (s->cfg.step_launches <= 0 && !ls.symmetric &&
-                                n <= LION_ONE_LAUNCH_IONS)))
+                                n <= (mixed ? LION_ONE_LAUNCH_IONS_FP32 : LION_ONE_LAUNCH_IONS))))
                   ? 1
                   : 0;
-    ls.rows_tr = n <= 1024 ? 1 : 2;
+    ls.rows_tr = n <= 256 ? 1 : (n <= 1536 ? 2 : 4);
     ls.uniform_q = s->uniform_q;
     ls.batch_tpt = s->cfg.batch_tpt > 0 ? s->cfg.batch_tpt : 0;
     ls.small_path = s->cfg.small_trap > 0 ? (s->cfg.small_trap == 2 ? 1 : 0)

@@ -205,7 +205,7 @@ struct LaunchShape {
     int sym_masked;    // pair-once kernels with the per-pair body test (bodies share tiles)
     bool bath_on;      // a bath is on: launch_noise goes ahead of the steps
     int rows;          // one launch per step (k_rows) for the single trap
-    int rows_tr;       // targets per workgroup of that launch: 2, 4 or 8
+    int rows_tr;       // targets per workgroup of that launch: 1, 2 or 4
 };
 
 // Tiles of 256 ions used by the pair kernels that evaluate each pair once; the
@@ -249,6 +249,14 @@ hipError_t launch_pack_mixed(const DevState& s, hipStream_t st);
 hipError_t launch_pack_inputs(const double* x, const double* y, const double* z,
                               const double* charge, const double* mass, const DevState& s,
                               const TrapDev& T, hipStream_t st);
+// FP64 accelerations (out: ax, ay, az) of the ions in the device arrays in[] = x, y, z,
+// charge (C), mass (kg) in one launch, up to kDirectIons; out must not overlap in.
+// Up to there four targets per workgroup leave all workgroups resident at once; us a
+// call against packing, pair kernel and epilogue: 5000 ions 19.7 / 25.2, 6500 ions 35.0
+// / 33.6.
+constexpr int64_t kDirectIons = 5120;
+hipError_t launch_accel_direct(const double* const* in, int64_t n, const TrapDev& T,
+                               double* const* out, hipStream_t st);
 // Message returned by lion_last_error(NULL) (calls without a handle).
 void set_handle_free_error(const std::string& msg);
 // Steps of a batch (or a lone trap in one workgroup); with a bath on, the table

@@ -1664,16 +1664,14 @@ __global__ __launch_bounds__(kRowsBlock) void k_rows(const RowsArgs A, int mode,
             sz[k] += (double)fz[k] - (double)cz[k];
         }
     }
-    const int lane = tid & 63, wave = tid >> 6;
+    double sums[3 * TR];
 #pragma unroll
     for (int k = 0; k < TR; ++k) {
-        const double x = wave_sum(sx[k]), y = wave_sum(sy[k]), z = wave_sum(sz[k]);
-        if (lane == 0) {
-            red[wave][3 * k + 0] = x;
-            red[wave][3 * k + 1] = y;
-            red[wave][3 * k + 2] = z;
-        }
+        sums[3 * k] = sx[k];
+        sums[3 * k + 1] = sy[k];
+        sums[3 * k + 2] = sz[k];
     }
+    wave_sums(sums, red[tid >> 6]);
     const double t = counted ? T.t_start + (double)kc * T.dt : T.t_start;
     const double crf = (own && T.ps == 0.0) ? cos(T.omega * t) : 0.0;
     __syncthreads();
@@ -2647,6 +2645,87 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
     }
 }
 
+// ------------------------------------------- forces of the caller's arrays, one launch
+//
+// The allocation-free FP64 evaluation in one launch: workgroup g owns the TR targets
+// [g TR, g TR + TR) (wave-uniform, so they sit in scalar registers), its threads take
+// every 256th source straight from the caller's arrays, and the owners add the trap.
+// Bound by FP64 issue of the pairs plus one launch: 3001 ions 9.1 us a call against
+// 16.5 with packing, pair kernel and epilogue, up to 2048 ions 6.2 against 12.
+constexpr int kDirectBlock = 256;
+
+// q / e, rounded as the division is (one correction of the product with 1/e).
+__device__ __forceinline__ double charge_in_e(double q) {
+    constexpr double inv = 1.0 / kElementaryCharge;
+    const double r = q * inv;
+    return fma(fma(-r, kElementaryCharge, q), inv, r);
+}
+
+template <int TR>
+__global__ __launch_bounds__(kDirectBlock) void k_accel_direct(
+    const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
+    const double* __restrict__ charge, const double* __restrict__ mass, int n, const TrapDev T,
+    double* __restrict__ ax, double* __restrict__ ay, double* __restrict__ az) {
+    constexpr int kW = kDirectBlock / 64, U = 4;
+    __shared__ double red[kW][3 * TR];
+    const int i0 = (int)blockIdx.x * TR, tid = threadIdx.x, i = i0 + tid;
+    const bool own = tid < TR && i < n;
+    double px = 0.0, py = 0.0, pz = 0.0, qm = 0.0, crf = 0.0;
+    if (own) {
+        px = x[i];
+        py = y[i];
+        pz = z[i];
+        qm = charge[i] / mass[i];
+        if (T.a_rf != 0.0) crf = cos(T.omega * T.t_start);
+    }
+    double tx[TR], ty[TR], tz[TR], sx[TR], sy[TR], sz[TR];
+#pragma unroll
+    for (int k = 0; k < TR; ++k) {
+        const int t = min(i0 + k, n - 1);
+        tx[k] = x[t];
+        ty[k] = y[t];
+        tz[k] = z[t];
+        sx[k] = sy[k] = sz[k] = 0.0;
+    }
+    for (int j0 = tid; j0 < n; j0 += U * kDirectBlock) {
+        double4 P[U];  // past n the last ion again, with zero weight
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = j0 + u * kDirectBlock, jj = min(j, n - 1);
+            P[u] = make_double4(x[jj], y[jj], z[jj], j < n ? charge[jj] : 0.0);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            P[u].w = 1.5 * charge_in_e(P[u].w);
+#pragma unroll
+            for (int k = 0; k < TR; ++k)
+                pair_f64(P[u], tx[k], ty[k], tz[k], sx[k], sy[k], sz[k]);
+        }
+    }
+    double sums[3 * TR];
+#pragma unroll
+    for (int k = 0; k < TR; ++k) {
+        sums[3 * k] = sx[k];
+        sums[3 * k + 1] = sy[k];
+        sums[3 * k + 2] = sz[k];
+    }
+    wave_sums(sums, red[tid >> 6]);
+    __syncthreads();
+    if (!own) return;
+    double Sx = red[0][3 * tid], Sy = red[0][3 * tid + 1], Sz = red[0][3 * tid + 2];
+#pragma unroll
+    for (int w = 1; w < kW; ++w) {
+        Sx += red[w][3 * tid];
+        Sy += red[w][3 * tid + 1];
+        Sz += red[w][3 * tid + 2];
+    }
+    double a, b, c;
+    trap_accel_c(T, crf, qm, px, py, pz, Sx, Sy, Sz, a, b, c);
+    ax[i] = a;
+    ay[i] = b;
+    az[i] = c;
+}
+
 // ------------------------------------------------------------ rigid bodies
 
 __device__ __forceinline__ void quat_rot(const double q[4], double A[9]) {
@@ -3333,15 +3412,14 @@ __global__ __launch_bounds__(kMinRows) void k_min_rows(const MinArgs A, int from
         }
     }
     __syncthreads();  // the reduction above is read
+    double sums[3 * TR];
 #pragma unroll
     for (int k = 0; k < TR; ++k) {
-        const double X = wave_sum(sx[k]), Y = wave_sum(sy[k]), Z = wave_sum(sz[k]);
-        if (lane == 0) {
-            red[wave][3 * k] = X;
-            red[wave][3 * k + 1] = Y;
-            red[wave][3 * k + 2] = Z;
-        }
+        sums[3 * k] = sx[k];
+        sums[3 * k + 1] = sy[k];
+        sums[3 * k + 2] = sz[k];
     }
+    wave_sums(sums, red[wave]);
     __syncthreads();
     if (wave > 0) return;
     double P = 0.0, FF = 0.0, fm = 0.0;
@@ -3937,7 +4015,6 @@ hipError_t rows_dispatch(const RowsArgs& A, int tr, bool cool_on, int mode, int 
     switch (tr) {
         case 1: return rows_launch<PREC, 1>(A, cool_on, mode, k, bath_idx, st);
         case 2: return rows_launch<PREC, 2>(A, cool_on, mode, k, bath_idx, st);
-        case 8: return rows_launch<PREC, 8>(A, cool_on, mode, k, bath_idx, st);
         default: return rows_launch<PREC, 4>(A, cool_on, mode, k, bath_idx, st);
     }
 }
@@ -3976,6 +4053,31 @@ hipError_t launch_rows(const DevState& s, int precision, const LaunchShape& ls, 
         case 2: return rows_dispatch<2>(A, ls.rows_tr, ls.cool_on, mode, k_in_chunk, bath_idx, st);
         default: return rows_dispatch<1>(A, ls.rows_tr, ls.cool_on, mode, k_in_chunk, bath_idx, st);
     }
+}
+
+namespace {
+
+template <int TR>
+void direct_launch(const double* const* in, int n, const TrapDev& T, double* const* out,
+                   hipStream_t st) {
+    k_accel_direct<TR><<<blocks_for(n, TR), kDirectBlock, 0, st>>>(in[0], in[1], in[2], in[3], in[4],
+                                                                   n, T, out[0], out[1], out[2]);
+}
+
+}  // namespace
+
+hipError_t launch_accel_direct(const double* const* in, int64_t n, const TrapDev& T,
+                               double* const* out, hipStream_t st) {
+    if (n < 1 || n > kDirectIons) return hipErrorInvalidValue;
+    // one target per CU, then two and four (us a call with 2 / 4: 1024 ions 6.2 / 6.1,
+    // 2048 6.7 / 6.2, 3001 11.5 / 9.1)
+    if (n <= 256)
+        direct_launch<1>(in, (int)n, T, out, st);
+    else if (n <= 1024)
+        direct_launch<2>(in, (int)n, T, out, st);
+    else
+        direct_launch<4>(in, (int)n, T, out, st);
+    return hipGetLastError();
 }
 
 hipError_t launch_begin(const DevState& s, const TrapDev* one_trap, double t_start, int n_traps,

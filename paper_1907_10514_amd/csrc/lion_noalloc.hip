@@ -6,7 +6,8 @@
 // inputs and outputs; everything else the kernels need (the packed source
 // streams, Q/M per ion, the trap parameters and the per-slice partial sums)
 // lives in one file-scope device array of kScratchBytes, which each GPU the
-// library runs on holds until the process ends.  Host code addresses that
+// library runs on holds until the process ends.  Smaller FP64 calls go straight from the
+// caller's arrays to the accelerations in one launch and leave that array alone.  Host code addresses that
 // array only through the pointer hipGetSymbolAddress returns for the current
 // device (taken once per device, on the first call there).
 #include <hip/hip_runtime.h>
@@ -79,6 +80,25 @@ extern "C" int lion_accel_noalloc(int64_t n, const double* x, const double* y, c
         return fail(LION_ERR_ARG, "trap parameter or time not finite");
     if (r0 <= 0 || z0 <= 0) return fail(LION_ERR_ARG, "r0 and z0 must be > 0");
     if (V_rf != 0.0 && Omega <= 0.0) return fail(LION_ERR_ARG, "Omega must be > 0 when V_rf != 0");
+    lion::TrapDev T{};
+    T.a_rf = V_rf / (r0 * r0);
+    T.omega = Omega;
+    T.a_dc = kappa * U_dc / (z0 * z0);
+    T.f = 1.0;
+    T.t_start = t;
+    hipStream_t st = (hipStream_t)hip_stream;
+    // FP64: one launch from the caller's arrays unless an output overlaps an input, which
+    // the packed copies below allow
+    const double* const in[5] = {x, y, z, charges_C, masses_kg};
+    double* const out[3] = {ax, ay, az};
+    bool overlap = false;
+    for (const double* a : in)
+        for (const double* b : out) overlap = overlap || (a < b + n && b < a + n);
+    if (precision == LION_FP64 && n <= lion::kDirectIons && !overlap) {
+        const hipError_t e = lion::launch_accel_direct(in, n, T, out, st);
+        if (e != hipSuccess) return fail(LION_ERR_HIP, hipGetErrorString(e));
+        return LION_OK;
+    }
     void* base = nullptr;
     int rc = scratch_of_current_device(&base);
     if (rc) return rc;
@@ -125,13 +145,6 @@ extern "C" int lion_accel_noalloc(int64_t n, const double* x, const double* y, c
     d.ay = ay;
     d.az = az;
 
-    lion::TrapDev T{};
-    T.a_rf = V_rf / (r0 * r0);
-    T.omega = Omega;
-    T.a_dc = kappa * U_dc / (z0 * z0);
-    T.f = 1.0;
-    T.t_start = t;
-    hipStream_t st = (hipStream_t)hip_stream;
     hipError_t e = lion::launch_pack_inputs(x, y, z, charges_C, masses_kg, d, T, st);
     if (e == hipSuccess) e = lion::launch_pair(d, precision, ls, false, st);
     if (e == hipSuccess) e = lion::launch_update(d, precision, ls, lion::kModeAccel, false, 0, st);

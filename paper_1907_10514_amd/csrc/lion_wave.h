@@ -28,19 +28,43 @@ __device__ __forceinline__ double row16_sum(double v) {
     return dpp_add<0x140>(row8_sum(v));  // row_mirror
 }
 
-// Sum over the 64 lanes, in every lane: the rows, then rows 0 + 1 and 2 + 3 and the
-// two halves by the row swaps (each leaves one operand in the first result and the
-// other in the second).
+// a and b with halves (swap_rows: rows 0 and 1, 2 and 3) exchanged and added: one half
+// (the even rows) of the result holds a's sum over the pair, the other b's.
+template <bool HALVES>
+__device__ __forceinline__ double swap_add(double a, double b) {
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    auto swap = [](uint32_t u, uint32_t w) {
+        if constexpr (HALVES)
+            return __builtin_amdgcn_permlane32_swap(u, w, false, false);
+        else
+            return __builtin_amdgcn_permlane16_swap(u, w, false, false);
+    };
+    const auto lo = swap((uint32_t)x, (uint32_t)y);
+    const auto hi = swap((uint32_t)(x >> 32), (uint32_t)(y >> 32));
+    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+}
+
+// Sum over the 64 lanes, in every lane.
 __device__ __forceinline__ double wave_sum(double v) {
     v = row16_sum(v);
-    auto swap_add = [](double x, auto swap) {
-        const uint64_t b = __builtin_bit_cast(uint64_t, x);
-        const auto lo = swap((uint32_t)b), hi = swap((uint32_t)(b >> 32));
-        return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
-               __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
-    };
-    v = swap_add(v, [](uint32_t u) { return __builtin_amdgcn_permlane16_swap(u, u, false, false); });
-    return swap_add(v, [](uint32_t u) { return __builtin_amdgcn_permlane32_swap(u, u, false, false); });
+    v = swap_add<false>(v, v);
+    return swap_add<true>(v, v);
+}
+
+// The sums of N values over the 64 lanes into out[0 .. N): four at a time share the
+// lanes (21 instructions for four values, 72 for four single sums).
+template <int N>
+__device__ __forceinline__ void wave_sums(const double (&v)[N], double* out) {
+    const int lane = threadIdx.x & 63, row = lane >> 4;
+#pragma unroll
+    for (int g = 0; g < N; g += 4) {
+        auto at = [&](int k) { return g + k < N ? v[g + k] : 0.0; };
+        const double h0 = swap_add<true>(at(0), at(1)), h1 = swap_add<true>(at(2), at(3));
+        const double s = row16_sum(swap_add<false>(h0, h1));  // rows: values 0, 2, 1, 3
+        const int k = g + (row == 1 ? 2 : (row == 2 ? 1 : row));
+        if ((lane & 15) == 0 && k < N) out[k] = s;
+    }
 }
 
 }  // namespace lion
