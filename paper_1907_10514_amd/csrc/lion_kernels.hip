@@ -1388,6 +1388,111 @@ void k_pair_f64_sym(const double4* __restrict__ src, const double* __restrict__ 
     if (counter && blockIdx.x == 0 && threadIdx.x == 0) *counter += 1;
 }
 
+// The built-in FP64 pair-once kernel: an off-diagonal tile pair by wave rotation.  Each
+// wave holds the 256 targets (4 per lane) and 64 sources; at step s lane l meets source
+// (l + s) mod 64, and the sources' reaction sums ride along, one lane down a step, so
+// that after 64 steps each is back in its source's lane: no transposes and no column
+// sums.  Sources are read from LDS, stored twice in a row so that l + s needs no wrap.
+// Bound by FP64 issue: 16 instructions and a quarter-rate v_rsq_f64 a pair, 1.5 moves
+// for the rotation.  Against the LDS transposes of k_pair_f64_sym (us per launch):
+// 10000 ions 43.2 / 52.0, 16384 ions 89.3 / 96.2, 65536 ions 1273 / 1450.
+template <bool FQ>
+__device__ __forceinline__ void f64_turn_body(const double4* __restrict__ src,
+                                              const double* __restrict__ qe, int64_t n,
+                                              int64_t n_pad, double* __restrict__ part, int a,
+                                              int b, double uq, double* smem) {
+    constexpr int Q = FQ ? 3 : 4, U = 8;  // U sources unrolled: 2 to 8 measured alike
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t base = (int64_t)a * kSymTile + lane;
+    const int64_t j0 = (int64_t)b * kSymTile + wave * 64;
+    double* mine = smem + wave * Q * 128;
+    {
+        const double4 p = src[j0 + lane];
+        mine[lane] = mine[lane + 64] = p.x;
+        mine[lane + 128] = mine[lane + 192] = p.y;
+        mine[lane + 256] = mine[lane + 320] = p.z;
+        if constexpr (!FQ) mine[lane + 384] = mine[lane + 448] = p.w;
+    }
+    double xi[4], yi[4], zi[4], nqi[4], sx[4], sy[4], sz[4], rx = 0.0, ry = 0.0, rz = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const double4 p = src[base + 64 * k];
+        xi[k] = p.x;
+        yi[k] = p.y;
+        zi[k] = p.z;
+        nqi[k] = FQ ? 0.0 : -1.5 * qe[base + 64 * k];
+        sx[k] = sy[k] = sz[k] = 0.0;
+    }
+    // the wave's LDS writes are visible to all its lanes after this
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const double* p = mine + lane;
+    for (int s0 = 0; s0 < 64; s0 += U, p += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double px = p[u], py = p[u + 128], pz = p[u + 256];
+            const double pw = FQ ? 0.0 : p[u + 384];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const double dx = px - xi[k], dy = py - yi[k], dz = pz - zi[k];
+                const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, kR2FloorF64)));
+                const double y = __builtin_amdgcn_rsq(r2);
+                const double a2 = y * y;
+                const double c = (a2 * y) * fma(r2, a2, -5.0 / 3.0);  // -(2/3) r^-3
+                const double wi = FQ ? c : c * pw;                    // 1.5 q_j c = -q_j r^-3
+                sx[k] = fma(wi, dx, sx[k]);
+                sy[k] = fma(wi, dy, sy[k]);
+                sz[k] = fma(wi, dz, sz[k]);
+                const double wj = FQ ? c : c * nqi[k];                // -1.5 q_i c = q_i r^-3
+                rx = fma(wj, dx, rx);
+                ry = fma(wj, dy, ry);
+                rz = fma(wj, dz, rz);
+            }
+            rx = lane_above(rx);
+            ry = lane_above(ry);
+            rz = lane_above(rz);
+        }
+    }
+    const double fr = FQ ? -1.5 * uq : 1.0;
+    double* pr = part + (int64_t)(3 * a) * n_pad + j0 + lane;
+    pr[0] = rx * fr;
+    pr[n_pad] = ry * fr;
+    pr[2 * n_pad] = rz * fr;
+    if (FQ) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            sx[k] *= 1.5 * uq;
+            sy[k] *= 1.5 * uq;
+            sz[k] *= 1.5 * uq;
+        }
+    }
+    __syncthreads();  // every wave is done with its sources
+    reduce_store_in<4>(sx, sy, sz, part, b, n, n_pad, base, smem);
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+void k_pair_f64_turn(const double4* __restrict__ src, const double* __restrict__ qe, int64_t n,
+                     int nb, int64_t n_pad, double* __restrict__ part,
+                     int64_t* __restrict__ counter, double uq, int full_tiles,
+                     const int32_t* __restrict__ tile_body) {
+    // sources of four waves, the diagonal's buffer or the target sums of three waves
+    constexpr int kSrc = kWaves * 4 * 128, kRed = (kWaves - 1) * 3 * 64 * 4;
+    __shared__ double smem[kSrc > kRed ? kSrc : kRed];
+    int a, b;
+    sym_unit(nb, a, b);
+    if (sym_unit_excluded(tile_body, a, b))
+        sym_unit_zero(part, n, n_pad, a, b);
+    else if (a == b)
+        f64_sym_body<1, true, false, false, true>(src, qe, n, n_pad, part, a, b, uq, smem);
+    else if (uq != 0.0 && b < full_tiles)
+        f64_turn_body<true>(src, qe, n, n_pad, part, a, b, uq, smem);
+    else
+        f64_turn_body<false>(src, qe, n, n_pad, part, a, b, uq, smem);
+    if (counter && blockIdx.x == 0 && threadIdx.x == 0) *counter += 1;
+}
+
 // The per-ion inputs of the end of a step.
 struct IonIn {
     double4 p;  // position (w: the FP64 source weight, carried along)
@@ -3734,7 +3839,7 @@ hipError_t launch_pair(const DevState& s, int precision, const LaunchShape& ls, 
                     k_pair_f64_sym<2, 2><<<units, 256, 0, st>>>(s.src, s.qe, s.n, nb, s.n_pad, s.part, ctr, uq, full, tb);
                     break;
                 case 5:
-                    k_pair_f64_sym<4, 1, true><<<units, 256, 0, st>>>(s.src, s.qe, s.n, nb, s.n_pad, s.part, ctr, uq, full, tb);
+                    k_pair_f64_turn<<<units, 256, 0, st>>>(s.src, s.qe, s.n, nb, s.n_pad, s.part, ctr, uq, full, tb);
                     break;
                 case 6:
                     k_pair_f64_sym<3, 2, true><<<units, 256, 0, st>>>(s.src, s.qe, s.n, nb, s.n_pad, s.part, ctr, uq, full, tb);

@@ -15,6 +15,14 @@ __device__ __forceinline__ double dpp_add(double v) {
     return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
+// The value of the lane above, lane 0's in lane 63.
+__device__ __forceinline__ double lane_above(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, 0x134, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(b >> 32), 0x134, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
 // Sum over the 8 lanes of an octet, in every lane: xor 1, xor 2, then the mirrored
 // halves (every lane of a quad already holds the same sum).
 __device__ __forceinline__ double row8_sum(double v) {
