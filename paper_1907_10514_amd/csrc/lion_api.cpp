@@ -194,13 +194,16 @@ void default_shape(lion_sim* s) {
     ls.batch_block = s->cfg.batch_block > 0 ? s->cfg.batch_block : 256;
     ls.lds_sources = s->cfg.lds_sources > 0 ? (s->cfg.lds_sources == 2 ? 1 : 0) : 1;
     const int nb = lion::sym_tiles(n);
-    // pair-once kernels: when asked for, and by default for one trap from the
-    // size where they measured faster (8192 ions; from 12288 on by a wide margin
-    // in every precision)
+    // pair-once kernels: when asked for, and by default for one trap at the sizes
+    // where they measured faster (FP64 by rounds of tile pairs unless the per-pair body
+    // test is on, else from 8192 ions; from 12288 on by a wide margin in every precision)
     const bool sym_ok = nb <= lion::kMaxSymTiles && !s->batched;
     const int64_t sym_from = s->precision == LION_MIXED_F64ACC ? lion::kSymDefaultIonsMixed
                                                                 : lion::kSymDefaultIons;
-    const bool sym_default = s->cfg.symmetric <= 0 && n >= sym_from;
+    const bool per_pair_test = s->has_bodies && !s->tile_bodies;
+    const bool sym_default = s->cfg.symmetric <= 0 && (mixed || per_pair_test
+                                                           ? n >= sym_from
+                                                           : lion::sym_default_f64(n));
     ls.symmetric = (sym_ok && (s->cfg.symmetric == 2 || sym_default)) ? 1 : 0;
     // bodies that share tiles with other ions need the per-pair test in those kernels
     ls.sym_masked = (ls.symmetric && s->has_bodies && !s->tile_bodies) ? 1 : 0;

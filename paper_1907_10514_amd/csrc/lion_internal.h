@@ -217,6 +217,14 @@ constexpr int kMaxSymTiles = 512;
 // kernel families stored FP32 partials: 8192 ions 31.5 against 32.9 us per step).
 constexpr int64_t kSymDefaultIons = 8192;
 constexpr int64_t kSymDefaultIonsMixed = 8192;
+// FP64: a launch takes about 10 us per round of one tile pair on each of the 256 CUs,
+// so from 26 tiles on, and where 20 to 22 tiles fill just under one round (us per step
+// against the all-pairs kernels: 5000 ions 20.0 / 23.1, 5500 ions 20.5 / 25.7, 6000 ions
+// 28.9 / 28.0, 6500 ions 30.0 / 31.3, 7500 ions 30.3 / 39.0).
+inline bool sym_default_f64(int64_t n) {
+    const int nb = sym_tiles(n);
+    return nb >= 26 || (nb >= 20 && nb <= 22);
+}
 
 // Kernel launchers (lion_kernels.hip).  All return hipSuccess or the launch error.
 // Bath kicks of half_steps (<= s.noise_h) half-steps into the table, from the
