@@ -2709,12 +2709,16 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
             Sz = ((double)sz - (double)cz) * kMixedFieldScale;
         }
         // the parts of a target: a fixed butterfly over its P consecutive lanes
-#pragma unroll
-        for (int d = P / 2; d >= 1; d >>= 1) {
-            Sx += __shfl_xor(Sx, d);
-            Sy += __shfl_xor(Sy, d);
-            Sz += __shfl_xor(Sz, d);
-        }
+        // (DPP moves: exchanges through LDS put 0.15 us on each step's chain)
+        auto parts = [](double v) {
+            if constexpr (P >= 8) v = xor_add<4>(v);
+            if constexpr (P >= 4) v = xor_add<2>(v);
+            if constexpr (P >= 2) v = xor_add<1>(v);
+            return v;
+        };
+        Sx = parts(Sx);
+        Sy = parts(Sy);
+        Sz = parts(Sz);
         if (owner) {
             const double crf = T.ps == 0.0 ? rf[(step / kRf) & 1][step % kRf] : 0.0;
             trap_accel_c(T, crf, q_m, x, y, z, Sx, Sy, Sz, a0, a1, a2);
@@ -3183,9 +3187,12 @@ struct MinArgs {
 
 // Largest of the values of a wave in every lane.
 __device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off));
-    return v;
+    v = fmax(v, dpp_get<0xB1>(v));
+    v = fmax(v, dpp_get<0x4E>(v));
+    v = fmax(v, dpp_get<0x141>(v));
+    v = fmax(v, dpp_get<0x140>(v));
+    v = fmax(v, __shfl_xor(v, 16));
+    return fmax(v, __shfl_xor(v, 32));
 }
 
 // v.F, F.F and |F| of one ion.

@@ -6,13 +6,37 @@
 
 namespace lion {
 
-// v plus the value of the lane that the DPP control CTRL names.
+// The value of the lane that the DPP control CTRL names.
 template <int CTRL>
-__device__ __forceinline__ double dpp_add(double v) {
+__device__ __forceinline__ double dpp_get(double v) {
     const uint64_t b = __builtin_bit_cast(uint64_t, v);
     const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, false);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
-    return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    return v + dpp_get<CTRL>(v);
+}
+
+// v plus the value of lane ^ D, D = 1, 2 or 4 (4: from the lane four up in the lower
+// quad of an octet, four down in the upper).
+template <int D>
+__device__ __forceinline__ double xor_add(double v) {
+    if constexpr (D == 1) {
+        return dpp_add<0xB1>(v);
+    } else if constexpr (D == 2) {
+        return dpp_add<0x4E>(v);
+    } else {
+        static_assert(D == 4, "within an octet");
+        auto get = [](uint32_t u) {
+            const int up = __builtin_amdgcn_update_dpp(0, (int)u, 0x104, 0xf, 0x5, false);
+            return (uint32_t)__builtin_amdgcn_update_dpp(up, (int)u, 0x114, 0xf, 0xa, false);
+        };
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        return v + __builtin_bit_cast(double, ((uint64_t)get((uint32_t)(b >> 32)) << 32) | get((uint32_t)b));
+    }
 }
 
 // The value of the lane above, lane 0's in lane 63.
