@@ -1419,6 +1419,7 @@ int lion_normal_modes(lion_sim* s, void* dev_work, size_t bytes, double* omega2,
         LION_HIP(s, lion::launch_eigenvalues(A, m, W, E, base + fixed, st));
         LION_HIP(s, hipMemcpyAsync(omega2, W, (size_t)m * 8, hipMemcpyDeviceToHost, st));
         LION_HIP(s, hipStreamSynchronize(st));
+        if (!is_fin(omega2[0])) return fail(s, LION_ERR_HIP, "eigen-solver: the Hessian is not finite");
         // neighbours that agree to rounding may come out in either order
         for (int k = 1; k < m; ++k) omega2[k] = std::max(omega2[k], omega2[k - 1]);
         return LION_OK;
@@ -1484,8 +1485,8 @@ int lion_minimize(lion_sim* s, double dt, double dmax, double ftol, int64_t max_
     for (;;) {
         // up to 50 iterations and the last test; an even count, as one launch per
         // iteration alternates two buffers
-        const int64_t left = max_iter - m.iterations + 1;
-        rc = run_min_chunk(s, left >= 50 ? 50 : left + (left & 1));
+        const int64_t left = max_iter - m.iterations;
+        rc = run_min_chunk(s, left >= 50 ? 50 : (left + 2) & ~int64_t(1));
         if (rc) return rc;
         LION_HIP(s, hipMemcpyAsync(&m, s->d.minst, sizeof(m), hipMemcpyDeviceToHost, st));
         LION_HIP(s, hipStreamSynchronize(st));
