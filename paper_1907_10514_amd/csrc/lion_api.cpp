@@ -479,11 +479,12 @@ int64_t chunk_len(const lion_sim* s) {
 // the handle (so a trap stepped inside one workgroup gets them from that kernel).
 int refresh_accel(lion_sim* s) {
     for (int k = 0; k < s->n_traps; ++k) s->traps[k].t_start = s->t_now[k];
-    int rc = begin_call(s);
+    const TrapDev* lone = small_path_active(s) ? &s->traps[0] : nullptr;
+    int rc = lone ? LION_OK : begin_call(s);
     if (rc) return rc;
-    if (s->batched || small_path_active(s)) {
+    if (s->batched || lone) {
         LION_HIP(s, lion::launch_batch_accel(s->d, s->precision, s->n_traps, s->max_trap, s->ls,
-                                             s->stream));
+                                             lone, s->stream));
         return LION_OK;
     }
     if (rows_active(s)) {
@@ -511,7 +512,7 @@ hipError_t enqueue_one_workgroup(lion_sim* s, int64_t L, int64_t k0, hipStream_t
             e = lion::launch_noise(s->d, false, 2 * (k0 + done) + 2, (int)(2 * K), st);
         if (e == hipSuccess)
             e = lion::launch_batch(s->d, s->precision, s->n_traps, s->max_trap, s->ls, (int)K,
-                                   k0 + done, st);
+                                   k0 + done, s->batched ? nullptr : &s->traps[0], st);
         done += K;
     }
     return e;
@@ -1293,7 +1294,9 @@ static int step_common(lion_sim* s, int64_t nsteps, const double* dts) {
         if (dts[k] != dts[0])
             return fail(s, LION_ERR_UNSUPPORTED, "cooling beams and baths need one dt for all traps");
     int rc = prepare_cooling(s, dts[0]);
-    if (rc == LION_OK) rc = begin_call(s);
+    // a single trap in one workgroup gets its parameters by value and, without cooling,
+    // reads nothing else that a call sets
+    if (rc == LION_OK && (!small_path_active(s) || s->ls.cool_on)) rc = begin_call(s);
     if (rc) return rc;
     const int64_t S = chunk_len(s);
     for (int64_t done = 0; done < nsteps;) {

@@ -268,11 +268,13 @@ hipError_t launch_accel_direct(const double* const* in, int64_t n, const TrapDev
 // Message returned by lion_last_error(NULL) (calls without a handle).
 void set_handle_free_error(const std::string& msg);
 // Steps of a batch (or a lone trap in one workgroup); with a bath on, the table
-// holds the 2 nsteps half-steps from index 0.  k0: steps of the call done before.
+// holds the 2 nsteps half-steps from index 0.  k0: steps of the call done before;
+// lone_trap: a single trap's parameters, or NULL for those on the device.
 hipError_t launch_batch(const DevState& s, int precision, int n_traps, int max_trap,
-                        const LaunchShape& ls, int nsteps, int64_t k0, hipStream_t st);
+                        const LaunchShape& ls, int nsteps, int64_t k0, const TrapDev* lone_trap,
+                        hipStream_t st);
 hipError_t launch_batch_accel(const DevState& s, int precision, int n_traps, int max_trap,
-                              const LaunchShape& ls, hipStream_t st);
+                              const LaunchShape& ls, const TrapDev* lone_trap, hipStream_t st);
 hipError_t launch_rigid_wrench(const DevState& s, bool end_kick, hipStream_t st);
 hipError_t launch_rigid_drift(const DevState& s, hipStream_t st);
 hipError_t launch_rigid_place(const DevState& s, int precision, hipStream_t st);

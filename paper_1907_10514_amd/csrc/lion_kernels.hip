@@ -2021,6 +2021,13 @@ __global__ __launch_bounds__(256) void k_count_lost(const double4* __restrict__ 
     if (!(r2 <= r2_lost)) atomicAdd(count, 1);
 }
 
+// A single trap's parameters by value, which spares its steps the launch that would
+// bring them to the device (8 ions, 20 steps and an output: 28.8 us with it, 26.3).
+struct LoneTrap {
+    TrapDev T;
+    int on;
+};
+
 // ------------------------------------------------------------ batched traps
 //
 // One workgroup per trap, launched largest trap first so that the hardware
@@ -2302,7 +2309,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
                                                  int64_t k0, double* __restrict__ vacc,
                                                  double* __restrict__ vavg, int64_t n_pad,
                                                  int nsteps, int accel_only, double uq,
-                                                 int tpt_req) {
+                                                 int tpt_req, const LoneTrap lone) {
     // ions per owner thread at most (a 64-thread block takes traps of <= 64 ions only)
     constexpr int KMAX = BLOCK >= 256 ? kMaxTrap / BLOCK : 1;
     // pair work of larger traps: TPT targets per thread read each source once
@@ -2348,7 +2355,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
     const int jlen = ((send + JP - 1) / JP + kGran - 1) / kGran * kGran;
     const int jb = min(jpart * jlen, send);
     const int je = min(jb + jlen, send);
-    const TrapDev T = traps[tr];
+    const TrapDev T = lone.on ? lone.T : traps[tr];
     // a lone trap (the small-trap path) is latency-bound: one target per thread
     // below kBatchTpt4 ions saves the extra reduction rounds
     const int tpt2_from = gridDim.x == 1 ? kBatchTpt4 : kBatchTpt2;
@@ -2596,7 +2603,8 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
                                              const int32_t* __restrict__ order,
                                              int64_t k0, double* __restrict__ vacc,
                                              double* __restrict__ vavg, int64_t n_pad,
-                                             int nsteps, int accel_only) {
+                                             int nsteps, int accel_only,
+                                             const LoneTrap lone) {
     using S = typename BatchSrc<PREC>::T;
     constexpr int kSlots = 64 * W / P;  // targets per workgroup
     __shared__ S lds[kSlots];
@@ -2608,7 +2616,7 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
     const int lane = threadIdx.x;
     const int ti = lane / P, part = lane - ti * P;
     const bool owner = part == 0 && ti < m;
-    const TrapDev T = traps[tr];
+    const TrapDev T = lone.on ? lone.T : traps[tr];
     // with cooling: the beams in LDS, the baths of the next half-step loaded ahead
     __shared__ BeamDev beams[X ? kMaxBeams : 1];
     CoolRef cr = cool_switches<X>(cool);
@@ -3704,24 +3712,24 @@ hipError_t pair_mixed_dispatch_l(const DevState& s, const LaunchShape& ls, int64
 
 template <int PREC, int BLOCK, bool X>
 hipError_t batch_launch(const DevState& s, int n_traps, int max_trap, int nsteps,
-                        int accel_only, int64_t k0, double uq, int tpt, hipStream_t st) {
+                        int accel_only, int64_t k0, const LoneTrap& lone, double uq, int tpt, hipStream_t st) {
     const size_t stream_bytes = (size_t)max_trap * sizeof(double4);
     k_batch<PREC, BLOCK, X><<<n_traps, BLOCK, stream_bytes, st>>>(s.src, s.vx, s.vy, s.vz, s.ax, s.ay,
                                                        s.az, s.qm, s.qe, s.species, s.traps,
                                                        s.cool, bath_table(s), s.offsets, s.order,
                                                        k0, s.vacc, s.vavg, s.n_pad,
-                                                       nsteps, accel_only, uq, tpt);
+                                                       nsteps, accel_only, uq, tpt, lone);
     return hipGetLastError();
 }
 
 template <int PREC, int P, int W, bool X, int U = 1>
 hipError_t wave_launch_p(const DevState& s, int n_traps, int nsteps, int accel_only, int64_t k0,
-                         hipStream_t st) {
+                         const LoneTrap& lone, hipStream_t st) {
     k_wave<PREC, P, W, X, U><<<n_traps, 64 * W, 0, st>>>(s.src, s.vx, s.vy, s.vz, s.ax, s.ay, s.az,
                                                       s.qm, s.qe, s.species, s.traps, s.cool,
                                                       bath_table(s), s.offsets, s.order, k0,
                                                       s.vacc, s.vavg, s.n_pad, nsteps,
-                                                      accel_only);
+                                                      accel_only, lone);
     return hipGetLastError();
 }
 
@@ -3737,18 +3745,18 @@ inline int wave_parts(int max_trap) {
 
 template <int PREC, bool X>
 hipError_t wave_launch(const DevState& s, int n_traps, int max_trap, int nsteps, int accel_only,
-                       int64_t k0, hipStream_t st) {
+                       int64_t k0, const LoneTrap& lone, hipStream_t st) {
     switch (wave_parts(max_trap)) {
-        case 8: return wave_launch_p<PREC, 8, 1, X>(s, n_traps, nsteps, accel_only, k0, st);
+        case 8: return wave_launch_p<PREC, 8, 1, X>(s, n_traps, nsteps, accel_only, k0, lone, st);
         case 4:
             // a part's sources together: all two of traps of <= 8 ions, four of larger ones
             // (us per step, one by one / together: 16 ions 0.69 / 0.59; on several waves,
             // three to six sources a part, 2 or 3 together measured 7 % slower to 2 % faster)
             if (max_trap <= 8)
-                return wave_launch_p<PREC, 4, 1, X, 2>(s, n_traps, nsteps, accel_only, k0, st);
-            return wave_launch_p<PREC, 4, 1, X, 4>(s, n_traps, nsteps, accel_only, k0, st);
-        case 2: return wave_launch_p<PREC, 2, 1, X>(s, n_traps, nsteps, accel_only, k0, st);
-        default: return wave_launch_p<PREC, 1, 1, X>(s, n_traps, nsteps, accel_only, k0, st);
+                return wave_launch_p<PREC, 4, 1, X, 2>(s, n_traps, nsteps, accel_only, k0, lone, st);
+            return wave_launch_p<PREC, 4, 1, X, 4>(s, n_traps, nsteps, accel_only, k0, lone, st);
+        case 2: return wave_launch_p<PREC, 2, 1, X>(s, n_traps, nsteps, accel_only, k0, lone, st);
+        default: return wave_launch_p<PREC, 1, 1, X>(s, n_traps, nsteps, accel_only, k0, lone, st);
     }
 }
 
@@ -3757,37 +3765,37 @@ hipError_t wave_launch(const DevState& s, int n_traps, int max_trap, int nsteps,
 constexpr int kWaveMultiIons = 48;
 template <int PREC, bool X>
 hipError_t wave_launch_multi(const DevState& s, int n_traps, int block, int nsteps,
-                             int accel_only, int64_t k0, hipStream_t st) {
+                             int accel_only, int64_t k0, const LoneTrap& lone, hipStream_t st) {
     switch (block) {
-        case 1024: return wave_launch_p<PREC, 8, 16, X>(s, n_traps, nsteps, accel_only, k0, st);
-        case 512: return wave_launch_p<PREC, 8, 8, X>(s, n_traps, nsteps, accel_only, k0, st);
-        default: return wave_launch_p<PREC, 8, 4, X>(s, n_traps, nsteps, accel_only, k0, st);
+        case 1024: return wave_launch_p<PREC, 8, 16, X>(s, n_traps, nsteps, accel_only, k0, lone, st);
+        case 512: return wave_launch_p<PREC, 8, 8, X>(s, n_traps, nsteps, accel_only, k0, lone, st);
+        default: return wave_launch_p<PREC, 8, 4, X>(s, n_traps, nsteps, accel_only, k0, lone, st);
     }
 }
 
 template <int PREC, bool X>
 hipError_t batch_dispatch_x(const DevState& s, int n_traps, int max_trap, int block, int nsteps,
-                            int accel_only, int64_t k0, double uq, int tpt, hipStream_t st) {
+                            int accel_only, int64_t k0, const LoneTrap& lone, double uq, int tpt, hipStream_t st) {
     // traps of at most 48 ions and block / 8: the wave kernel on block / 64 waves
     // (us per step FP64 / FP32 pairs against the batched kernel: 20 ions 0.88 / 0.99
     // against 1.15 / 1.30, 32 ions 1.02 / 1.13 against 1.32 / 1.48, 48 ions 1.31 /
     // 1.39 against 1.50 / 1.49; 64 ions 1.64 / 1.63 against 1.63 / 1.52 and 100
     // ions 3.29 / 3.03 against 2.72 / 2.35, so larger traps keep the batched kernel)
     if (block != 64 && 8 * max_trap <= block && max_trap <= kWaveMultiIons)
-        return wave_launch_multi<PREC, X>(s, n_traps, block, nsteps, accel_only, k0, st);
+        return wave_launch_multi<PREC, X>(s, n_traps, block, nsteps, accel_only, k0, lone, st);
     switch (block) {
-        case 64: return wave_launch<PREC, X>(s, n_traps, max_trap, nsteps, accel_only, k0, st);
-        case 512: return batch_launch<PREC, 512, X>(s, n_traps, max_trap, nsteps, accel_only, k0, uq, tpt, st);
-        case 1024: return batch_launch<PREC, 1024, X>(s, n_traps, max_trap, nsteps, accel_only, k0, uq, tpt, st);
-        default: return batch_launch<PREC, 256, X>(s, n_traps, max_trap, nsteps, accel_only, k0, uq, tpt, st);
+        case 64: return wave_launch<PREC, X>(s, n_traps, max_trap, nsteps, accel_only, k0, lone, st);
+        case 512: return batch_launch<PREC, 512, X>(s, n_traps, max_trap, nsteps, accel_only, k0, lone, uq, tpt, st);
+        case 1024: return batch_launch<PREC, 1024, X>(s, n_traps, max_trap, nsteps, accel_only, k0, lone, uq, tpt, st);
+        default: return batch_launch<PREC, 256, X>(s, n_traps, max_trap, nsteps, accel_only, k0, lone, uq, tpt, st);
     }
 }
 
 template <int PREC>
 hipError_t batch_dispatch(const DevState& s, int n_traps, int max_trap, int block, int nsteps, int accel_only,
-                          int64_t k0, bool cool_on, double uq, int tpt, hipStream_t st) {
-    return cool_on ? batch_dispatch_x<PREC, true>(s, n_traps, max_trap, block, nsteps, accel_only, k0, uq, tpt, st)
-                   : batch_dispatch_x<PREC, false>(s, n_traps, max_trap, block, nsteps, accel_only, k0, uq, tpt, st);
+                          int64_t k0, const LoneTrap& lone, bool cool_on, double uq, int tpt, hipStream_t st) {
+    return cool_on ? batch_dispatch_x<PREC, true>(s, n_traps, max_trap, block, nsteps, accel_only, k0, lone, uq, tpt, st)
+                   : batch_dispatch_x<PREC, false>(s, n_traps, max_trap, block, nsteps, accel_only, k0, lone, uq, tpt, st);
 }
 
 }  // namespace
@@ -4117,20 +4125,23 @@ hipError_t launch_hessian(const DevState& s, const TrapDev& T, double* D, hipStr
 }
 
 hipError_t launch_batch(const DevState& s, int precision, int n_traps, int max_trap,
-                        const LaunchShape& ls, int nsteps, int64_t k0, hipStream_t st) {
+                        const LaunchShape& ls, int nsteps, int64_t k0, const TrapDev* lone_trap,
+                        hipStream_t st) {
+    const LoneTrap lone{lone_trap ? *lone_trap : TrapDev{}, lone_trap ? 1 : 0};
     switch (precision) {
-        case 0: return batch_dispatch<0>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, k0, ls.cool_on, ls.uniform_q, ls.batch_tpt, st);
-        case 2: return batch_dispatch<2>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, k0, ls.cool_on, ls.uniform_q, ls.batch_tpt, st);
-        default: return batch_dispatch<1>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, k0, ls.cool_on, ls.uniform_q, ls.batch_tpt, st);
+        case 0: return batch_dispatch<0>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, k0, lone, ls.cool_on, ls.uniform_q, ls.batch_tpt, st);
+        case 2: return batch_dispatch<2>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, k0, lone, ls.cool_on, ls.uniform_q, ls.batch_tpt, st);
+        default: return batch_dispatch<1>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, k0, lone, ls.cool_on, ls.uniform_q, ls.batch_tpt, st);
     }
 }
 
 hipError_t launch_batch_accel(const DevState& s, int precision, int n_traps, int max_trap,
-                              const LaunchShape& ls, hipStream_t st) {
+                              const LaunchShape& ls, const TrapDev* lone_trap, hipStream_t st) {
+    const LoneTrap lone{lone_trap ? *lone_trap : TrapDev{}, lone_trap ? 1 : 0};
     switch (precision) {
-        case 0: return batch_dispatch<0>(s, n_traps, max_trap, ls.batch_block, 0, 1, 0, false, ls.uniform_q, ls.batch_tpt, st);
-        case 2: return batch_dispatch<2>(s, n_traps, max_trap, ls.batch_block, 0, 1, 0, false, ls.uniform_q, ls.batch_tpt, st);
-        default: return batch_dispatch<1>(s, n_traps, max_trap, ls.batch_block, 0, 1, 0, false, ls.uniform_q, ls.batch_tpt, st);
+        case 0: return batch_dispatch<0>(s, n_traps, max_trap, ls.batch_block, 0, 1, 0, lone, false, ls.uniform_q, ls.batch_tpt, st);
+        case 2: return batch_dispatch<2>(s, n_traps, max_trap, ls.batch_block, 0, 1, 0, lone, false, ls.uniform_q, ls.batch_tpt, st);
+        default: return batch_dispatch<1>(s, n_traps, max_trap, ls.batch_block, 0, 1, 0, lone, false, ls.uniform_q, ls.batch_tpt, st);
     }
 }
 
