@@ -53,3 +53,36 @@ def test_state_round_trip(torch_gpu, n, prec, batched):
         x = x + 2.0 ** -26 * rows[3]
     assert np.array_equal(got["x"], x)
     sim.close()
+
+
+def test_threads_share_the_staging_memory(torch_gpu):
+    """Six threads, each with its own handle and stream, read and write states at once:
+    more calls under way than idle blocks are kept."""
+    import threading
+
+    from paper_1907_10514_amd import Simulation
+
+    torch, n, bad = torch_gpu, 20000, []
+
+    def work(k):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                sim = Simulation(np.full(n, li.REF_MASS), np.zeros(n), "fp64", autotuned=False)
+                rng = np.random.default_rng(k)
+                for _ in range(5):
+                    rows = rng.normal(0, 1e-4, (6, n))
+                    sim.set_state(*rows, 0.0)
+                    got, _ = sim.get_state()
+                    for c, r in zip(NAMES, rows):
+                        if not np.array_equal(got[c], r):
+                            bad.append((k, c))
+                sim.close()
+        except Exception as e:  # a thread's failure must reach the test
+            bad.append((k, repr(e)))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(6)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
