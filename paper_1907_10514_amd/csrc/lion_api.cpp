@@ -68,7 +68,7 @@ constexpr int kMaxTrap = 1024;
 // traps of at most this many ions step on one wave (the one-wave kernel, us per
 // step FP64 / FP32 pairs / compensated against 256 threads: 16 ions 0.69 / 0.75 /
 // 0.83 against 1.14 / 1.29 / 1.16; 20 ions 1.12 / 1.13 / 1.36 against 1.14 / 1.29
-// / 1.16)
+// / 1.16; since then 16 ions 0.59 and, on 256 threads, 20 ions 0.70)
 constexpr int64_t kOneWaveIons = 16;
 // steps per captured launch when not set: 1000 where one workgroup steps a trap
 // for the whole launch and a step takes a microsecond or two (a single trap of

@@ -3780,7 +3780,8 @@ hipError_t batch_dispatch_x(const DevState& s, int n_traps, int max_trap, int bl
     // (us per step FP64 / FP32 pairs against the batched kernel: 20 ions 0.88 / 0.99
     // against 1.15 / 1.30, 32 ions 1.02 / 1.13 against 1.32 / 1.48, 48 ions 1.31 /
     // 1.39 against 1.50 / 1.49; 64 ions 1.64 / 1.63 against 1.63 / 1.52 and 100
-    // ions 3.29 / 3.03 against 2.72 / 2.35, so larger traps keep the batched kernel)
+    // ions 3.29 / 3.03 against 2.72 / 2.35, so larger traps keep the batched kernel;
+    // measured before the part sums moved to DPP, which took 20 ions to 0.70)
     if (block != 64 && 8 * max_trap <= block && max_trap <= kWaveMultiIons)
         return wave_launch_multi<PREC, X>(s, n_traps, block, nsteps, accel_only, k0, lone, st);
     switch (block) {
