@@ -940,6 +940,8 @@ size_t modes_fixed_bytes(int64_t n) {
     return align_up(m * m * 8) + 2 * align_up(m * 8) + align_up(sizeof(int));
 }
 
+const char* const kHessianNotFinite = "normal modes: the Hessian is not finite";
+
 // Bytes the eigen-solver library wants for this handle's matrix, asked once per
 // handle (the query costs tens of microseconds).
 int solver_scratch(lion_sim* s, bool vectors, double* A, double* W, double* E, int* info,
@@ -1419,10 +1421,21 @@ int lion_normal_modes(lion_sim* s, void* dev_work, size_t bytes, double* omega2,
     // frequencies alone: the kernels here up to order kEigenMax, the library above it
     // and for the modes themselves
     if (!modes && m <= lion::kEigenMax && bytes - fixed >= lion::eigenvalues_scratch_bytes(m)) {
-        LION_HIP(s, lion::launch_eigenvalues(A, m, W, E, base + fixed, st));
+        int e = 0;
+        LION_HIP(s, lion::launch_eigenvalues(A, m, false, W, E, base + fixed, st));
         LION_HIP(s, hipMemcpyAsync(omega2, W, (size_t)m * 8, hipMemcpyDeviceToHost, st));
         LION_HIP(s, hipStreamSynchronize(st));
-        if (!is_fin(omega2[0])) return fail(s, LION_ERR_HIP, "eigen-solver: the Hessian is not finite");
+        if (!is_fin(omega2[0])) {
+            // its squares leave the range of a double: once more, scaled
+            LION_HIP(s, lion::launch_hessian(s->d, T, A, st));
+            LION_HIP(s, lion::launch_scale_matrix(A, m, info, st));
+            LION_HIP(s, lion::launch_eigenvalues(A, m, true, W, E, base + fixed, st));
+            LION_HIP(s, hipMemcpyAsync(omega2, W, (size_t)m * 8, hipMemcpyDeviceToHost, st));
+            LION_HIP(s, hipMemcpyAsync(&e, info, sizeof(int), hipMemcpyDeviceToHost, st));
+            LION_HIP(s, hipStreamSynchronize(st));
+            if (e == lion::kNotFinite) return fail(s, LION_ERR_HIP, kHessianNotFinite);
+            for (int k = 0; k < m; ++k) omega2[k] = std::ldexp(omega2[k], e);
+        }
         // neighbours that agree to rounding may come out in either order
         for (int k = 1; k < m; ++k) omega2[k] = std::max(omega2[k], omega2[k - 1]);
         return LION_OK;

@@ -17,20 +17,24 @@ namespace lion {
 namespace {
 
 // Reflector of a column x (entries below the diagonal; x0 the first, sigma the sum of
-// squares of the others): (I - beta v v^T) x = alpha e1 with v = x but v0 first.
+// squares of the others): (I - beta v v^T) x = alpha e1 with v = x but v0 first.  A
+// column whose squares add up to less than kTinySquare is taken as zero below x0: beta
+// would leave the range of a double, and against a matrix of norm kNormMin or more, the
+// least that k_bisect accepts, what is left out is below 2^-150.
+constexpr double kTinySquare = 0x1p-900, kNormMin = 0x1p-300, kNormMax = 0x1p+500;
 struct Reflector {
     double beta, alpha, v0;
 };
 
 __device__ __forceinline__ Reflector reflector(double x0, double sigma) {
     Reflector h;
-    if (sigma == 0.0) {
+    const double s = fma(x0, x0, sigma);
+    if (sigma == 0.0 || s < kTinySquare) {
         h.beta = 0.0;
         h.alpha = x0;
         h.v0 = 0.0;
     } else {
         // the hardware's seeds with a cubic step each: every wave runs this chain
-        const double s = fma(x0, x0, sigma);
         const double y0 = __builtin_amdgcn_rsq(s);
         const double e = fma(-(s * y0), y0, 1.0);
         const double y = fma(y0 * e, fma(e, 0.375, 0.5), y0);
@@ -317,8 +321,10 @@ __device__ __forceinline__ int sturm_count(const double2* de, int m8, double x) 
 
 // One wave per eigenvalue: 64 points cut its interval into 65 parts a round, until
 // the ends are neighbours to rounding.  Bound by the chain of m minors a round: 41 us
-// at order 192.
-__global__ __launch_bounds__(64) void k_bisect(TriWork t, int m, double* __restrict__ W) {
+// at order 192.  NaN for a matrix that is not finite or (checked: not after k_scale) whose
+// norm leaves its reduction's squares out of range.
+__global__ __launch_bounds__(64) void k_bisect(TriWork t, int m, bool checked,
+                                               double* __restrict__ W) {
     __shared__ double2 de[kEigenMax];
     const int lane = threadIdx.x, m8 = (m + 7) & ~7;
     double lo = __builtin_inf(), hi = -__builtin_inf();
@@ -335,11 +341,11 @@ __global__ __launch_bounds__(64) void k_bisect(TriWork t, int m, double* __restr
         lo = fmin(lo, __shfl_xor(lo, off));
         hi = fmax(hi, __shfl_xor(hi, off));
     }
-    if (__ballot(!finite) != 0) {
+    const double norm = fmax(fabs(lo), fabs(hi));
+    if (__ballot(!finite) != 0 || (checked && !(norm >= kNormMin && norm <= kNormMax))) {
         if (lane == 0) W[blockIdx.x] = __builtin_nan("");
         return;
     }
-    const double norm = fmax(fabs(lo), fabs(hi));
     if (norm == 0.0) {  // the zero matrix
         if (lane == 0) W[blockIdx.x] = 0.0;
         return;
@@ -370,12 +376,47 @@ __global__ __launch_bounds__(64) void k_bisect(TriWork t, int m, double* __restr
     if (lane == 0) W[k] = __builtin_amdgcn_ldexp(0.5 * (lo + hi), ex);
 }
 
+// One workgroup: A (count entries) times the power of two that brings its largest entry
+// into [1/2, 1), and that power's negative exponent; kNotFinite and A as it was if an entry
+// is not finite.
+__global__ __launch_bounds__(1024) void k_scale(double* __restrict__ A, int count,
+                                                int* __restrict__ exponent) {
+    __shared__ double top;
+    __shared__ double red[16];
+    const int tid = threadIdx.x;
+    double mx = 0.0;
+    for (int i = tid; i < count; i += 1024) {
+        const double a = fabs(A[i]);
+        mx = a <= 0x1.fffffffffffffp+1023 ? fmax(mx, a) : __builtin_inf();
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
+    if ((tid & 63) == 0) red[tid >> 6] = mx;
+    __syncthreads();
+    if (tid == 0) {
+        for (int k = 0; k < 16; ++k) mx = fmax(mx, red[k]);
+        top = mx;
+    }
+    __syncthreads();
+    const bool finite = __builtin_isfinite(top);
+    const int e = finite ? __builtin_amdgcn_frexp_exp(top) : kNotFinite;
+    if (tid == 0) *exponent = e;
+    if (!finite) return;  // the same in every thread
+    for (int i = tid; i < count; i += 1024) A[i] = __builtin_amdgcn_ldexp(A[i], -e);
+}
+
 }  // namespace
+
+hipError_t launch_scale_matrix(double* A, int m, int* exponent, hipStream_t st) {
+    if (m < 1 || m > kEigenMax) return hipErrorInvalidValue;
+    k_scale<<<1, 1024, 0, st>>>(A, m * m, exponent);
+    return hipGetLastError();
+}
 
 size_t eigenvalues_scratch_bytes(int m) { return (size_t)(7 * m + 2) * sizeof(double); }
 
-hipError_t launch_eigenvalues(double* A, int m, double* W, double* E, void* scratch,
-                              hipStream_t st) {
+hipError_t launch_eigenvalues(double* A, int m, bool scaled, double* W, double* E,
+                              void* scratch, hipStream_t st) {
     if (m < 1 || m > kEigenMax) return hipErrorInvalidValue;
     double* s = (double*)scratch;
     TriWork t{};
@@ -399,7 +440,7 @@ hipError_t launch_eigenvalues(double* A, int m, double* W, double* E, void* scra
         k_tri_regs<2><<<1, 64 * kTriWaves, 0, st>>>(A, m, j0, t);
     else
         k_tri_regs<3><<<1, 64 * kTriWaves, 0, st>>>(A, m, j0, t);
-    k_bisect<<<m, 64, 0, st>>>(t, m, W);
+    k_bisect<<<m, 64, 0, st>>>(t, m, !scaled, W);
     return hipGetLastError();
 }
 

@@ -311,11 +311,16 @@ int eigh_device(void* h, double* A, int m, double* W, double* E, int* info, bool
 // Eigenvalues alone (ascending up to rounding, into W) of a symmetric m x m matrix,
 // m <= kEigenMax, by the kernels of lion_eigen.hip; A is overwritten, E is m doubles,
 // scratch eigenvalues_scratch_bytes(m).  NaN throughout for a matrix that is not
-// finite.
+// finite and, unless `scaled` says that launch_scale_matrix has seen to it, for one whose
+// norm is below 2^-300 or above 2^500 (or whose squares leave the range of a double).
 constexpr int kEigenMax = 512;
+constexpr int kNotFinite = INT32_MAX;
 size_t eigenvalues_scratch_bytes(int m);
-hipError_t launch_eigenvalues(double* A, int m, double* W, double* E, void* scratch,
-                              hipStream_t st);
+hipError_t launch_eigenvalues(double* A, int m, bool scaled, double* W, double* E,
+                              void* scratch, hipStream_t st);
+// The m x m matrix A, m <= kEigenMax, times 2^-e so that its largest entry is in [1/2, 1);
+// *exponent = e, or kNotFinite.
+hipError_t launch_scale_matrix(double* A, int m, int* exponent, hipStream_t st);
 // One step (or, with kModeAccel, one force evaluation) of one trap in a single
 // launch: positions read from buffer parity_in (0: src/srcm, 1: src2/srcm2);
 // drifted positions written to the other buffer, or with home_out to buffer 0.
