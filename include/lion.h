@@ -264,7 +264,8 @@ size_t lion_normal_modes_workspace_bytes(lion_sim *sim);
  * eigenvector of omega2[k], component 3i + axis.  A minimum of the potential
  * (lion_minimize) gives omega2 >= 0.  Time-dependent trap, batched handle or
  * rigid bodies -> LION_ERR_UNSUPPORTED; workspace too small or misaligned ->
- * LION_ERR_WORKSPACE; solver failure -> LION_ERR_HIP.  Synchronises. */
+ * LION_ERR_WORKSPACE; a Hessian that is not finite or solver failure ->
+ * LION_ERR_HIP.  Synchronises. */
 int lion_normal_modes(lion_sim *sim, void *dev_work, size_t bytes, double *omega2,
                       double *modes);
 

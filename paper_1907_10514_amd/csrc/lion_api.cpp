@@ -1440,10 +1440,16 @@ int lion_normal_modes(lion_sim* s, void* dev_work, size_t bytes, double* omega2,
         for (int k = 1; k < m; ++k) omega2[k] = std::max(omega2[k], omega2[k - 1]);
         return LION_OK;
     }
+    // the library is handed finite matrices only
+    int info_h = 0;
+    LION_HIP(s, hipMemsetAsync(info, 0, sizeof(int), st));
+    LION_HIP(s, lion::launch_matrix_finite(A, (int64_t)m * m, info, st));
+    LION_HIP(s, hipMemcpyAsync(&info_h, info, sizeof(int), hipMemcpyDeviceToHost, st));
+    LION_HIP(s, hipStreamSynchronize(st));
+    if (info_h == lion::kNotFinite) return fail(s, LION_ERR_HIP, kHessianNotFinite);
     if (lion::eigh_device(s->eigh, A, m, W, E, info, modes != nullptr, base + fixed,
                           bytes - fixed, st, err) != 0)
         return fail(s, LION_ERR_HIP, err);
-    int info_h = 0;
     LION_HIP(s, hipMemcpyAsync(omega2, W, (size_t)m * 8, hipMemcpyDeviceToHost, st));
     LION_HIP(s, hipMemcpyAsync(&info_h, info, sizeof(int), hipMemcpyDeviceToHost, st));
     if (modes) LION_HIP(s, hipMemcpyAsync(modes, A, (size_t)m * m * 8, hipMemcpyDeviceToHost, st));

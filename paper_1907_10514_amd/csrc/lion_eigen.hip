@@ -405,11 +405,27 @@ __global__ __launch_bounds__(1024) void k_scale(double* __restrict__ A, int coun
     for (int i = tid; i < count; i += 1024) A[i] = __builtin_amdgcn_ldexp(A[i], -e);
 }
 
+// *flag = kNotFinite if one of the count entries is not finite.
+__global__ __launch_bounds__(256) void k_matrix_finite(const double* __restrict__ A,
+                                                       int64_t count, int* __restrict__ flag) {
+    bool finite = true;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count;
+         i += (int64_t)gridDim.x * 256)
+        finite = finite && __builtin_isfinite(A[i]);
+    if (!finite) *flag = kNotFinite;
+}
+
 }  // namespace
 
 hipError_t launch_scale_matrix(double* A, int m, int* exponent, hipStream_t st) {
     if (m < 1 || m > kEigenMax) return hipErrorInvalidValue;
     k_scale<<<1, 1024, 0, st>>>(A, m * m, exponent);
+    return hipGetLastError();
+}
+
+hipError_t launch_matrix_finite(const double* A, int64_t count, int* flag, hipStream_t st) {
+    const unsigned g = (unsigned)std::min<int64_t>((count + 255) / 256, 4096);
+    k_matrix_finite<<<g, 256, 0, st>>>(A, count, flag);
     return hipGetLastError();
 }
 

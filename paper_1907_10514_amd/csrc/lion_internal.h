@@ -321,6 +321,8 @@ hipError_t launch_eigenvalues(double* A, int m, bool scaled, double* W, double* 
 // The m x m matrix A, m <= kEigenMax, times 2^-e so that its largest entry is in [1/2, 1);
 // *exponent = e, or kNotFinite.
 hipError_t launch_scale_matrix(double* A, int m, int* exponent, hipStream_t st);
+// *flag (device) = kNotFinite if an entry of A is not finite, else left alone.
+hipError_t launch_matrix_finite(const double* A, int64_t count, int* flag, hipStream_t st);
 // One step (or, with kModeAccel, one force evaluation) of one trap in a single
 // launch: positions read from buffer parity_in (0: src/srcm, 1: src2/srcm2);
 // drifted positions written to the other buffer, or with home_out to buffer 0.

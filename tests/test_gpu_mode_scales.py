@@ -1,7 +1,7 @@
 """Mode frequencies over the range of a double: couplings whose squares underflow inside an
 ordinary matrix, matrices whose entries' squares overflow or underflow, with and without
 the column-per-launch part of the solver (order above 192), against the oracle's dense
-eigenvalues."""
+eigenvalues; and a Hessian that is not finite is refused on every path."""
 from __future__ import annotations
 
 import numpy as np
@@ -68,3 +68,22 @@ def test_all_entries_large_or_small(torch_gpu, oracle_mod, n, spacing):
     """No trap: the entries go as spacing^-3."""
     pos = spacing * np.random.default_rng(n).normal(0, n ** (1 / 3), (3, n))
     _check(oracle_mod, pos, False)
+
+
+@pytest.mark.parametrize("vectors", [False, True])
+@pytest.mark.parametrize("n", [3, 66, 171])
+def test_not_finite(torch_gpu, n, vectors):
+    from paper_1907_10514_amd import LionError, Simulation
+    from paper_1907_10514_amd import lion as L
+
+    sim = Simulation(np.full(n, li.REF_MASS), np.full(n, li.E_CHARGE), "fp64")
+    pos = np.random.default_rng(n).normal(0, 1e160, (3, n))  # r^2 overflows
+    sim.set_state(*pos, *np.zeros((3, n)), 0.0)
+    for _ in range(2):
+        with pytest.raises(LionError) as ei:
+            sim.normal_modes(vectors=vectors)
+        assert ei.value.code == L.LION_ERR_HIP and "not finite" in str(ei.value)
+    pos = np.random.default_rng(n).normal(0, 1e-5 * n ** (1 / 3), (3, n))
+    sim.set_state(*pos, *np.zeros((3, n)), 0.0)  # the handle goes on
+    assert np.all(np.isfinite(sim.normal_modes(vectors=vectors)[0]))
+    sim.close()
