@@ -265,7 +265,9 @@ void clear_graphs(lion_sim* s) {
 // for itself (each thread its own), at most kStageKept idle ones are kept, and all go
 // with the last handle.  A half of a block takes kStageIons ions of a state; larger
 // states go in pieces that alternate between the halves, so that the host copies one
-// while the device moves the next.
+// while the device moves the next.  The blocks are coherent whatever the process's default
+// is and their events release to the system: the host reads and rewrites a half after an
+// event alone, with later pieces still under way.
 constexpr int64_t kStageIons = 8192;
 constexpr size_t kStageKept = 4;
 std::mutex g_stage_mutex;
@@ -296,7 +298,8 @@ public:
             }
         }
         if (!p_)
-            status_ = hipHostMalloc((void**)&p_, 2 * 6 * kStageIons * sizeof(double), hipHostMallocPortable);
+            status_ = hipHostMalloc((void**)&p_, 2 * 6 * kStageIons * sizeof(double),
+                                    hipHostMallocPortable | hipHostMallocCoherent);
     }
     Stage(const Stage&) = delete;
     Stage& operator=(const Stage&) = delete;
@@ -320,7 +323,8 @@ private:
 
 int stage_events(lion_sim* s) {
     for (auto& e : s->stage_ev)
-        if (!e && s->n > kStageIons) LION_HIP(s, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        if (!e && s->n > kStageIons)
+            LION_HIP(s, hipEventCreateWithFlags(&e, hipEventDisableTiming | hipEventReleaseToSystem));
     return LION_OK;
 }
 
