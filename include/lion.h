@@ -29,8 +29,8 @@
  *     a second caller-owned workspace for its eigen-solver).  The HIP runtime
  *     allocates what it needs to instantiate launch graphs.
  *   - Host memory: states and results pass through blocks of 0.8 MB of pinned
- *     memory, one per call under way; at most four idle ones are kept, until
- *     the last handle is destroyed.
+ *     memory, one per call under way; idle ones are kept, at most sixteen and
+ *     one per handle, until the last handle is destroyed.
  *   - Every call runs on the HIP stream given at creation (a hipStream_t
  *     passed as void*, NULL = the default stream) and returns once its work is
  *     queued, except lion_get_state / lion_compute_accel / lion_get_energy,

@@ -262,29 +262,31 @@ void clear_graphs(lion_sim* s) {
 
 // Pinned host memory through which states and results pass.  Allocating it costs some
 // hundred microseconds, so blocks of one size outlive the calls: a call leases one
-// for itself (each thread its own), at most kStageKept idle ones are kept, and all go
-// with the last handle.  A half of a block takes kStageIons ions of a state; larger
+// for itself (each thread its own), idle ones are kept up to one per handle (no more calls
+// can be under way) and kStageKept, and all go with the last handle.  The lock covers the
+// list alone, as freeing a block takes as long as allocating it and other threads' calls
+// would wait.  A half of a block takes kStageIons ions of a state; larger
 // states go in pieces that alternate between the halves, so that the host copies one
 // while the device moves the next.  The blocks are coherent whatever the process's default
 // is and their events release to the system: the host reads and rewrites a half after an
 // event alone, with later pieces still under way.
 constexpr int64_t kStageIons = 8192;
-constexpr size_t kStageKept = 4;
+constexpr int kStageKept = 16;
 std::mutex g_stage_mutex;
-std::vector<double*> g_stage_idle;
+double* g_stage_idle[kStageKept];
+int g_stage_count = 0;
 int g_handles = 0;
 
-void stage_trim(size_t keep) {  // with the mutex held
-    while (g_stage_idle.size() > keep) {
-        (void)hipHostFree(g_stage_idle.back());
-        g_stage_idle.pop_back();
-    }
-}
-
+// One handle more or less.
 void count_handle(int by) {
-    std::lock_guard<std::mutex> lock(g_stage_mutex);
-    g_handles += by;
-    if (g_handles == 0) stage_trim(0);
+    double* spare[kStageKept];
+    int n = 0;
+    {
+        std::lock_guard<std::mutex> lock(g_stage_mutex);
+        g_handles += by;
+        while (g_stage_count > g_handles) spare[n++] = g_stage_idle[--g_stage_count];
+    }
+    while (n > 0) (void)hipHostFree(spare[--n]);
 }
 
 class Stage {
@@ -292,10 +294,7 @@ public:
     explicit Stage(hipStream_t st) : stream_(st) {
         {
             std::lock_guard<std::mutex> lock(g_stage_mutex);
-            if (!g_stage_idle.empty()) {
-                p_ = g_stage_idle.back();
-                g_stage_idle.pop_back();
-            }
+            if (g_stage_count > 0) p_ = g_stage_idle[--g_stage_count];
         }
         if (!p_)
             status_ = hipHostMalloc((void**)&p_, 2 * 6 * kStageIons * sizeof(double),
@@ -306,9 +305,14 @@ public:
     ~Stage() {
         if (status_ != hipSuccess) return;
         if (busy_) (void)hipStreamSynchronize(stream_);  // an error came before the call's own
-        std::lock_guard<std::mutex> lock(g_stage_mutex);
-        g_stage_idle.push_back(p_);
-        stage_trim(g_handles > 0 ? kStageKept : 0);
+        {
+            std::lock_guard<std::mutex> lock(g_stage_mutex);
+            if (g_stage_count < std::min(kStageKept, g_handles)) {
+                g_stage_idle[g_stage_count++] = p_;
+                return;
+            }
+        }
+        (void)hipHostFree(p_);
     }
     hipError_t status() const { return status_; }
     double* half(int h) { return p_ + h * 6 * kStageIons; }
