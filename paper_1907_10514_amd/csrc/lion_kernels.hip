@@ -2791,11 +2791,13 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
 // 16.5 with packing, pair kernel and epilogue, up to 2048 ions 6.2 against 12.
 constexpr int kDirectBlock = 256;
 
-// q / e, rounded as the division is (one correction of the product with 1/e).
+// q / e, rounded as the division is (one correction of the product with 1/e) and, for
+// charges that are infinite or leave a double's range, infinite as it is.
 __device__ __forceinline__ double charge_in_e(double q) {
     constexpr double inv = 1.0 / kElementaryCharge;
     const double r = q * inv;
-    return fma(fma(-r, kElementaryCharge, q), inv, r);
+    return __builtin_amdgcn_div_fixup(fma(fma(-r, kElementaryCharge, q), inv, r),
+                                      kElementaryCharge, q);
 }
 
 template <int TR>
