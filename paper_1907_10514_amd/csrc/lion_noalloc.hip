@@ -91,10 +91,10 @@ extern "C" int lion_accel_noalloc(int64_t n, const double* x, const double* y, c
     // the packed copies below allow
     const double* const in[5] = {x, y, z, charges_C, masses_kg};
     double* const out[3] = {ax, ay, az};
-    bool overlap = false;
-    for (const double* a : in)
-        for (const double* b : out) overlap = overlap || (a < b + n && b < a + n);
-    if (precision == LION_FP64 && n <= lion::kDirectIons && !overlap) {
+    bool direct = precision == LION_FP64 && n <= lion::kDirectIons;
+    for (int a = 0; a < 5 && direct; ++a)
+        for (const double* b : out) direct = direct && !(in[a] < b + n && b < in[a] + n);
+    if (direct) {
         const hipError_t e = lion::launch_accel_direct(in, n, T, out, st);
         if (e != hipSuccess) return fail(LION_ERR_HIP, hipGetErrorString(e));
         return LION_OK;

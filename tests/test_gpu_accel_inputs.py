@@ -51,4 +51,5 @@ def test_like_the_packed_path(torch_gpu, n, row, value):
         # sums of n terms in another order, against the largest of the ion's components
         scale = np.max(np.abs(np.where(fin, ref, 0.0)), axis=0)
         cap = np.maximum(scale, np.median(scale))
-        assert np.all(np.abs(np.where(fin, got, 0.0) - np.where(fin, ref, 0.0)) <= 4e-15 * n * cap + 1e-300)
+        off = np.abs(np.where(fin, got, 0.0) - np.where(fin, ref, 0.0))
+        assert np.all(off <= 4e-15 * n * cap + 1e-300)
