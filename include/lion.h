@@ -192,6 +192,17 @@ int lion_set_beam(lion_sim *sim, int32_t beam, int32_t species, double kx, doubl
 int lion_set_bath(lion_sim *sim, int32_t bath, int32_t species, double temperature_K,
                   double damping_time_s, uint64_t seed);
 
+/* Optional memory for the kicks of the baths: dev_memory (caller-owned device
+ * memory, 256-byte aligned, `bytes` long, alive until lion_destroy or the next
+ * call of this) lets all of the chip make the draws of many half-steps ahead of
+ * the steps: 24 bytes per ion and half-step and 8 per ion, ions rounded up to
+ * 64, at most 1024 half-steps.  Results do not change.  Without it (the default,
+ * or NULL), or where it holds fewer than 3 half-steps, the
+ * stepping kernels draw for themselves, which is slower for single traps and for
+ * batches of up to about 50000 ions.  Synchronises; drops captured launch
+ * graphs.  Misaligned -> LION_ERR_WORKSPACE. */
+int lion_set_bath_memory(lion_sim *sim, void *dev_memory, size_t bytes);
+
 /* Run-wide step count that numbers the bath draws (steps completed so far; it
  * grows by nsteps in every lion_step).  Set it when resuming a run so that the
  * bath draws continue the same sequence.  steps_done < 0 -> LION_ERR_ARG. */

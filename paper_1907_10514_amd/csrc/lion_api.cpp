@@ -100,18 +100,20 @@ int slices_for(int64_t n) {
     return std::max(j_max_for(n), nb <= lion::kMaxSymTiles ? nb : 0);
 }
 
-// Bath kicks drawn ahead of the steps: half-steps per launch of the draws, at
-// most 2^21 ion half-steps (50 MB) and 1024 half-steps, at least the three that
-// the start and the first step of a chunk need.
+// Table of bath kicks drawn ahead of the steps, in memory that lion_set_bath_memory was
+// given: as many half-steps as fit, at most 1024, at least the three that the start and the
+// first step of a chunk take.
 int64_t noise_stride_for(int64_t n) { return round_up(n, 64); }
-int noise_half_steps(int64_t n) {
-    return (int)std::max<int64_t>(3, std::min<int64_t>(1024, (int64_t(1) << 21) / noise_stride_for(n)));
+int noise_half_steps(int64_t n, size_t bytes) {
+    const size_t row = noise_stride_for(n) * sizeof(double);
+    const size_t h = bytes < row ? 0 : std::min<size_t>((bytes - row) / (3 * row), 1024);
+    return h < 3 ? 0 : (int)h;
 }
 
 struct Layout {
     size_t src, srcm, v, a, qm, qe, mass, trap_of, part, scratch, traps, offsets, order, counter,
         flags, body_code, tile_body, tile_brange, body_gmin, body_gmax, cool, species, vacc, vavg, rigid, rb, dbody,
-        rmembers, rstart, minst, minpart, src2, srcm2, noise_c, noise, total;
+        rmembers, rstart, minst, minpart, src2, srcm2, total;
 };
 
 Layout layout_for(int64_t n, int32_t n_traps, int precision, bool batched) {
@@ -158,8 +160,6 @@ Layout layout_for(int64_t n, int32_t n_traps, int precision, bool batched) {
     // second position buffers of the one-launch step (single trap)
     L.src2 = batched ? SIZE_MAX : take(np * sizeof(double4));
     L.srcm2 = (precision != LION_FP64 && !batched) ? take(np * sizeof(lion::MixedSrc)) : SIZE_MAX;
-    L.noise_c = take(noise_stride_for(n) * sizeof(double));
-    L.noise = take((size_t)noise_half_steps(n) * 3 * noise_stride_for(n) * sizeof(double));
     L.total = o;
     return L;
 }
@@ -418,16 +418,21 @@ int begin_call(lion_sim* s) {
     return LION_OK;
 }
 
-// Captured graphs hold the kernels built with or without cooling, and the draws
-// of the baths only while one is on.
+// Captured graphs hold one build of the kernels, and the draws of the baths into the
+// table only while one is on.
 int switch_cooling(lion_sim* s, bool on, bool baths) {
-    if (on == s->ls.cool_on && baths == s->ls.bath_on) return LION_OK;
+    const lion::CoolKind kind = !on ? lion::kCoolOff
+                                    : (baths && !s->d.noise_h ? lion::kCoolDraw : lion::kCoolTable);
+    if (kind == s->ls.cool && baths == s->ls.bath_on) return LION_OK;
     LION_HIP(s, hipStreamSynchronize(s->stream));  // no launch of a graph still pending
     clear_graphs(s);
-    s->ls.cool_on = on;
+    s->ls.cool = kind;
     s->ls.bath_on = baths;
     return LION_OK;
 }
+
+// The baths' draws go into the table ahead of the steps.
+bool table_on(const lion_sim* s) { return s->ls.bath_on && s->d.noise_h > 0; }
 
 // Half-step factors of the beams and baths for step size dt, and the run-wide
 // step count, into the handle's mirror.  Uses one dt for every trap (the first).
@@ -509,14 +514,14 @@ int refresh_accel(lion_sim* s) {
 // draws), which no graph makes cheaper.
 bool one_workgroup(const lion_sim* s) { return s->batched || small_path_active(s); }
 
-// L steps of those kernels after k0 of the call, as many per launch as the bath table
-// holds half-steps of.
+// L steps of those kernels after k0 of the call, as many per launch as the bath table (if
+// there is one) holds half-steps of.
 hipError_t enqueue_one_workgroup(lion_sim* s, int64_t L, int64_t k0, hipStream_t st) {
-    const int64_t most = s->ls.bath_on ? s->d.noise_h / 2 : L;
+    const int64_t most = table_on(s) ? s->d.noise_h / 2 : L;
     hipError_t e = hipSuccess;
     for (int64_t done = 0; done < L && e == hipSuccess;) {
         const int64_t K = std::min(most, L - done);
-        if (s->ls.bath_on)
+        if (table_on(s))
             e = lion::launch_noise(s->d, false, 2 * (k0 + done) + 2, (int)(2 * K), st);
         if (e == hipSuccess)
             e = lion::launch_batch(s->d, s->precision, s->n_traps, s->max_trap, s->ls, (int)K,
@@ -534,12 +539,12 @@ hipError_t enqueue_chunk(lion_sim* s, int64_t L, hipStream_t st) {
     // bath table: the first block holds the drift's half-step and those of the
     // steps that follow, later blocks whole steps; step k (from 1) ends with its
     // second half at bath_at(k) and the next step's first half behind it
-    const int64_t per = (s->d.noise_h - 1) / 2;  // steps per block
+    const int64_t per = std::max(1, (s->d.noise_h - 1) / 2);  // steps per block
     auto bath_at = [&](int64_t k) { return (int)(2 * ((k - 1) % per) + (k <= per ? 1 : 0)); };
     // the draws of step k's block when it starts one (steps: steps completed by
     // the device's counter when the launch runs)
     auto draws = [&](int64_t k, int64_t steps) {
-        if (!s->ls.bath_on || (k - 1) % per != 0) return hipSuccess;
+        if (!table_on(s) || (k - 1) % per != 0) return hipSuccess;
         const int64_t K = std::min(per, L - (k - 1));
         const int first = k == 1 ? 1 : 0;
         return lion::launch_noise(s->d, true, 2 * (k - steps) + 1 - first, (int)(2 * K) + first, st);
@@ -549,7 +554,7 @@ hipError_t enqueue_chunk(lion_sim* s, int64_t L, hipStream_t st) {
     if (rows_active(s)) {
         // one launch per step; positions alternate between the two buffers and
         // the last step of the chunk leaves them in the first
-        e = lion::launch_drift(s->d, s->ls.cool_on, 0, st);
+        e = lion::launch_drift(s->d, s->ls.cool, 0, st);
         for (int64_t k = 0; k < L && e == hipSuccess; ++k) {
             const bool last = k + 1 == L;
             if (k > 0) e = draws(k + 1, 0);
@@ -566,7 +571,7 @@ hipError_t enqueue_chunk(lion_sim* s, int64_t L, hipStream_t st) {
         e = lion::launch_rigid_wrench(s->d, false, st);
         if (e != hipSuccess) return e;
     }
-    e = lion::launch_drift(s->d, s->ls.cool_on, 0, st);
+    e = lion::launch_drift(s->d, s->ls.cool, 0, st);
     if (e != hipSuccess) return e;
     if (rigid) {
         e = lion::launch_rigid_drift(s->d, st);
@@ -782,10 +787,9 @@ int create_common(lion_sim** out, int32_t n_traps, const int64_t* n_per_trap, in
     d.minpart = (double*)(base + L.minpart);
     d.src2 = L.src2 == SIZE_MAX ? nullptr : (double4*)(base + L.src2);
     d.srcm2 = L.srcm2 == SIZE_MAX ? nullptr : (lion::MixedSrc*)(base + L.srcm2);
-    d.noise_c = (double*)(base + L.noise_c);
-    d.noise = (double*)(base + L.noise);
     d.noise_stride = noise_stride_for(n);
-    d.noise_h = noise_half_steps(n);
+    d.noise_h = 0;  // set by lion_set_bath_memory
+    d.noise_c = d.noise = nullptr;
     d.nbodies = 0;  // set by lion_set_rigid_bodies
     d.rigid = nullptr;
     d.rb = nullptr;
@@ -1236,6 +1240,20 @@ int lion_set_bath(lion_sim* s, int32_t bath, int32_t species, double temperature
     return LION_OK;
 }
 
+int lion_set_bath_memory(lion_sim* s, void* dev_memory, size_t bytes) {
+    if (check_handle(s)) return LION_ERR_ARG;
+    if (((uintptr_t)dev_memory) % kAlign)
+        return fail(s, LION_ERR_WORKSPACE, "bath memory not 256-byte aligned");
+    LION_HIP(s, hipSetDevice(s->device));
+    LION_HIP(s, hipStreamSynchronize(s->stream));  // no launch with the old memory pending
+    clear_graphs(s);
+    DevState& d = s->d;
+    d.noise_h = dev_memory ? noise_half_steps(s->n, bytes) : 0;
+    d.noise_c = d.noise_h ? (double*)dev_memory : nullptr;
+    d.noise = d.noise_h ? d.noise_c + d.noise_stride : nullptr;
+    return LION_OK;
+}
+
 int lion_set_step_index(lion_sim* s, int64_t steps_done) {
     if (check_handle(s)) return LION_ERR_ARG;
     if (steps_done < 0) return fail(s, LION_ERR_ARG, "steps_done must be >= 0");
@@ -1306,7 +1324,7 @@ static int step_common(lion_sim* s, int64_t nsteps, const double* dts) {
     int rc = prepare_cooling(s, dts[0]);
     // a single trap in one workgroup gets its parameters by value and, without cooling,
     // reads nothing else that a call sets
-    if (rc == LION_OK && (!small_path_active(s) || s->ls.cool_on)) rc = begin_call(s);
+    if (rc == LION_OK && (!small_path_active(s) || s->ls.cool != lion::kCoolOff)) rc = begin_call(s);
     if (rc) return rc;
     const int64_t S = chunk_len(s);
     for (int64_t done = 0; done < nsteps;) {

@@ -161,6 +161,7 @@ struct DevState {
     int32_t* flags;   // [4] diagnostics (non-finite count)
     CoolDev* cool;    // beams, baths and the velocity time average
     int32_t* species; // [n_pad] species label per ion (default 0)
+    // bath table, in memory from lion_set_bath_memory (else NULL and 0)
     double* noise_c;  // [noise_stride] bath factor per ion and half-step
     double* noise;    // [noise_h][3][noise_stride] bath kicks of the half-steps ahead
     int64_t noise_stride;
@@ -188,6 +189,10 @@ struct DevState {
     MixedSrc* srcm2;
 };
 
+// Builds of the stepping kernels: without beams, baths and time averages; with them and
+// the baths from the table (or no bath on); with them and the draws made in the kernel.
+enum CoolKind : int { kCoolOff = 0, kCoolTable = 1, kCoolDraw = 2 };
+
 struct LaunchShape {
     int i_per_lane;
     int j_split;
@@ -200,10 +205,10 @@ struct LaunchShape {
     int update_waves; // waves per 64 ions in the step epilogue (4, 8 or 16)
     int small_path;   // single trap stepped by the one-workgroup kernel (k_batch, one trap)
     int batch_tpt;    // batched kernel: targets per thread for traps of >= 128 ions (0: by size)
-    bool cool_on;     // a beam, bath or time average is on: the kernels built with them run
+    CoolKind cool;    // which build of the stepping kernels runs
     double uniform_q;  // every ion's charge in units of e when all are equal, else 0
     int sym_masked;    // pair-once kernels with the per-pair body test (bodies share tiles)
-    bool bath_on;      // a bath is on: launch_noise goes ahead of the steps
+    bool bath_on;      // a bath is on: with a table, launch_noise goes ahead of the steps
     int rows;          // one launch per step (k_rows) for the single trap
     int rows_tr;       // targets per workgroup of that launch: 1, 2 or 4
 };
@@ -246,7 +251,7 @@ hipError_t launch_import(const DevState& s, const double* in, int64_t i0, int64_
 // bath_idx: table index of the step's first half (launch_drift) or of the second
 // half of the step that ends (launch_update, launch_rows; the first half of the
 // next step follows it).
-hipError_t launch_drift(const DevState& s, bool cool_on, int bath_idx, hipStream_t st);
+hipError_t launch_drift(const DevState& s, CoolKind cool, int bath_idx, hipStream_t st);
 hipError_t launch_pair(const DevState& s, int precision, const LaunchShape& ls, bool count_step,
                        hipStream_t st);
 hipError_t launch_update(const DevState& s, int precision, const LaunchShape& ls, int mode,
@@ -267,8 +272,8 @@ hipError_t launch_accel_direct(const double* const* in, int64_t n, const TrapDev
                                double* const* out, hipStream_t st);
 // Message returned by lion_last_error(NULL) (calls without a handle).
 void set_handle_free_error(const std::string& msg);
-// Steps of a batch (or a lone trap in one workgroup); with a bath on, the table
-// holds the 2 nsteps half-steps from index 0.  k0: steps of the call done before;
+// Steps of a batch (or a lone trap in one workgroup); with kCoolTable and a bath on, the
+// table holds the 2 nsteps half-steps from index 0.  k0: steps of the call done before;
 // lone_trap: a single trap's parameters, or NULL for those on the device.
 hipError_t launch_batch(const DevState& s, int precision, int n_traps, int max_trap,
                         const LaunchShape& ls, int nsteps, int64_t k0, const TrapDev* lone_trap,

@@ -275,11 +275,11 @@ struct CoolRef {
     int64_t origin;
 };
 
-// X = false: a kernel built with beams, baths and time averages compiled out
-// (all switches constant zero), launched while none of them is on.
-template <bool X>
+// X (CoolKind) = kCoolOff: a kernel built with beams, baths and time averages compiled
+// out (all switches constant zero), launched while none of them is on.
+template <int X>
 __device__ __forceinline__ CoolRef cool_switches(const CoolDev* __restrict__ C) {
-    if constexpr (X) {
+    if constexpr (X != kCoolOff) {
         return CoolRef{C->beams, C->nbeams, C->nbaths, C->avg_window, C->avg_origin};
     } else {
         return CoolRef{nullptr, 0, 0, 0, 0};
@@ -291,13 +291,46 @@ struct BathMap {
     double c = 1.0, nx = 0.0, ny = 0.0, nz = 0.0;
 };
 
+// That of the baths C[0 .. nt) for an ion in the half-step h = 2 s + half of the run-wide
+// step s (one or both of its halves).
+__device__ __forceinline__ BathMap bath_map(const BathDev* __restrict__ C, int nt, int32_t sp,
+                                            double m, int64_t ion, int64_t h) {
+#pragma clang fp contract(off)
+    BathMap B;
+    for (int c = 0; c < nt; ++c) {
+        const BathDev T = C[c];
+        if (!T.on || (T.species >= 0 && T.species != sp)) continue;
+        const double sig = sqrt(T.kt / m * T.omc2);
+        double z0, z1, z2;
+        bath_normals(T.seed, ion, h >> 1, c, (int)(h & 1), z0, z1, z2);
+        B.nx = T.c1 * B.nx + sig * z0;
+        B.ny = T.c1 * B.ny + sig * z1;
+        B.nz = T.c1 * B.nz + sig * z2;
+        B.c = T.c1 * B.c;
+    }
+    return B;
+}
+
+// Its factor alone, without the draws.
+__device__ __forceinline__ double bath_factor(const BathDev* __restrict__ C, int nt, int32_t sp) {
+    double f = 1.0;
+    for (int c = 0; c < nt; ++c)
+        if (C[c].on && (C[c].species < 0 || C[c].species == sp)) f = C[c].c1 * f;
+    return f;
+}
+
 // The maps of a sequence of half-steps, filled by k_noise ahead of the kernels
 // that step the ions: draws depend on the seed, ion and step only, so they need
-// not sit on a step's dependent chain.
+// not sit on a step's dependent chain.  Where the handle has no memory for the table
+// (c is NULL) kernels built with kCoolDraw make the draws themselves, on lanes and waves
+// beside the owners' (us per step with a bath, a beam and a time average, table / kernel:
+// 8 ions 1.5 / 1.9, 100 ions 3.4 / 4.9, 1024 ions 5.3 / 7.4, 5000 ions 22.4 / 23.7,
+// FP32 pairs 16000 ions 81.2 / 81.0; on the owners' own chain 4.2, 7.0, 13.8, 28.4, 83.4).
 struct BathTable {
     const double* __restrict__ c;  // [stride] factor per ion
     const double* __restrict__ n;  // [half-steps][3][stride] kicks
     int64_t stride;
+    const double* __restrict__ mass;
     __device__ __forceinline__ BathMap load(const CoolRef& R, int64_t ion, int idx) const {
         BathMap m;
         if (R.nt > 0) {
@@ -308,6 +341,22 @@ struct BathTable {
             m.nz = p[2 * stride];
         }
         return m;
+    }
+};
+
+// Two half-steps that other waves of the workgroup draw for the owners of N ions, so that
+// the draws run side by side and beside the pair work or the slice sums.
+template <int N>
+struct DrawnMaps {
+    double v[2][4][N];
+    __device__ __forceinline__ void put(int which, int k, const BathMap& B) {
+        v[which][0][k] = B.c;
+        v[which][1][k] = B.nx;
+        v[which][2][k] = B.ny;
+        v[which][3][k] = B.nz;
+    }
+    __device__ __forceinline__ BathMap get(int which, int k) const {
+        return BathMap{v[which][0][k], v[which][1][k], v[which][2][k], v[which][3][k]};
     }
 };
 
@@ -338,9 +387,6 @@ __device__ __forceinline__ void velocity_half(const CoolRef& R, int32_t species,
 // idx = blockIdx.y (half-step 2 s + h is half h of the run-wide step s), one
 // thread per ion.  Bound by FP64 issue of log, sqrt, sin and cos and spread over
 // the whole chip: 100 ions x 400 half-steps take about as long as one launch.
-// With the draws inside the stepping kernels each step waited for two of them:
-// 100 ions, one bath, one beam and a time average 8.3 us a step against 3.6 now
-// (2.7 without cooling); 600 ions 11.0 against 7.2, 16000 ions 89 against 86.
 __global__ __launch_bounds__(256) void k_noise(const double* __restrict__ mass,
                                                const int32_t* __restrict__ species, int64_t n,
                                                int64_t stride, const CoolDev* __restrict__ C,
@@ -348,25 +394,10 @@ __global__ __launch_bounds__(256) void k_noise(const double* __restrict__ mass,
                                                int64_t g0,
                                                double* __restrict__ factor,
                                                double* __restrict__ kicks) {
-#pragma clang fp contract(off)
     const int64_t ion = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (ion >= n) return;
     const int64_t h = 2 * (C->step_base + (counter ? *counter : 0)) + g0 + blockIdx.y;
-    const int32_t sp = species[ion];
-    const double m = mass[ion];
-    const int nt = C->nbaths;
-    BathMap B;
-    for (int c = 0; c < nt; ++c) {
-        const BathDev T = C->baths[c];
-        if (!T.on || (T.species >= 0 && T.species != sp)) continue;
-        const double sig = sqrt(T.kt / m * T.omc2);
-        double z0, z1, z2;
-        bath_normals(T.seed, ion, h >> 1, c, (int)(h & 1), z0, z1, z2);
-        B.nx = T.c1 * B.nx + sig * z0;
-        B.ny = T.c1 * B.ny + sig * z1;
-        B.nz = T.c1 * B.nz + sig * z2;
-        B.c = T.c1 * B.c;
-    }
+    const BathMap B = bath_map(C->baths, C->nbaths, species[ion], mass[ion], ion, h);
     double* p = kicks + (int64_t)(3 * blockIdx.y) * stride + ion;
     p[0] = B.nx;
     p[stride] = B.ny;
@@ -452,7 +483,7 @@ __device__ __forceinline__ void end_kick(const TrapDev& T, const CoolRef& C, int
 
 // ------------------------------------------------------------------ kernels
 
-template <bool X>
+template <int X>
 __global__ __launch_bounds__(256) void k_drift(double4* __restrict__ src,
                                                MixedSrc* __restrict__ srcm,
                                                double* __restrict__ vx, double* __restrict__ vy,
@@ -464,6 +495,7 @@ __global__ __launch_bounds__(256) void k_drift(double4* __restrict__ src,
                                                const int32_t* __restrict__ species,
                                                const TrapDev* __restrict__ traps,
                                                const CoolDev* __restrict__ cool,
+                                               const int64_t* __restrict__ counter,
                                                const BathTable bath, int bath_idx,
                                                const int32_t* __restrict__ rb, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -473,8 +505,13 @@ __global__ __launch_bounds__(256) void k_drift(double4* __restrict__ src,
     const CoolRef cr = cool_switches<X>(cool);
     double4 p = src[i];
     double u = vx[i], v = vy[i], w = vz[i];
-    half_step_drift(T, cr, species[i], bath.load(cr, i, bath_idx), p.x, p.y, p.z, u, v, w, ax[i],
-                    ay[i], az[i]);
+    const int32_t sp = species[i];
+    BathMap b;
+    if constexpr (X == kCoolDraw)
+        b = bath_map(cool->baths, cr.nt, sp, bath.mass[i], i, 2 * (cool->step_base + *counter + 1));
+    else
+        b = bath.load(cr, i, bath_idx);
+    half_step_drift(T, cr, sp, b, p.x, p.y, p.z, u, v, w, ax[i], ay[i], az[i]);
     src[i] = p;
     vx[i] = u;
     vy[i] = v;
@@ -1525,7 +1562,7 @@ __device__ __forceinline__ IonIn load_ion(int64_t i, const double4* src_in,
 // kModeAccel stores the acceleration only.  kc is the call's step counter
 // after this step; b1 and b0 are the baths of this step's second half and of
 // the next step's first.
-template <bool X>
+template <int X>
 __device__ __forceinline__ void end_step_vals(
     int mode, int64_t i, int64_t kc, const TrapDev& T, double c, double Sx, double Sy,
     double Sz, IonIn in, const CoolRef& cr, const BathMap& b1, const BathMap& b0,
@@ -1542,7 +1579,7 @@ __device__ __forceinline__ void end_step_vals(
     if (mode == kModeAccel) return;
     double u = in.u, v = in.v, w = in.w;
     end_kick(T, cr, in.sp, b1, u, v, w, a_x, a_y, a_z);
-    if constexpr (X)  // of the step this epilogue completes
+    if constexpr (X != kCoolOff)  // of the step this epilogue completes
         time_average(cr, i, n_pad, cool->step_base + kc, vacc, vavg, u, v, w);
     if (mode == kModeEndDrift) {
         half_step_drift(T, cr, in.sp, b0, p.x, p.y, p.z, u, v, w, a_x, a_y, a_z);
@@ -1556,7 +1593,7 @@ __device__ __forceinline__ void end_step_vals(
 
 // As end_step_vals, loading the inputs first; rigid-body members (rb[i] >= 0)
 // only get their acceleration (their body kicks them).
-template <bool X>
+template <int X>
 __device__ __forceinline__ void end_step_ion(
     int mode, int64_t i, int64_t kc, const TrapDev& T, double t, double Sx, double Sy,
     double Sz, const double4* src_in, double4* src_out, MixedSrc* __restrict__ srcm_out,
@@ -1564,12 +1601,9 @@ __device__ __forceinline__ void end_step_ion(
     double* __restrict__ ax, double* __restrict__ ay, double* __restrict__ az,
     const double* __restrict__ qm, const double* __restrict__ qe,
     const int32_t* __restrict__ species, int64_t n_pad, const CoolDev* __restrict__ cool,
-    const BathTable& bath, int bath_idx, double* __restrict__ vacc, double* __restrict__ vavg,
-    const int32_t* __restrict__ rb) {
+    const CoolRef& cr, const BathMap& b1, const BathMap& b0, double* __restrict__ vacc,
+    double* __restrict__ vavg, const int32_t* __restrict__ rb) {
     const IonIn in = load_ion(i, src_in, vx, vy, vz, qm, qe, species);
-    const CoolRef cr = cool_switches<X>(cool);
-    const BathMap b1 = bath.load(cr, i, bath_idx);
-    const BathMap b0 = mode == kModeEndDrift ? bath.load(cr, i, bath_idx + 1) : BathMap{};
     const double c = T.ps != 0.0 ? 0.0 : cos(T.omega * t);
     const int m = (mode != kModeAccel && rb && rb[i] >= 0) ? kModeAccel : mode;
     end_step_vals<X>(m, i, kc, T, c, Sx, Sy, Sz, in, cr, b1, b0, src_out, srcm_out, vx, vy, vz,
@@ -1582,7 +1616,7 @@ __device__ __forceinline__ void end_step_ion(
 // ions with 4 waves: wave g adds the partial slots [g*per, (g+1)*per) in slot
 // order, wave 0 adds the four group sums in group order (deterministic for a
 // given number of slots), then applies the trap field and kick / damp / drift.
-template <int MODE, int UW, bool X, typename PT = double>
+template <int MODE, int UW, int X, typename PT = double>
 __global__ __launch_bounds__(64 * UW) void k_update(double4* __restrict__ src,
                                                 MixedSrc* __restrict__ srcm,
                                                 double* __restrict__ vx, double* __restrict__ vy,
@@ -1622,6 +1656,14 @@ __global__ __launch_bounds__(64 * UW) void k_update(double4* __restrict__ src,
         red[g - 1][1][lane] = Sy;
         red[g - 1][2][lane] = Sz;
     }
+    const CoolRef cr = cool_switches<X>(cool);
+    __shared__ DrawnMaps<X == kCoolDraw ? 64 : 1> drawn;
+    if constexpr (X == kCoolDraw) {
+        // this step's second half by the second wave, the next step's first by the third
+        if (i < n && (g == 1 || (g == 2 && MODE == kModeEndDrift)))
+            drawn.put(g - 1, lane, bath_map(cool->baths, cr.nt, species[i], bath.mass[i], i,
+                                            2 * (cool->step_base + (counter ? *counter : 0)) + g));
+    }
     __syncthreads();
     if (g > 0 || i >= n) return;
 #pragma unroll
@@ -1632,9 +1674,17 @@ __global__ __launch_bounds__(64 * UW) void k_update(double4* __restrict__ src,
     }
     const TrapDev T = traps[0];
     const double t = counter ? T.t_start + (double)(*counter) * T.dt : T.t_start;
+    BathMap b1, b0;
+    if constexpr (X == kCoolDraw) {
+        b1 = drawn.get(0, lane);
+        if (MODE == kModeEndDrift) b0 = drawn.get(1, lane);
+    } else {
+        b1 = bath.load(cr, i, bath_idx);
+        if (MODE == kModeEndDrift) b0 = bath.load(cr, i, bath_idx + 1);
+    }
     end_step_ion<X>(MODE, i, counter ? *counter : 0, T, t, Sx * field_scale, Sy * field_scale,
                     Sz * field_scale, src, src, srcm, vx, vy, vz, ax, ay, az, qm, qe, species,
-                    n_pad, cool, bath, bath_idx, vacc, vavg, rb);
+                    n_pad, cool, cr, b1, b0, vacc, vavg, rb);
 }
 
 // ---------------------------------------------- one launch per step (mid-size traps)
@@ -1664,7 +1714,7 @@ struct RowsArgs {
     int64_t n, n_pad;
 };
 
-template <int PREC, int TR, bool X>
+template <int PREC, int TR, int X>
 __global__ __launch_bounds__(kRowsBlock) void k_rows(const RowsArgs A, int mode, int k_in_chunk,
                                                      int bath_idx) {
     __shared__ double red[kRowsBlock / 64][3 * TR];
@@ -1682,7 +1732,16 @@ __global__ __launch_bounds__(kRowsBlock) void k_rows(const RowsArgs A, int mode,
         me = load_ion(i0 + tid, A.src_in, A.vx, A.vy, A.vz, A.qm, A.qe, A.species);
     const CoolRef cr = cool_switches<X>(A.cool);
     BathMap b1, b0;
-    if (own && counted) {
+    __shared__ DrawnMaps<X == kCoolDraw ? TR : 1> drawn;
+    if constexpr (X == kCoolDraw) {
+        // this step's second half by the second wave, the next step's first by the third
+        const int which = (tid >> 6) - 1, k = tid & 63;
+        if (counted && k < TR && i0 + k < n &&
+            (which == 0 || (which == 1 && mode == kModeEndDrift)))
+            drawn.put(which, k, bath_map(A.cool->baths, cr.nt, A.species[i0 + k],
+                                         A.bath.mass[i0 + k], i0 + k,
+                                         2 * (A.cool->step_base + kc) + 1 + which));
+    } else if (own && counted) {
         b1 = A.bath.load(cr, i0 + tid, bath_idx);
         if (mode == kModeEndDrift) b0 = A.bath.load(cr, i0 + tid, bath_idx + 1);
     }
@@ -1788,6 +1847,10 @@ __global__ __launch_bounds__(kRowsBlock) void k_rows(const RowsArgs A, int mode,
         Sx += red[w][3 * k];
         Sy += red[w][3 * k + 1];
         Sz += red[w][3 * k + 2];
+    }
+    if constexpr (X == kCoolDraw) {
+        b1 = drawn.get(0, k);
+        b0 = drawn.get(1, k);  // read with kModeEndDrift only
     }
     const double fs = PREC == 0 ? 1.0 : kMixedFieldScale;
     const int64_t i = i0 + k;
@@ -2027,6 +2090,38 @@ struct LoneTrap {
     TrapDev T;
     int on;
 };
+
+// Steps whose bath kicks a workgroup draws at a time for a trap of m ions: as many as its
+// LDS array of 3 cap doubles holds, at most 16.  A draw is some 750 instructions, half of
+// them FP64, in one dependent chain: one draw per thread fills the issue slots as well as a
+// batch allows.
+__device__ __forceinline__ int kick_steps(int cap, int m) { return min(cap / (2 * m), 16); }
+
+// The kicks of the half-steps h0 .. h0 + half_steps of the ions [o, o + m) into
+// kicks[half-step][3][m], spread over the workgroup's `threads` threads.
+__device__ __forceinline__ void draw_kicks(const CoolDev* __restrict__ C, int nt,
+                                           const int32_t* __restrict__ species,
+                                           const double* __restrict__ mass, int64_t o, int m,
+                                           int64_t h0, int half_steps, double* kicks,
+                                           int threads) {
+    for (int q = threadIdx.x; q < half_steps * m; q += threads) {
+        const int h = q / m, il = q - h * m;
+        const BathMap B = bath_map(C->baths, nt, species[o + il], mass[o + il], o + il, h0 + h);
+        double* p = kicks + 3 * h * m + il;
+        p[0] = B.nx;
+        p[m] = B.ny;
+        p[2 * m] = B.nz;
+    }
+}
+
+__device__ __forceinline__ void load_kick(const double* kicks, int m, int h, int il, int nt,
+                                          BathMap& B) {
+    if (nt == 0) return;
+    const double* p = kicks + 3 * h * m + il;
+    B.nx = p[0];
+    B.ny = p[m];
+    B.nz = p[2 * m];
+}
 
 // ------------------------------------------------------------ batched traps
 //
@@ -2290,7 +2385,7 @@ __device__ __forceinline__ void batch_pairs_multi(const typename BatchSrc<PREC>:
     }
 }
 
-template <int PREC, int BLOCK, bool X>
+template <int PREC, int BLOCK, int X>
 __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
                                                  double* __restrict__ vx,
                                                  double* __restrict__ vy,
@@ -2309,7 +2404,8 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
                                                  int64_t k0, double* __restrict__ vacc,
                                                  double* __restrict__ vavg, int64_t n_pad,
                                                  int nsteps, int accel_only, double uq,
-                                                 int tpt_req, const LoneTrap lone) {
+                                                 int tpt_req, const LoneTrap lone,
+                                                 int max_trap, int kick_cap) {
     // ions per owner thread at most (a 64-thread block takes traps of <= 64 ions only)
     constexpr int KMAX = BLOCK >= 256 ? kMaxTrap / BLOCK : 1;
     // pair work of larger traps: TPT targets per thread read each source once
@@ -2379,9 +2475,21 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
     double q_m[KMAX], q_e[KMAX];
     int32_t sp[KMAX];
     // with cooling: the beams and each owner's velocity sums of the open averaging
-    // window in LDS, the baths of the next half-step loaded ahead of it
+    // window in LDS, the baths of the next half-step from the table ahead of it or drawn
+    // into LDS for `ahead` steps at a time; those builds keep sums and kicks behind the
+    // source stream, sized by the largest trap (a lone trap of 100 ions, which reads the
+    // table, steps in 3.37 us with the sums in an array of their own and in 3.51 there)
     __shared__ BeamDev beams[X ? kMaxBeams : 1];
-    __shared__ double sums[X ? 3 : 1][X ? KMAX * BLOCK : 1];
+    __shared__ double own_sums[X == kCoolTable ? 3 : 1][X == kCoolTable ? KMAX * BLOCK : 1];
+    double* const sums = reinterpret_cast<double*>(lds_stream + max_trap);
+    double* const kicks = sums + 3 * max_trap;
+    auto sum_of = [&](int c, int k, int il) -> double& {
+        if constexpr (X == kCoolTable)
+            return own_sums[c][k * BLOCK + tid];
+        else
+            return sums[c * m + il];
+    };
+    const int ahead = X == kCoolDraw ? kick_steps(kick_cap, m) : 1;
     BathMap bath_next[X ? KMAX : 1];
     CoolRef cr = cool_switches<X>(cool);
     if constexpr (X) {
@@ -2408,8 +2516,11 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
             sp[k] = species[o + il];
             if constexpr (X) {
                 if (cr.W > 0)
-                    for (int c = 0; c < 3; ++c) sums[c][k * BLOCK + tid] = vacc[c * n_pad + o + il];
-                if (!accel_only) bath_next[k] = bath.load(cr, o + il, 0);
+                    for (int c = 0; c < 3; ++c) sum_of(c, k, il) = vacc[c * n_pad + o + il];
+                if constexpr (X == kCoolDraw)
+                    bath_next[k].c = bath_factor(cool->baths, cr.nt, sp[k]);
+                else if (!accel_only)
+                    bath_next[k] = bath.load(cr, o + il, 0);
             }
         } else {
             x[k] = y[k] = z[k] = u[k] = v[k] = w[k] = a0[k] = a1[k] = a2[k] = 0.0;
@@ -2431,15 +2542,27 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
             const double tq = T.t_start + (double)(k0 + sq + (accel_only ? 0 : 1)) * T.dt;
             rf[(step / kRf) & 1][tid] = cos(T.omega * tq);
         }
+        if constexpr (X == kCoolDraw) {
+            if (cr.nt > 0 && !accel_only && step % ahead == 0) {
+                __syncthreads();  // the owners are past the kicks of the steps before
+                draw_kicks(cool, cr.nt, species, bath.mass, o, m,
+                           2 * (cool->step_base + k0 + step + 1), 2 * min(ahead, total - step),
+                           kicks, BLOCK);
+                __syncthreads();
+            }
+        }
         // first half of the step; positions into the LDS source stream
 #pragma unroll
         for (int k = 0; k < KMAX; ++k) {
             const int il = slot + IS * k;
             if (owner && il < m) {
                 if (!accel_only) {
+                    if constexpr (X == kCoolDraw)
+                        load_kick(kicks, m, 2 * (step % ahead), il, cr.nt, bath_next[k]);
                     half_step_drift(T, cr, sp[k], bath_next[X ? k : 0], x[k], y[k], z[k], u[k],
                                     v[k], w[k], a0[k], a1[k], a2[k]);
-                    if constexpr (X) bath_next[k] = bath.load(cr, o + il, 2 * step + 1);
+                    if constexpr (X == kCoolTable)
+                        bath_next[k] = bath.load(cr, o + il, 2 * step + 1);
                 }
                 if constexpr (PREC == 0) {
                     lds[il] = make_double4(x[k], y[k], z[k], 1.5 * q_e[k]);
@@ -2540,15 +2663,19 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
                 trap_accel_c(T, crf, q_m[k], x[k], y[k], z[k], Sx[k], Sy[k], Sz[k], a0[k],
                              a1[k], a2[k]);
                 if (!accel_only) {
+                    if constexpr (X == kCoolDraw)
+                        load_kick(kicks, m, 2 * (step % ahead) + 1, il, cr.nt, bath_next[k]);
                     end_kick(T, cr, sp[k], bath_next[X ? k : 0], u[k], v[k], w[k], a0[k],
                              a1[k], a2[k]);
-                    if constexpr (X) {
+                    if constexpr (X == kCoolTable) {
                         if (step + 1 < total)
                             bath_next[k] = bath.load(cr, o + il, 2 * step + 2);
-                        const int at = k * BLOCK + tid;
+                    }
+                    if constexpr (X != kCoolOff) {
                         if (cr.W > 0)
                             window_add(cr, in_window + 1 == cr.W, o + il, n_pad, vavg, u[k],
-                                       v[k], w[k], sums[0][at], sums[1][at], sums[2][at]);
+                                       v[k], w[k], sum_of(0, k, il), sum_of(1, k, il),
+                                       sum_of(2, k, il));
                     }
                 }
             }
@@ -2568,7 +2695,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
             az[o + il] = a2[k];
             if constexpr (X) {
                 if (cr.W > 0 && !accel_only)
-                    for (int c = 0; c < 3; ++c) vacc[c * n_pad + o + il] = sums[c][k * BLOCK + tid];
+                    for (int c = 0; c < 3; ++c) vacc[c * n_pad + o + il] = sum_of(c, k, il);
             }
         }
     }
@@ -2588,7 +2715,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch(double4* __restrict__ src,
 // sums the sources p, p + P, ... in order, the parts are added by the
 // butterfly.
 
-template <int PREC, int P, int W, bool X, int U>
+template <int PREC, int P, int W, int X, int U>
 __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
                                              double* __restrict__ vx, double* __restrict__ vy,
                                              double* __restrict__ vz, double* __restrict__ ax,
@@ -2604,7 +2731,7 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
                                              int64_t k0, double* __restrict__ vacc,
                                              double* __restrict__ vavg, int64_t n_pad,
                                              int nsteps, int accel_only,
-                                             const LoneTrap lone) {
+                                             const LoneTrap lone, int kick_cap) {
     using S = typename BatchSrc<PREC>::T;
     constexpr int kSlots = 64 * W / P;  // targets per workgroup
     __shared__ S lds[kSlots];
@@ -2617,8 +2744,12 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
     const int ti = lane / P, part = lane - ti * P;
     const bool owner = part == 0 && ti < m;
     const TrapDev T = lone.on ? lone.T : traps[tr];
-    // with cooling: the beams in LDS, the baths of the next half-step loaded ahead
+    // with cooling: the beams in LDS, the baths of the next half-step from the table ahead
+    // of it or drawn into LDS for `ahead` steps at a time
     __shared__ BeamDev beams[X ? kMaxBeams : 1];
+    extern __shared__ double4 lds_stream[];
+    double* const kicks = reinterpret_cast<double*>(lds_stream);
+    const int ahead = X == kCoolDraw ? kick_steps(kick_cap, m) : 1;
     CoolRef cr = cool_switches<X>(cool);
     if constexpr (X) {
         if (lane < cr.nb) beams[lane] = cr.beams[lane];
@@ -2653,7 +2784,10 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
                 sum1 = vacc[n_pad + ion];
                 sum2 = vacc[2 * n_pad + ion];
             }
-            if (!accel_only) bath_next = bath.load(cr, ion, 0);
+            if constexpr (X == kCoolDraw)
+                bath_next.c = bath_factor(cool->baths, cr.nt, sp);
+            else if (!accel_only)
+                bath_next = bath.load(cr, ion, 0);
         }
     }
     const int total = accel_only ? 1 : nsteps;
@@ -2663,10 +2797,20 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
                 T.t_start + (double)(k0 + step + lane + (accel_only ? 0 : 1)) * T.dt;
             rf[(step / kRf) & 1][lane] = cos(T.omega * tq);
         }
+        if constexpr (X == kCoolDraw) {
+            if (cr.nt > 0 && !accel_only && step % ahead == 0) {
+                draw_kicks(cool, cr.nt, species, bath.mass, o, m,
+                           2 * (cool->step_base + k0 + step + 1), 2 * min(ahead, total - step),
+                           kicks, 64 * W);
+                __syncthreads();
+            }
+        }
         if (owner) {
             if (!accel_only) {
+                if constexpr (X == kCoolDraw)
+                    load_kick(kicks, m, 2 * (step % ahead), ti, cr.nt, bath_next);
                 half_step_drift(T, cr, sp, bath_next, x, y, z, u, v, w, a0, a1, a2);
-                if constexpr (X) bath_next = bath.load(cr, ion, 2 * step + 1);
+                if constexpr (X == kCoolTable) bath_next = bath.load(cr, ion, 2 * step + 1);
             }
             if constexpr (PREC == 0) {
                 lds[ti] = make_double4(x, y, z, 1.5 * q_e);
@@ -2751,9 +2895,13 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
             const double crf = T.ps == 0.0 ? rf[(step / kRf) & 1][step % kRf] : 0.0;
             trap_accel_c(T, crf, q_m, x, y, z, Sx, Sy, Sz, a0, a1, a2);
             if (!accel_only) {
+                if constexpr (X == kCoolDraw)
+                    load_kick(kicks, m, 2 * (step % ahead) + 1, ti, cr.nt, bath_next);
                 end_kick(T, cr, sp, bath_next, u, v, w, a0, a1, a2);
-                if constexpr (X) {
+                if constexpr (X == kCoolTable) {
                     if (step + 1 < total) bath_next = bath.load(cr, ion, 2 * step + 2);
+                }
+                if constexpr (X != kCoolOff) {
                     if (cr.W > 0)
                         window_add(cr, in_window + 1 == cr.W, ion, n_pad, vavg, u, v, w, sum0,
                                    sum1, sum2);
@@ -3020,7 +3168,7 @@ __global__ __launch_bounds__(256) void k_rigid_wrench(RigidDev* __restrict__ bod
         vx[i] = u;
         vy[i] = v;
         vz[i] = w;
-        time_average(cool_switches<true>(cool), i, n_pad, step, vacc, vavg, u, v, w);
+        time_average(cool_switches<kCoolTable>(cool), i, n_pad, step, vacc, vavg, u, v, w);
     }
 }
 
@@ -3667,7 +3815,7 @@ __global__ __launch_bounds__(kHessBlock) void k_hessian(const double4* __restric
 inline unsigned blocks_for(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 inline BathTable bath_table(const DevState& s) {
-    return BathTable{s.noise_c, s.noise, s.noise_stride};
+    return BathTable{s.noise_c, s.noise, s.noise_stride, s.mass};
 }
 
 inline int n64_of(int64_t n) { return (int)((n + 63) & ~int64_t(63)); }
@@ -3712,26 +3860,37 @@ hipError_t pair_mixed_dispatch_l(const DevState& s, const LaunchShape& ls, int64
     }
 }
 
-template <int PREC, int BLOCK, bool X>
+// Ion half-steps of kicks that a workgroup of `block` threads draws at a time: one round of
+// its threads for the largest trap, at least one step and at most what LDS has room for.
+inline int kick_cap(int max_trap, int block) {
+    const int steps = std::max(1, std::min(16, block / (2 * max_trap)));
+    return 2 * steps * max_trap;
+}
+
+template <int PREC, int BLOCK, int X>
 hipError_t batch_launch(const DevState& s, int n_traps, int max_trap, int nsteps,
                         int accel_only, int64_t k0, const LoneTrap& lone, double uq, int tpt, hipStream_t st) {
-    const size_t stream_bytes = (size_t)max_trap * sizeof(double4);
-    k_batch<PREC, BLOCK, X><<<n_traps, BLOCK, stream_bytes, st>>>(s.src, s.vx, s.vy, s.vz, s.ax, s.ay,
+    const int cap = X == kCoolDraw ? kick_cap(max_trap, BLOCK) : 0;
+    const size_t lds = (size_t)max_trap * sizeof(double4) +
+                       (X == kCoolDraw ? (size_t)(max_trap + cap) * 3 * sizeof(double) : 0);
+    k_batch<PREC, BLOCK, X><<<n_traps, BLOCK, lds, st>>>(s.src, s.vx, s.vy, s.vz, s.ax, s.ay,
                                                        s.az, s.qm, s.qe, s.species, s.traps,
                                                        s.cool, bath_table(s), s.offsets, s.order,
                                                        k0, s.vacc, s.vavg, s.n_pad,
-                                                       nsteps, accel_only, uq, tpt, lone);
+                                                       nsteps, accel_only, uq, tpt, lone,
+                                                       max_trap, cap);
     return hipGetLastError();
 }
 
-template <int PREC, int P, int W, bool X, int U = 1>
-hipError_t wave_launch_p(const DevState& s, int n_traps, int nsteps, int accel_only, int64_t k0,
+template <int PREC, int P, int W, int X, int U = 1>
+hipError_t wave_launch_p(const DevState& s, int n_traps, int max_trap, int nsteps, int accel_only, int64_t k0,
                          const LoneTrap& lone, hipStream_t st) {
-    k_wave<PREC, P, W, X, U><<<n_traps, 64 * W, 0, st>>>(s.src, s.vx, s.vy, s.vz, s.ax, s.ay, s.az,
+    const int cap = X == kCoolDraw ? kick_cap(max_trap, 64 * W) : 0;
+    k_wave<PREC, P, W, X, U><<<n_traps, 64 * W, (size_t)cap * 3 * sizeof(double), st>>>(s.src, s.vx, s.vy, s.vz, s.ax, s.ay, s.az,
                                                       s.qm, s.qe, s.species, s.traps, s.cool,
                                                       bath_table(s), s.offsets, s.order, k0,
                                                       s.vacc, s.vavg, s.n_pad, nsteps,
-                                                      accel_only, lone);
+                                                      accel_only, lone, cap);
     return hipGetLastError();
 }
 
@@ -3745,37 +3904,37 @@ inline int wave_parts(int max_trap) {
     return P;
 }
 
-template <int PREC, bool X>
+template <int PREC, int X>
 hipError_t wave_launch(const DevState& s, int n_traps, int max_trap, int nsteps, int accel_only,
                        int64_t k0, const LoneTrap& lone, hipStream_t st) {
     switch (wave_parts(max_trap)) {
-        case 8: return wave_launch_p<PREC, 8, 1, X>(s, n_traps, nsteps, accel_only, k0, lone, st);
+        case 8: return wave_launch_p<PREC, 8, 1, X>(s, n_traps, max_trap, nsteps, accel_only, k0, lone, st);
         case 4:
             // a part's sources together: all two of traps of <= 8 ions, four of larger ones
             // (us per step, one by one / together: 16 ions 0.69 / 0.59; on several waves,
             // three to six sources a part, 2 or 3 together measured 7 % slower to 2 % faster)
             if (max_trap <= 8)
-                return wave_launch_p<PREC, 4, 1, X, 2>(s, n_traps, nsteps, accel_only, k0, lone, st);
-            return wave_launch_p<PREC, 4, 1, X, 4>(s, n_traps, nsteps, accel_only, k0, lone, st);
-        case 2: return wave_launch_p<PREC, 2, 1, X>(s, n_traps, nsteps, accel_only, k0, lone, st);
-        default: return wave_launch_p<PREC, 1, 1, X>(s, n_traps, nsteps, accel_only, k0, lone, st);
+                return wave_launch_p<PREC, 4, 1, X, 2>(s, n_traps, max_trap, nsteps, accel_only, k0, lone, st);
+            return wave_launch_p<PREC, 4, 1, X, 4>(s, n_traps, max_trap, nsteps, accel_only, k0, lone, st);
+        case 2: return wave_launch_p<PREC, 2, 1, X>(s, n_traps, max_trap, nsteps, accel_only, k0, lone, st);
+        default: return wave_launch_p<PREC, 1, 1, X>(s, n_traps, max_trap, nsteps, accel_only, k0, lone, st);
     }
 }
 
 // The same kernel on block / 64 waves with 8 parts per target, for traps of at
 // most block / 8 ions (a target's parts stay within one wave).
 constexpr int kWaveMultiIons = 48;
-template <int PREC, bool X>
-hipError_t wave_launch_multi(const DevState& s, int n_traps, int block, int nsteps,
+template <int PREC, int X>
+hipError_t wave_launch_multi(const DevState& s, int n_traps, int max_trap, int block, int nsteps,
                              int accel_only, int64_t k0, const LoneTrap& lone, hipStream_t st) {
     switch (block) {
-        case 1024: return wave_launch_p<PREC, 8, 16, X>(s, n_traps, nsteps, accel_only, k0, lone, st);
-        case 512: return wave_launch_p<PREC, 8, 8, X>(s, n_traps, nsteps, accel_only, k0, lone, st);
-        default: return wave_launch_p<PREC, 8, 4, X>(s, n_traps, nsteps, accel_only, k0, lone, st);
+        case 1024: return wave_launch_p<PREC, 8, 16, X>(s, n_traps, max_trap, nsteps, accel_only, k0, lone, st);
+        case 512: return wave_launch_p<PREC, 8, 8, X>(s, n_traps, max_trap, nsteps, accel_only, k0, lone, st);
+        default: return wave_launch_p<PREC, 8, 4, X>(s, n_traps, max_trap, nsteps, accel_only, k0, lone, st);
     }
 }
 
-template <int PREC, bool X>
+template <int PREC, int X>
 hipError_t batch_dispatch_x(const DevState& s, int n_traps, int max_trap, int block, int nsteps,
                             int accel_only, int64_t k0, const LoneTrap& lone, double uq, int tpt, hipStream_t st) {
     // traps of at most 48 ions and block / 8: the wave kernel on block / 64 waves
@@ -3785,7 +3944,7 @@ hipError_t batch_dispatch_x(const DevState& s, int n_traps, int max_trap, int bl
     // ions 3.29 / 3.03 against 2.72 / 2.35, so larger traps keep the batched kernel;
     // measured before the part sums moved to DPP, which took 20 ions to 0.70)
     if (block != 64 && 8 * max_trap <= block && max_trap <= kWaveMultiIons)
-        return wave_launch_multi<PREC, X>(s, n_traps, block, nsteps, accel_only, k0, lone, st);
+        return wave_launch_multi<PREC, X>(s, n_traps, max_trap, block, nsteps, accel_only, k0, lone, st);
     switch (block) {
         case 64: return wave_launch<PREC, X>(s, n_traps, max_trap, nsteps, accel_only, k0, lone, st);
         case 512: return batch_launch<PREC, 512, X>(s, n_traps, max_trap, nsteps, accel_only, k0, lone, uq, tpt, st);
@@ -3796,22 +3955,27 @@ hipError_t batch_dispatch_x(const DevState& s, int n_traps, int max_trap, int bl
 
 template <int PREC>
 hipError_t batch_dispatch(const DevState& s, int n_traps, int max_trap, int block, int nsteps, int accel_only,
-                          int64_t k0, const LoneTrap& lone, bool cool_on, double uq, int tpt, hipStream_t st) {
-    return cool_on ? batch_dispatch_x<PREC, true>(s, n_traps, max_trap, block, nsteps, accel_only, k0, lone, uq, tpt, st)
-                   : batch_dispatch_x<PREC, false>(s, n_traps, max_trap, block, nsteps, accel_only, k0, lone, uq, tpt, st);
+                          int64_t k0, const LoneTrap& lone, CoolKind cool, double uq, int tpt, hipStream_t st) {
+    switch (cool) {
+        case kCoolOff: return batch_dispatch_x<PREC, kCoolOff>(s, n_traps, max_trap, block, nsteps, accel_only, k0, lone, uq, tpt, st);
+        case kCoolTable: return batch_dispatch_x<PREC, kCoolTable>(s, n_traps, max_trap, block, nsteps, accel_only, k0, lone, uq, tpt, st);
+        default: return batch_dispatch_x<PREC, kCoolDraw>(s, n_traps, max_trap, block, nsteps, accel_only, k0, lone, uq, tpt, st);
+    }
 }
 
 }  // namespace
 
-hipError_t launch_drift(const DevState& s, bool cool_on, int bath_idx, hipStream_t st) {
-    if (cool_on)
-        k_drift<true><<<blocks_for(s.n, 256), 256, 0, st>>>(
+hipError_t launch_drift(const DevState& s, CoolKind cool, int bath_idx, hipStream_t st) {
+    auto launch = [&](auto kernel) {
+        kernel<<<blocks_for(s.n, 256), 256, 0, st>>>(
             s.src, s.srcm, s.vx, s.vy, s.vz, s.ax, s.ay, s.az, s.qe, s.species, s.traps, s.cool,
-            bath_table(s), bath_idx, s.rb, s.n);
-    else
-        k_drift<false><<<blocks_for(s.n, 256), 256, 0, st>>>(
-            s.src, s.srcm, s.vx, s.vy, s.vz, s.ax, s.ay, s.az, s.qe, s.species, s.traps, s.cool,
-            bath_table(s), bath_idx, s.rb, s.n);
+            s.counter, bath_table(s), bath_idx, s.rb, s.n);
+    };
+    switch (cool) {
+        case kCoolOff: launch(k_drift<kCoolOff>); break;
+        case kCoolTable: launch(k_drift<kCoolTable>); break;
+        default: launch(k_drift<kCoolDraw>); break;
+    }
     return hipGetLastError();
 }
 
@@ -3951,16 +4115,17 @@ void update_launch(const DevState& s, const LaunchShape& ls, double scale, Mixed
                    const int64_t* ctr, int bath_idx, hipStream_t st) {
     const unsigned g = blocks_for(s.n, 64);  // 64 ions per block of UW waves
     const PT* part = reinterpret_cast<const PT*>(s.part);
-    if (ls.cool_on && MODE != kModeAccel)
-        k_update<MODE, UW, true, PT><<<g, 64 * UW, 0, st>>>(
+    auto launch = [&](auto kernel) {
+        kernel<<<g, 64 * UW, 0, st>>>(
             s.src, srcm, s.vx, s.vy, s.vz, s.ax, s.ay, s.az, s.qm, s.qe, s.species, part,
             ls.j_split, s.n, s.n_pad, scale, s.traps, s.cool, ctr, bath_table(s), bath_idx,
             s.vacc, s.vavg, s.rb);
-    else
-        k_update<MODE, UW, false, PT><<<g, 64 * UW, 0, st>>>(
-            s.src, srcm, s.vx, s.vy, s.vz, s.ax, s.ay, s.az, s.qm, s.qe, s.species, part,
-            ls.j_split, s.n, s.n_pad, scale, s.traps, s.cool, ctr, bath_table(s), bath_idx,
-            s.vacc, s.vavg, s.rb);
+    };
+    if constexpr (MODE != kModeAccel) {
+        if (ls.cool == kCoolTable) return launch(k_update<MODE, UW, kCoolTable, PT>);
+        if (ls.cool == kCoolDraw) return launch(k_update<MODE, UW, kCoolDraw, PT>);
+    }
+    launch(k_update<MODE, UW, kCoolOff, PT>);
 }
 
 template <int MODE, typename PT>
@@ -4132,9 +4297,9 @@ hipError_t launch_batch(const DevState& s, int precision, int n_traps, int max_t
                         hipStream_t st) {
     const LoneTrap lone{lone_trap ? *lone_trap : TrapDev{}, lone_trap ? 1 : 0};
     switch (precision) {
-        case 0: return batch_dispatch<0>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, k0, lone, ls.cool_on, ls.uniform_q, ls.batch_tpt, st);
-        case 2: return batch_dispatch<2>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, k0, lone, ls.cool_on, ls.uniform_q, ls.batch_tpt, st);
-        default: return batch_dispatch<1>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, k0, lone, ls.cool_on, ls.uniform_q, ls.batch_tpt, st);
+        case 0: return batch_dispatch<0>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, k0, lone, ls.cool, ls.uniform_q, ls.batch_tpt, st);
+        case 2: return batch_dispatch<2>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, k0, lone, ls.cool, ls.uniform_q, ls.batch_tpt, st);
+        default: return batch_dispatch<1>(s, n_traps, max_trap, ls.batch_block, nsteps, 0, k0, lone, ls.cool, ls.uniform_q, ls.batch_tpt, st);
     }
 }
 
@@ -4142,32 +4307,34 @@ hipError_t launch_batch_accel(const DevState& s, int precision, int n_traps, int
                               const LaunchShape& ls, const TrapDev* lone_trap, hipStream_t st) {
     const LoneTrap lone{lone_trap ? *lone_trap : TrapDev{}, lone_trap ? 1 : 0};
     switch (precision) {
-        case 0: return batch_dispatch<0>(s, n_traps, max_trap, ls.batch_block, 0, 1, 0, lone, false, ls.uniform_q, ls.batch_tpt, st);
-        case 2: return batch_dispatch<2>(s, n_traps, max_trap, ls.batch_block, 0, 1, 0, lone, false, ls.uniform_q, ls.batch_tpt, st);
-        default: return batch_dispatch<1>(s, n_traps, max_trap, ls.batch_block, 0, 1, 0, lone, false, ls.uniform_q, ls.batch_tpt, st);
+        case 0: return batch_dispatch<0>(s, n_traps, max_trap, ls.batch_block, 0, 1, 0, lone, kCoolOff, ls.uniform_q, ls.batch_tpt, st);
+        case 2: return batch_dispatch<2>(s, n_traps, max_trap, ls.batch_block, 0, 1, 0, lone, kCoolOff, ls.uniform_q, ls.batch_tpt, st);
+        default: return batch_dispatch<1>(s, n_traps, max_trap, ls.batch_block, 0, 1, 0, lone, kCoolOff, ls.uniform_q, ls.batch_tpt, st);
     }
 }
 
 namespace {
 
 template <int PREC, int TR>
-hipError_t rows_launch(const RowsArgs& A, bool cool_on, int mode, int k, int bath_idx,
+hipError_t rows_launch(const RowsArgs& A, CoolKind cool, int mode, int k, int bath_idx,
                        hipStream_t st) {
     const unsigned g = (unsigned)((A.n + TR - 1) / TR);
-    if (cool_on && mode != kModeAccel)
-        k_rows<PREC, TR, true><<<g, kRowsBlock, 0, st>>>(A, mode, k, bath_idx);
+    if (cool == kCoolOff || mode == kModeAccel)
+        k_rows<PREC, TR, kCoolOff><<<g, kRowsBlock, 0, st>>>(A, mode, k, 0);
+    else if (cool == kCoolTable)
+        k_rows<PREC, TR, kCoolTable><<<g, kRowsBlock, 0, st>>>(A, mode, k, bath_idx);
     else
-        k_rows<PREC, TR, false><<<g, kRowsBlock, 0, st>>>(A, mode, k, 0);
+        k_rows<PREC, TR, kCoolDraw><<<g, kRowsBlock, 0, st>>>(A, mode, k, bath_idx);
     return hipGetLastError();
 }
 
 template <int PREC>
-hipError_t rows_dispatch(const RowsArgs& A, int tr, bool cool_on, int mode, int k,
+hipError_t rows_dispatch(const RowsArgs& A, int tr, CoolKind cool, int mode, int k,
                          int bath_idx, hipStream_t st) {
     switch (tr) {
-        case 1: return rows_launch<PREC, 1>(A, cool_on, mode, k, bath_idx, st);
-        case 2: return rows_launch<PREC, 2>(A, cool_on, mode, k, bath_idx, st);
-        default: return rows_launch<PREC, 4>(A, cool_on, mode, k, bath_idx, st);
+        case 1: return rows_launch<PREC, 1>(A, cool, mode, k, bath_idx, st);
+        case 2: return rows_launch<PREC, 2>(A, cool, mode, k, bath_idx, st);
+        default: return rows_launch<PREC, 4>(A, cool, mode, k, bath_idx, st);
     }
 }
 
@@ -4201,9 +4368,9 @@ hipError_t launch_rows(const DevState& s, int precision, const LaunchShape& ls, 
     A.n = s.n;
     A.n_pad = s.n_pad;
     switch (precision) {
-        case 0: return rows_dispatch<0>(A, ls.rows_tr, ls.cool_on, mode, k_in_chunk, bath_idx, st);
-        case 2: return rows_dispatch<2>(A, ls.rows_tr, ls.cool_on, mode, k_in_chunk, bath_idx, st);
-        default: return rows_dispatch<1>(A, ls.rows_tr, ls.cool_on, mode, k_in_chunk, bath_idx, st);
+        case 0: return rows_dispatch<0>(A, ls.rows_tr, ls.cool, mode, k_in_chunk, bath_idx, st);
+        case 2: return rows_dispatch<2>(A, ls.rows_tr, ls.cool, mode, k_in_chunk, bath_idx, st);
+        default: return rows_dispatch<1>(A, ls.rows_tr, ls.cool, mode, k_in_chunk, bath_idx, st);
     }
 }
 

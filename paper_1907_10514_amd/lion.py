@@ -83,6 +83,7 @@ def load(path: str = LIB_PATH):
     lib.lion_set_rigid_bodies.argtypes = [vp, ctypes.POINTER(ctypes.c_int32)]
     lib.lion_get_rigid_state.argtypes = [vp, ctypes.POINTER(ctypes.c_int32), dp, dp, dp, dp]
     lib.lion_set_beam.argtypes = [vp, i32, i32, d, d, d, d]
+    lib.lion_set_bath_memory.argtypes = [vp, vp, sz]
     lib.lion_set_bath.argtypes = [vp, i32, i32, d, d, ctypes.c_uint64]
     lib.lion_set_step_index.argtypes = [vp, i64]
     lib.lion_get_step_index.argtypes = [vp]
@@ -115,7 +116,7 @@ def load(path: str = LIB_PATH):
                  "lion_get_rigid_state", "lion_set_pseudo_trap", "lion_minimize",
                  "lion_normal_modes",
                  "lion_set_species", "lion_set_beam",
-                 "lion_set_bath", "lion_set_step_index", "lion_set_time_average",
+                 "lion_set_bath", "lion_set_bath_memory", "lion_set_step_index", "lion_set_time_average",
                  "lion_get_time_average", "lion_step", "lion_step_batch", "lion_prepare_step",
                  "lion_get_state",
                  "lion_compute_accel", "lion_get_energy", "lion_check_finite", "lion_count_lost",
@@ -260,6 +261,20 @@ def lion_set_beam(h, beam, species, kx, ky, kz, gamma):
 def lion_set_bath(h, bath, species, temperature, damping_time, seed):
     _check(load().lion_set_bath(h, int(bath), int(species), float(temperature),
                                 float(damping_time), int(seed) & 0xffffffffffffffff), h)
+
+
+def lion_set_bath_memory(h, ptr, nbytes):
+    _check(load().lion_set_bath_memory(h, ctypes.c_void_p(ptr), int(nbytes)), h)
+
+
+def bath_memory_bytes(n: int, batched: bool) -> int:
+    """Device memory that makes the baths of n ions fast (lion_set_bath_memory; 0: none
+    does): 400 half-steps within 16 MB, or within 48 MB for a batch, whose launches end where
+    the table does."""
+    row = 8 * ((int(n) + 63) // 64 * 64)
+    most, least = (48 << 20 if batched else 16 << 20), 3
+    half_steps = min(400, (most - row) // (3 * row))
+    return row * (1 + 3 * half_steps) if half_steps >= least else 0
 
 
 def lion_set_step_index(h, steps_done):
@@ -417,6 +432,7 @@ class Simulation:
             else:
                 self.h = lion_create(self.n, m, q, self.precision, ptr, ws, sptr)
         self.ws_bytes = ws
+        self._bath_memory = None  # for draws ahead of the steps, once a bath is on
         self.tuned = None
         if autotuned:
             from . import tune
@@ -489,6 +505,12 @@ class Simulation:
 
     def set_bath(self, bath, temperature, damping_time, seed, species=-1):
         lion_set_bath(self.h, bath, species, temperature, damping_time, seed)
+        if damping_time > 0.0 and self._bath_memory is None:
+            nb = bath_memory_bytes(self.n, self.batched)
+            with self.torch.cuda.device(self.device), self.torch.cuda.stream(self.stream):
+                self._bath_memory = self.torch.empty(nb + 256, dtype=self.torch.uint8,
+                                                     device=self.device)
+            lion_set_bath_memory(self.h, (self._bath_memory.data_ptr() + 255) // 256 * 256, nb)
 
     def set_step_index(self, steps_done):
         lion_set_step_index(self.h, steps_done)
