@@ -197,7 +197,7 @@ int lion_set_bath(lion_sim *sim, int32_t bath, int32_t species, double temperatu
  * call of this) lets all of the chip make the draws of many half-steps ahead of
  * the steps: 24 bytes per ion and half-step and 8 per ion, ions rounded up to
  * 64, at most 1024 half-steps.  Results do not change.  Without it (the default,
- * or NULL), or where it holds fewer than 3 half-steps, the
+ * or NULL), or where it holds fewer than 3 half-steps (32 for a batch), the
  * stepping kernels draw for themselves, which is slower for single traps and for
  * batches of up to about 50000 ions.  Synchronises; drops captured launch
  * graphs.  Misaligned -> LION_ERR_WORKSPACE. */

@@ -101,13 +101,18 @@ int slices_for(int64_t n) {
 }
 
 // Table of bath kicks drawn ahead of the steps, in memory that lion_set_bath_memory was
-// given: as many half-steps as fit, at most 1024, at least the three that the start and the
-// first step of a chunk take.
+// given: as many half-steps as fit, at most 1024.  Single traps take it from three on (the
+// start and the first step of a chunk).  A batch, whose launch ends where the table does,
+// takes it from kBatchTableHalfSteps on and else draws in its kernel (FP64, us per step
+// with a bath, a beam and a time average, table of h half-steps / kernel: 512 traps of 40
+// ions, h = 102, 5.7 / 7.0; 512 of 100, h = 40, 11.9 / 13.6; 512 of 256, h = 16, 32.9 /
+// 30.7; 52429 of 20, h = 3, 306 / 208; 16384 of 64, h = 3, 462 / 267).
+constexpr size_t kBatchTableHalfSteps = 32;
 int64_t noise_stride_for(int64_t n) { return round_up(n, 64); }
-int noise_half_steps(int64_t n, size_t bytes) {
+int noise_half_steps(int64_t n, bool batched, size_t bytes) {
     const size_t row = noise_stride_for(n) * sizeof(double);
     const size_t h = bytes < row ? 0 : std::min<size_t>((bytes - row) / (3 * row), 1024);
-    return h < 3 ? 0 : (int)h;
+    return h < (batched ? kBatchTableHalfSteps : 3) ? 0 : (int)h;
 }
 
 struct Layout {
@@ -1248,7 +1253,7 @@ int lion_set_bath_memory(lion_sim* s, void* dev_memory, size_t bytes) {
     LION_HIP(s, hipStreamSynchronize(s->stream));  // no launch with the old memory pending
     clear_graphs(s);
     DevState& d = s->d;
-    d.noise_h = dev_memory ? noise_half_steps(s->n, bytes) : 0;
+    d.noise_h = dev_memory ? noise_half_steps(s->n, s->batched, bytes) : 0;
     d.noise_c = d.noise_h ? (double*)dev_memory : nullptr;
     d.noise = d.noise_h ? d.noise_c + d.noise_stride : nullptr;
     return LION_OK;

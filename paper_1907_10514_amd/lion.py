@@ -272,7 +272,7 @@ def bath_memory_bytes(n: int, batched: bool) -> int:
     does): 400 half-steps within 16 MB, or within 48 MB for a batch, whose launches end where
     the table does."""
     row = 8 * ((int(n) + 63) // 64 * 64)
-    most, least = (48 << 20 if batched else 16 << 20), 3
+    most, least = (48 << 20, 32) if batched else (16 << 20, 3)
     half_steps = min(400, (most - row) // (3 * row))
     return row * (1 + 3 * half_steps) if half_steps >= least else 0
 

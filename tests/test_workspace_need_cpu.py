@@ -22,6 +22,6 @@ def test_need_does_not_grow(n, traps, need):
 @pytest.mark.parametrize("n", [1, 64, 65, 1024, 16384, 65536, 109226, 131072, 10 ** 7])
 def test_bath_memory_is_useful_or_none(n, batched):
     extra, row = lion.bath_memory_bytes(n, batched), 8 * ((n + 63) // 64 * 64)
-    least, most = 10 * row, 48 << 20 if batched else 16 << 20
+    least, most = ((1 + 3 * 32) * row, 48 << 20) if batched else (10 * row, 16 << 20)
     assert extra == 0 or least <= extra <= most
     assert extra > 0 or least > most
