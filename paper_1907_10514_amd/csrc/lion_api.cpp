@@ -493,6 +493,13 @@ int64_t chunk_len(const lion_sim* s) {
     return one_wg ? kChunkLong : kChunkDefault;
 }
 
+// Accelerations at the current positions by the pair kernel and its epilogue.
+int pair_accel(lion_sim* s) {
+    LION_HIP(s, lion::launch_pair(s->d, s->precision, s->ls, false, s->stream));
+    LION_HIP(s, lion::launch_update(s->d, s->precision, s->ls, lion::kModeAccel, false, 0, s->stream));
+    return LION_OK;
+}
+
 // Accelerations at the current positions and clocks, by the kernels that step
 // the handle (so a trap stepped inside one workgroup gets them from that kernel).
 int refresh_accel(lion_sim* s) {
@@ -510,9 +517,7 @@ int refresh_accel(lion_sim* s) {
                                       0, s->stream));
         return LION_OK;
     }
-    LION_HIP(s, lion::launch_pair(s->d, s->precision, s->ls, false, s->stream));
-    LION_HIP(s, lion::launch_update(s->d, s->precision, s->ls, lion::kModeAccel, false, 0, s->stream));
-    return LION_OK;
+    return pair_accel(s);
 }
 
 // Traps that step inside one workgroup each: a chunk is one launch (and the bath
@@ -1532,7 +1537,11 @@ int lion_minimize(lion_sim* s, double dt, double dmax, double ftol, int64_t max_
     if (rows) {
         LION_HIP(s, lion::launch_min_rows(s->d, s->precision, 0, false, st));
     } else {
-        rc = refresh_accel(s);  // forces at the current positions, trap clock fixed
+        // forces at the current positions by the kernels of the iterations, whatever steps
+        // the handle, so that a call goes on exactly where the last one stopped
+        s->traps[0].t_start = s->t_now[0];
+        rc = begin_call(s);
+        if (rc == LION_OK) rc = pair_accel(s);
         if (rc) return rc;
     }
     for (;;) {
