@@ -17,10 +17,10 @@ namespace lion {
 namespace {
 
 // Reflector of a column x (entries below the diagonal; x0 the first, sigma the sum of
-// squares of the others): (I - beta v v^T) x = alpha e1 with v = x but v0 first.  A
-// column whose squares add up to less than kTinySquare is taken as zero below x0: beta
-// would leave the range of a double, and against a matrix of norm kNormMin or more, the
-// least that k_bisect accepts, what is left out is below 2^-150.
+// squares of the others): (I - beta v v^T) x = alpha e1 with v = x but v0 first.  Others
+// whose squares add up to less than kTinySquare are taken as zero: beta could leave the
+// range of a double, and against a matrix of norm kNormMin or more, the least that
+// k_bisect accepts, what is left out is below 2^-150.
 constexpr double kTinySquare = 0x1p-900, kNormMin = 0x1p-300, kNormMax = 0x1p+500;
 struct Reflector {
     double beta, alpha, v0;
@@ -28,13 +28,13 @@ struct Reflector {
 
 __device__ __forceinline__ Reflector reflector(double x0, double sigma) {
     Reflector h;
-    const double s = fma(x0, x0, sigma);
-    if (sigma == 0.0 || s < kTinySquare) {
+    if (sigma < kTinySquare) {
         h.beta = 0.0;
         h.alpha = x0;
         h.v0 = 0.0;
     } else {
         // the hardware's seeds with a cubic step each: every wave runs this chain
+        const double s = fma(x0, x0, sigma);
         const double y0 = __builtin_amdgcn_rsq(s);
         const double e = fma(-(s * y0), y0, 1.0);
         const double y = fma(y0 * e, fma(e, 0.375, 0.5), y0);
