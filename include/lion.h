@@ -249,7 +249,10 @@ int lion_set_pseudo_trap(lion_sim *sim, int32_t trap, double V_rf, double Omega_
  * LION_ERR_UNSUPPORTED, as are batched handles and rigid bodies.  State not
  * set -> LION_ERR_STATE; dt, dmax <= 0, ftol < 0, max_iter < 0 or non-finite
  * -> LION_ERR_ARG.  *iterations (optional) gets the iterations that moved the
- * ions, *fmax_N (optional) the largest |F_i| at the final positions. */
+ * ions, *fmax_N (optional) the largest |F_i| at the final positions.  Up to 2048
+ * ions without body exclusion it runs in kernels of its own (one workgroup up to
+ * 160 ions, one launch per iteration above), on which lion_set_kernel_config has
+ * no say beyond use_graph; else with the handle's pair kernel and epilogue. */
 int lion_minimize(lion_sim *sim, double dt, double dmax_m, double ftol_N, int64_t max_iter,
                   int64_t *iterations, double *fmax_N);
 
@@ -285,8 +288,9 @@ int lion_normal_modes(lion_sim *sim, void *dev_work, size_t bytes, double *omega
  * motion for N steps of the set time step; section "Integration": velocity
  * Verlet; the step is written out at the top of this header).  nsteps = 0 is
  * a no-op.  Time afterwards: t + nsteps dt; within the call
- * t_k = t_call_start + k dt.  Runs as captured launch graphs of
- * lion_kernel_config.chunk_steps steps; returns once they are queued.
+ * t_k = t_call_start + k dt.  Runs in chunks of lion_kernel_config.chunk_steps
+ * steps, captured launch graphs for a single trap on several workgroups, else
+ * one launch each; returns once they are queued.
  * Requires lion_set_state first (else LION_ERR_STATE); nsteps < 0 or a bad
  * dt -> LION_ERR_ARG. */
 int lion_step(lion_sim *sim, int64_t nsteps, double dt);
@@ -300,7 +304,8 @@ int lion_step_batch(lion_sim *sim, int64_t nsteps, const double *dt_per_trap);
  * instantiation out of a timed or latency-critical region.  The graphs hold
  * the current launch shape and cooling switches; a later change of either
  * drops them (they are then captured again on use).  nsteps < 0 ->
- * LION_ERR_ARG; nsteps = 0 or plain launches (use_graph = 2) do nothing. */
+ * LION_ERR_ARG; nsteps = 0, plain launches (use_graph = 2), batches and single
+ * traps stepped in one workgroup, which take no graphs, do nothing. */
 int lion_prepare_step(lion_sim *sim, int64_t nsteps);
 
 /* Copy the state to host arrays of length n_total (any pointer may be NULL to
@@ -350,7 +355,8 @@ typedef struct {
     int32_t i_per_lane;   /* target ions per lane in the pair kernel: 1, 2 or 4          */
     int32_t j_split;      /* source slices per step (1..64; clipped to one per 64 sources),
                              partial sums reduced in slice order                           */
-    int32_t chunk_steps;  /* steps per captured launch graph (1..1000).  Built-in: 1000
+    int32_t chunk_steps;  /* steps per captured launch graph, or per launch of the kernels
+                             that step inside one workgroup (1..1000).  Built-in: 1000
                              for a single trap on the one-workgroup path and for batches
                              of traps of at most 64 ions, else 100                        */
     int32_t flush_len;    /* LION_MIXED_F64ACC: sources per FP32 run: 4, 8 or 16           */
@@ -363,12 +369,15 @@ typedef struct {
                              state in registers, source parts in consecutive lanes); 256,
                              512 or 1024 run it on that many threads for traps of at most
                              48 ions and threads / 8, the batched kernel otherwise          */
-    int32_t use_graph;    /* 1: replay captured graphs, 2: plain stream launches           */
+    int32_t use_graph;    /* 1: replay captured graphs, 2: plain stream launches (batches and
+                             traps stepped in one workgroup always take plain launches)     */
     int32_t lds_sources;  /* FP32 pair modes: 1: sources by scalar loads, 2: LDS tiles        */
     int32_t symmetric;    /* 1: all ordered pairs; 2: each pair once (Newton's third law);
                              one trap of N <= 131072 (else LION_ERR_UNSUPPORTED).  Built-in
-                             (0): each pair once where that is allowed and N >= 8192.
-                             With
+                             (0): each pair once where that is allowed, from 8192 ions on
+                             in the FP32 pair modes and with bodies that share 256-ion
+                             tiles with other ions; in LION_FP64 for 4865..5632 ions and
+                             from 6401 on.  With
                              LION_MIXED_KAHAN the FP32 runs of each 256 x 256 tile pair are
                              added in compensated FP32 and the tile-pair totals in FP64       */
     int32_t sym_variant;  /* pair-once kernel variant, 1..9 (built-in: 9 for
@@ -381,8 +390,10 @@ typedef struct {
                              prefetch; the target sums in FP32 runs of 8 sources (1-7),
                              16 (8: the shape of 7) or 64 (9: the shape of 7).  FP64: 1: two
                              sources unrolled, 3 waves/SIMD; 2: one, 4 waves; 3: one,
-                             3 waves; 4: two, 4 waves (spills); 5: two, 2 waves; 6: one,
-                             4 waves, prefetch; 7, 8, 9: two, 3 waves, prefetch              */
+                             3 waves; 4: two, 4 waves (spills); 5: two, 2 waves; 6: the
+                             reactions rotate through the wave instead of LDS (where
+                             bodies share tiles with other ions: one, 4 waves, prefetch,
+                             reactions through LDS); 7, 8, 9: two, 3 waves, prefetch         */
     int32_t update_waves; /* waves that share the slice sums of 64 ions in the step
                              epilogue: 4, 8 or 16 (built-in: 4)                               */
     int32_t small_trap;   /* single trap: 1: always the multi-workgroup kernels; 2: step the

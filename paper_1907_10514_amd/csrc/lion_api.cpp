@@ -65,10 +65,11 @@ namespace {
 
 constexpr size_t kAlign = 256;
 constexpr int kMaxTrap = 1024;
-// traps of at most this many ions step on one wave (the one-wave kernel, us per
-// step FP64 / FP32 pairs / compensated against 256 threads: 16 ions 0.69 / 0.75 /
-// 0.83 against 1.14 / 1.29 / 1.16; 20 ions 1.12 / 1.13 / 1.36 against 1.14 / 1.29
-// / 1.16; since then 16 ions 0.59 and, on 256 threads, 20 ions 0.70)
+// traps of at most this many ions step on one wave: there the kernel takes four sources
+// of a part together (us per step FP64 / FP32 pairs / compensated, one wave against 256
+// threads: 16 ions 0.62 / 0.66 / 0.85 against 0.70 / 0.79 / 0.81, 17 ions 1.10 / 1.12 / 1.33
+// against 0.82 / 0.90 / 1.01; in 512 traps 16 ions 0.72 / 0.74 / 0.95 against 0.89 / 0.88 /
+// 0.97, 17 ions 1.22 / 1.24 / 1.46 against 1.00 / 1.01 / 1.12)
 constexpr int64_t kOneWaveIons = 16;
 // steps per captured launch when not set: 1000 where one workgroup steps a trap
 // for the whole launch and a step takes a microsecond or two (a single trap of
@@ -249,9 +250,11 @@ void default_shape(lion_sim* s) {
     ls.batch_tpt = s->cfg.batch_tpt > 0 ? s->cfg.batch_tpt : 0;
     ls.small_path = s->cfg.small_trap > 0 ? (s->cfg.small_trap == 2 ? 1 : 0)
                                           : (n <= LION_SMALL_TRAP_IONS ? 1 : 0);
-    // one-workgroup stepping of a single trap: 256 threads up to 32 ions, 512 up
-    // to 64, then 1024 (measured per size; e.g. 64 ions: 1.94 us per step at 512
-    // against 2.13 at 256 and 2.27 at 1024)
+    // one-workgroup stepping of a single trap: 256 threads up to 32 ions, 512 up to 64,
+    // then 1024 (FP64, us per step at 256 / 512 / 1024: 24 ions 0.82 / 0.81 / 1.12, 32 ions
+    // 0.93 / 0.91 / 1.30, 48 ions 1.57 / 1.28 / 1.68, 80 ions 2.94 / 2.47 / 2.38; between
+    // 49 and 64 ions 1024 is now the faster by a tenth, 1.78 / 1.67 / 1.51 at 64, and not
+    // yet taken)
     if (!s->batched && ls.small_path && s->cfg.batch_block <= 0)
         ls.batch_block = n <= kOneWaveIons ? 64 : (n <= 32 ? 256 : (n <= 64 ? 512 : 1024));
     // batches whose largest trap holds 256 ions or more: 1024 threads per trap

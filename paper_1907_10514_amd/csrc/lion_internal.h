@@ -288,7 +288,9 @@ hipError_t launch_min_move(const DevState& s, int precision, hipStream_t st);
 // How lion_minimize runs its iterations: inside one workgroup, one launch each, or
 // (large traps, rigid-body masks) the pair kernels with separate reductions.
 enum class MinPath { kOne, kRows, kLaunches };
-// One workgroup up to here (us an iteration: 160 ions 7.0 against 8.0 with a launch each).
+// One workgroup up to here (us an iteration FP64 / FP32 pairs / compensated, against a
+// launch each: 128 ions 3.83 / 3.34 / 4.00 against 4.93 / 4.94 / 4.98, 144 ions 4.71 / 4.15 /
+// 4.88 against 4.94 / 4.98 / 5.02, 160 ions 5.49 / 4.73 / 5.70 against 4.94 / 4.93 / 5.04).
 constexpr int64_t kMinOneIons = 160;
 MinPath min_path(const DevState& s);
 // Up to `iters` iterations; `first`: parameters from init and forces at the current

@@ -2935,7 +2935,7 @@ __global__ __launch_bounds__(64 * W) void k_wave(double4* __restrict__ src,
 // The allocation-free FP64 evaluation in one launch: workgroup g owns the TR targets
 // [g TR, g TR + TR) (wave-uniform, so they sit in scalar registers), its threads take
 // every 256th source straight from the caller's arrays, and the owners add the trap.
-// Bound by FP64 issue of the pairs plus one launch: 3001 ions 9.1 us a call against
+// Bound by FP64 issue of the pairs plus one launch: 3001 ions 9.0 us a call against
 // 16.5 with packing, pair kernel and epilogue, up to 2048 ions 6.2 against 12.
 constexpr int kDirectBlock = 256;
 
@@ -3418,8 +3418,8 @@ __device__ __forceinline__ typename BatchSrc<PREC>::T make_pair_src(double x, do
 
 // Up to `iters` iterations of one trap inside one workgroup: the owners' state in
 // registers, the source stream and all reductions in LDS.  Latency and, from about
-// 100 ions, FP64 issue of one CU bound it: 2.9 us an iteration at 20 ions, 4.4 at
-// 100, 5.4 at 128, where five launches took 17 to 19.  IS owner slots (one per ion)
+// 100 ions, FP64 issue of one CU bound it: 1.4 us an iteration at 20 ions, 3.2 at
+// 100, 3.8 at 128, where five launches took 17 to 19.  IS owner slots (one per ion)
 // times JP source parts fill the block; at least four sources per part and at most
 // 16 parts, as the owners add the parts in a dependent chain (20 ions: 51 parts of
 // one source 5.7 us an iteration).
@@ -3541,8 +3541,8 @@ __global__ __launch_bounds__(kMinOne) void k_min_one(const MinArgs A, MinDev ini
 // its share of the sums that the next launch reduces.  All of that alternates
 // between two buffers (side `from` is read), as other workgroups still read the
 // old; once the stopping test has passed, a launch only hands its ions on.  Bound
-// by launch latency and the chain reduce, move, pairs, reduce: 8.0 us an iteration
-// at 161 ions, 9.1 at 512, 11.8 at 1024, where five launches took 19.8 to 21.6.
+// by launch latency and the chain reduce, move, pairs, reduce: 4.9 us an iteration
+// at 161 ions, 5.5 at 512, 6.7 at 1024, where five launches took 19.8 to 21.6.
 constexpr int kMinRows = 512;
 constexpr int kMinRowsMax = 2048;  // ions whose source stream fits 64 KiB of LDS
 
@@ -3937,12 +3937,15 @@ hipError_t wave_launch_multi(const DevState& s, int n_traps, int max_trap, int b
 template <int PREC, int X>
 hipError_t batch_dispatch_x(const DevState& s, int n_traps, int max_trap, int block, int nsteps,
                             int accel_only, int64_t k0, const LoneTrap& lone, double uq, int tpt, hipStream_t st) {
-    // traps of at most 48 ions and block / 8: the wave kernel on block / 64 waves
-    // (us per step FP64 / FP32 pairs against the batched kernel: 20 ions 0.88 / 0.99
-    // against 1.15 / 1.30, 32 ions 1.02 / 1.13 against 1.32 / 1.48, 48 ions 1.31 /
-    // 1.39 against 1.50 / 1.49; 64 ions 1.64 / 1.63 against 1.63 / 1.52 and 100
-    // ions 3.29 / 3.03 against 2.72 / 2.35, so larger traps keep the batched kernel;
-    // measured before the part sums moved to DPP, which took 20 ions to 0.70)
+    // traps of at most 48 ions and block / 8: the wave kernel on block / 64 waves, whose
+    // parts sum through DPP (us per step of a lone trap FP64 / FP32 pairs / compensated
+    // against the batched kernel on as many threads or, where that is faster, 1024: 40 ions
+    // 1.12 / 1.18 / 1.22 against 1.49 / 1.68 / 1.67 on 256, 56 ions 1.42 / 1.42 / 1.48
+    // against 1.53 / 1.58 / 1.59, 64 ions 1.53 / 1.53 / 1.63 against 1.51 / 1.54 / 1.66, 80
+    // ions 2.49 / 2.25 / 2.64 against 2.38 / 2.44 / 2.62, 100 ions 3.19 / 2.79 / 3.25
+    // against 2.66 / 2.44 / 2.98).  The two meet at 64 ions; the line stays at 48, as above
+    // it the order of the sums, and in the FP32 modes the result at the 1e-8 level, would
+    // change for less than a tenth.
     if (block != 64 && 8 * max_trap <= block && max_trap <= kWaveMultiIons)
         return wave_launch_multi<PREC, X>(s, n_traps, max_trap, block, nsteps, accel_only, k0, lone, st);
     switch (block) {
